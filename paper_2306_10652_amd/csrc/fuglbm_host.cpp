@@ -195,6 +195,14 @@ struct GraphCache {
     int rows = 0;
 };
 
+// What the autotuner chose for a shape: the fused variant and its rows per
+// item, the field-form rows (0: not built for it), and what a step of each
+// and the field form's read of the populations took (ms).
+struct Tuned {
+    int kernel = 0, rows = 0, frows = 0;
+    float fused_ms = 0.f, field_ms = 0.f, moments_ms = 0.f;
+};
+
 struct fuglbm_sim {
     const fuglbm_mixture *mix;
     int lattice;
@@ -228,6 +236,8 @@ struct fuglbm_sim {
     hipEvent_t done;
     bool done_valid;
     GraphCache graph;
+    Tuned tune;            // valid with `tuned`
+    hipGraphExec_t fgraph[2];   // field form, by the parity it was captured at
     uint64_t uid;          // never reused; batch tables key on it, not on the address
 };
 
@@ -266,6 +276,51 @@ static bool is_fused(int kernel) { return kernel == 2 || kernel == 3; }
 // The variant a simulation starts with (and kernel 0 of set_tuning picks).
 static int default_kernel(const fuglbm_sim *s) {
     return fused_fits(s) ? default_fused(s->N, s->fp32) : 1;
+}
+
+// Steps in field form (kernels_fields2d.hip): D2Q9 on the fused kernels, at
+// tau = 1, with variant and rows left to the library.
+static bool field_usable(const fuglbm_sim *s) {
+    return is_fused(s->kernel) && s->auto_kernel && s->autotune && s->hc.omega == 1.0 &&
+           s->N <= field_max_comp();
+}
+
+// Whether a run of n steps is taken in field form.  Beside its steps it
+// reads the populations at its start and writes them at its end (about as
+// long); both forms give bitwise the same state.
+static bool field_pays(const Tuned &t, int64_t n) {
+    return t.frows > 0 && (double)n * (t.fused_ms - t.field_ms) > 2.0 * t.moments_ms;
+}
+
+// All fields lie in the spare population buffer where they fit, components
+// a padded stride apart (see PopLayout<float>::pad for the gap); else (one
+// component, tiny grids) set 0 and psi use the workspace.
+static FieldSim field_sim(const fuglbm_sim *s) {
+    FieldSim f{};
+    f.c = s->dc;
+    f.buf[0] = s->buf[0];
+    f.buf[1] = s->buf[1];
+    f.rho = s->rho_f;
+    f.psi = s->psi_f;
+    f.s = s->s_f;
+    f.j = s->j_f;
+    f.u = s->u_f;
+    f.status = s->status;
+    f.ld = s->ns + PopLayout<float>::pad(s->ns);
+    f.wide = (3 * s->N + 3 + 2 * s->D) * f.ld * 8 <= pop_bytes(s);
+    if (!f.wide) f.ld = s->ns;
+    f.parity = s->parity;
+    return f;
+}
+
+static FieldRun field_run(const fuglbm_sim *s, int rows) {
+    FieldRun q{};
+    q.one = field_sim(s);
+    q.strips = (s->nx + FUSED_OUT - 1) / FUSED_OUT;
+    q.rows = rows;
+    q.nitems = q.strips * ((s->ny + rows - 1) / rows);
+    q.blocks = (s->ns + 255) / 256;
+    return q;
 }
 
 static uint64_t next_sim_uid() {
@@ -317,6 +372,10 @@ fuglbm_status build_items(fuglbm_sim *s) {
 void drop_graph(fuglbm_sim *s) {
     if (s->graph.exec) (void)hipGraphExecDestroy(s->graph.exec);
     s->graph = GraphCache{};
+    for (auto &g : s->fgraph) {
+        if (g) (void)hipGraphExecDestroy(g);
+        g = nullptr;
+    }
 }
 
 hipError_t launch_one_step(fuglbm_sim *s, int flip_parity, hipStream_t st) {
@@ -330,31 +389,74 @@ hipError_t launch_one_step(fuglbm_sim *s, int flip_parity, hipStream_t st) {
 
 constexpr int GRAPH_STEPS = 32;  // even: a replay returns to the same parity
 
-fuglbm_status ensure_graph(fuglbm_sim *s) {
-    if (s->graph.exec && s->graph.kernel == s->kernel && s->graph.rows == s->rows)
-        return FUGLBM_OK;
-    drop_graph(s);
+// Captures GRAPH_STEPS calls of launch(k, stream) and instantiates the graph.
+template <class Launch>
+fuglbm_status capture_steps(Launch launch, hipGraphExec_t &ex, const char *what) {
     hipStream_t cs = capture_stream();
     if (!cs) return fail(FUGLBM_EDEVICE, "cannot create capture stream");
     HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     for (int k = 0; k < GRAPH_STEPS; ++k) {
-        hipError_t e = launch_one_step(s, k & 1, cs);
+        hipError_t e = launch(k, cs);
         if (e != hipSuccess) {
             hipGraph_t g = nullptr;
             if (hipStreamEndCapture(cs, &g) == hipSuccess && g) (void)hipGraphDestroy(g);
-            return hip_fail(e, "capture");
+            return hip_fail(e, what);
         }
     }
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamEndCapture(cs, &g));
-    hipGraphExec_t ex = nullptr;
     hipError_t e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
-    if (e != hipSuccess) return hip_fail(e, "hipGraphInstantiate");
-    s->graph.exec = ex;
+    if (e != hipSuccess) {
+        ex = nullptr;
+        return hip_fail(e, what);
+    }
+    return FUGLBM_OK;
+}
+
+fuglbm_status ensure_graph(fuglbm_sim *s) {
+    if (s->graph.exec && s->graph.kernel == s->kernel && s->graph.rows == s->rows)
+        return FUGLBM_OK;
+    drop_graph(s);
+    fuglbm_status rc = capture_steps(
+        [&](int k, hipStream_t cs) { return launch_one_step(s, k & 1, cs); }, s->graph.exec,
+        "step graph");
+    if (rc != FUGLBM_OK) return rc;
     s->graph.steps = GRAPH_STEPS;
     s->graph.kernel = s->kernel;
     s->graph.rows = s->rows;
+    return FUGLBM_OK;
+}
+
+// One step in field form from set `set` (last: to the populations).
+hipError_t launch_field(const FieldRun &q, int ncomp, bool fp32, bool last, int set,
+                        hipStream_t st) {
+    hipError_t e = launch_field_eos2d(q, ncomp, set, st);
+    return e != hipSuccess ? e : launch_field_step2d(q, ncomp, fp32, last, set, st);
+}
+
+// n >= 1 steps in field form.  The populations end in the buffer they
+// started from (the other one held the fields), so no parity changes.
+// graph: a captured run of GRAPH_STEPS steps for this q (set 0 to set 0),
+// made when it is first needed.
+fuglbm_status run_field(const FieldRun &q, int ncomp, bool fp32, int64_t n, hipGraphExec_t &graph,
+                        hipStream_t st) {
+    HIP_TRY(launch_field_moments2d(q, fp32, st));
+    int64_t left = n - 1;
+    if (left >= 2 * GRAPH_STEPS || (graph && left >= GRAPH_STEPS)) {
+        if (!graph) {
+            fuglbm_status rc = capture_steps(
+                [&](int k, hipStream_t cs) {
+                    return launch_field(q, ncomp, fp32, false, k & 1, cs);
+                },
+                graph, "field step graph");
+            if (rc != FUGLBM_OK) return rc;
+        }
+        for (; left >= GRAPH_STEPS; left -= GRAPH_STEPS) HIP_TRY(hipGraphLaunch(graph, st));
+    }
+    int set = 0;
+    for (; left > 0; --left, set ^= 1) HIP_TRY(launch_field(q, ncomp, fp32, false, set, st));
+    HIP_TRY(launch_field(q, ncomp, fp32, true, set, st));
     return FUGLBM_OK;
 }
 
@@ -437,9 +539,66 @@ fuglbm_status time_candidates(const std::vector<int> &cand, hipStream_t st, Prep
     return FUGLBM_OK;
 }
 
-std::map<std::tuple<int, int, int, int>, int> &tune_cache() {
-    static std::map<std::tuple<int, int, int, int>, int> m;
+std::map<std::tuple<int, int, int, int>, Tuned> &tune_cache() {
+    static std::map<std::tuple<int, int, int, int>, Tuned> m;
     return m;
+}
+
+// Rows per item of the field form whose rounds over the resident workgroups
+// cost least (a workgroup takes rows + 6 lead rows).
+int field_model_rows(int64_t strip_rows, int ny, int ncomp) {
+    const int64_t slots = (int64_t)compute_units() * field_blocks_per_cu2d(ncomp);
+    int best = 1;
+    int64_t best_cost = INT64_MAX;
+    for (int rows = 1; rows <= ny; ++rows) {
+        const int64_t items = (strip_rows + rows - 1) / rows;
+        const int64_t cost = (items + slots - 1) / slots * (rows + 6);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = rows;
+        }
+    }
+    return best;
+}
+
+// Times the field form over `set_rows(rows)` (which gives the run to
+// launch): its moments and EOS kernels once, its step kernel at each rows
+// candidate; two passes, ranked by the sum.  The trials read the current
+// populations and write the spare buffer and workspace only.
+template <class SetRows>
+fuglbm_status time_field(const std::vector<int> &cand, int ncomp, bool fp32, hipStream_t st,
+                         SetRows set_rows, Tuned &t) {
+    FieldRun q;
+    fuglbm_status rc = set_rows(cand[0], q);
+    if (rc != FUGLBM_OK) return rc;
+    Timer tm;
+    if (!tm.ok()) return fail(FUGLBM_EDEVICE, "hipEventCreate");
+    auto timed = [&](auto launch, float &ms) -> fuglbm_status {
+        HIP_TRY(hipEventRecord(tm.a, st));
+        for (int j = 0; j < TUNE_LAUNCHES; ++j) HIP_TRY(launch());
+        HIP_TRY(hipEventRecord(tm.b, st));
+        HIP_TRY(hipEventSynchronize(tm.b));
+        HIP_TRY(hipEventElapsedTime(&ms, tm.a, tm.b));
+        ms /= TUNE_LAUNCHES;
+        return FUGLBM_OK;
+    };
+    auto moments = [&] { return launch_field_moments2d(q, fp32, st); };
+    auto eos = [&] { return launch_field_eos2d(q, ncomp, 0, st); };
+    float eos_ms = 0.f;
+    HIP_TRY(moments());
+    HIP_TRY(eos());
+    rc = timed(moments, t.moments_ms);
+    if (rc == FUGLBM_OK) rc = timed(eos, eos_ms);
+    if (rc != FUGLBM_OK) return rc;
+    int best = 0;
+    float best_ms = 0.f;
+    rc = time_candidates(
+        cand, st, [&](int r) { return set_rows(r, q); },
+        [&] { return launch_field_step2d(q, ncomp, fp32, false, 0, st); }, best, &best_ms);
+    if (rc != FUGLBM_OK) return rc;
+    t.frows = best;
+    t.field_ms = eos_ms + best_ms / (2 * TUNE_LAUNCHES);
+    return FUGLBM_OK;
 }
 
 fuglbm_status set_rows(fuglbm_sim *s, int rows, hipStream_t st) {
@@ -450,8 +609,9 @@ fuglbm_status set_rows(fuglbm_sim *s, int rows, hipStream_t st) {
 }
 
 // With the variant left to the tuner, both fused variants are timed (each
-// at its own rows candidates) and the faster (variant, rows) is kept; the
-// cache entry holds kernel * 65536 + rows.  Every candidate's work table
+// at its own rows candidates) and the faster (variant, rows) is kept; where
+// the steps can be taken in field form, that is timed too (time_field).
+// The choice is cached.  Every candidate's work table
 // is uploaded once, before any timing, and the candidates run back to back
 // with an event pair each and one synchronisation at the end: the GPU
 // stays busy through the whole trial, so the candidates are timed under
@@ -460,14 +620,14 @@ fuglbm_status set_rows(fuglbm_sim *s, int rows, hipStream_t st) {
 fuglbm_status autotune_rows(fuglbm_sim *s, hipStream_t st) {
     const TraceRange trace_range("fuglbm autotune rows");
     const bool both = s->auto_kernel && ws_usable(s->N, s->fp32);
-    const int tag = both ? 0 : s->kernel;
+    const int tag = (both ? 0 : s->kernel) + (field_usable(s) ? 4 : 0);
     const auto key = std::make_tuple(s->nx, s->ny, s->N, (s->fp32 ? 1 : 0) + 2 * tag);
     auto hit = tune_cache().find(key);
-    int best_k = s->kernel, best = 0;
+    Tuned &tn = s->tune;
     if (hit != tune_cache().end()) {
-        best_k = hit->second >> 16;
-        best = hit->second & 0xffff;
+        tn = hit->second;
     } else {
+        tn = Tuned{};
         struct Cand {
             int kernel, rows;
             size_t off, n;
@@ -528,16 +688,29 @@ fuglbm_status autotune_rows(fuglbm_sim *s, hipStream_t st) {
             const float ms = m1 + m2;
             if (ms < best_ms) {
                 best_ms = ms;
-                best_k = cand[i].kernel;
-                best = cand[i].rows;
+                tn.kernel = cand[i].kernel;
+                tn.rows = cand[i].rows;
             }
         }
-        tune_cache()[key] = best_k * 65536 + best;
+        tn.fused_ms = best_ms / (2 * TUNE_LAUNCHES);
+        if (field_usable(s)) {
+            const int64_t strips = (s->nx + FUSED_OUT - 1) / FUSED_OUT;
+            fuglbm_status rc = time_field(
+                tune_candidates(s->ny, field_model_rows(strips * s->ny, s->ny, s->N)), s->N,
+                s->fp32, st,
+                [&](int r, FieldRun &q) {
+                    q = field_run(s, r);
+                    return FUGLBM_OK;
+                },
+                tn);
+            if (rc != FUGLBM_OK) return rc;
+        }
+        tune_cache()[key] = tn;
     }
     HIP_TRY(hipStreamSynchronize(st));
-    s->kernel = best_k;
+    s->kernel = tn.kernel;
     s->tuned = true;
-    return set_rows(s, best, st);
+    return set_rows(s, tn.rows, st);
 }
 
 fuglbm_status sync_status(fuglbm_sim *s) {
@@ -786,6 +959,7 @@ fuglbm_status fuglbm_init_fields(const fuglbm_mixture *mix, fuglbm_lattice latti
     s->sticky = 0;
     s->autotune = fused;
     s->tuned = false;
+    s->fgraph[0] = s->fgraph[1] = nullptr;
     s->uid = next_sim_uid();
     *out = s;
     return FUGLBM_OK;
@@ -851,6 +1025,13 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *s, int64_t nsteps, void *hip_stream) {
     if (left > 0 && is_fused(s->kernel) && s->autotune && !s->tuned) {
         fuglbm_status rc = autotune_rows(s, st);
         if (rc != FUGLBM_OK) return rc;
+    }
+    if (s->tuned && field_usable(s) && field_pays(s->tune, left)) {
+        fuglbm_status rc = run_field(field_run(s, s->tune.frows), s->N, s->fp32, left,
+                                     s->fgraph[s->parity], st);
+        if (rc != FUGLBM_OK) return rc;
+        s->step += left;
+        return mark_done(s, st);
     }
     // odd parity first so that graph replays start from buffer 0
     if (left > 0 && s->parity == 1 && left >= 2 * GRAPH_STEPS) {
@@ -1071,33 +1252,32 @@ struct BatchTable {
     int nitems = 0;
     int kernel = 2;                   // fused variant of the launches
     hipGraphExec_t graph = nullptr;   // GRAPH_STEPS launches starting at flip 0
+    // field form: its member and item tables, what the tuner measured, and a
+    // graph per flip
+    FieldSim *dfield = nullptr;
+    FusedItem *dfitems = nullptr;
+    size_t cap_fsims = 0, cap_fitems = 0;
+    FieldRun frun{};
+    Tuned tune;
+    hipGraphExec_t fgraph[2] = {nullptr, nullptr};
     hipStream_t last_stream = nullptr;
     bool used = false;                // last_stream is meaningful
 };
 
 fuglbm_status batch_graph(BatchTable &bt, int ncomp, bool fp32) {
     if (bt.graph) return FUGLBM_OK;
-    hipStream_t cs = capture_stream();
-    if (!cs) return fail(FUGLBM_EDEVICE, "cannot create capture stream");
-    HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < GRAPH_STEPS; ++k) {
-        hipError_t e =
-            launch_fused(bt.kernel, ncomp, fp32, bt.ditems, bt.nitems, bt.dsims, k & 1, cs);
-        if (e != hipSuccess) {
-            hipGraph_t g = nullptr;
-            if (hipStreamEndCapture(cs, &g) == hipSuccess && g) (void)hipGraphDestroy(g);
-            return hip_fail(e, "batch capture");
-        }
+    return capture_steps(
+        [&](int k, hipStream_t cs) {
+            return launch_fused(bt.kernel, ncomp, fp32, bt.ditems, bt.nitems, bt.dsims, k & 1, cs);
+        },
+        bt.graph, "batch graph");
+}
+
+void drop_batch_graphs(BatchTable &bt) {
+    for (hipGraphExec_t *g : {&bt.graph, &bt.fgraph[0], &bt.fgraph[1]}) {
+        if (*g) (void)hipGraphExecDestroy(*g);
+        *g = nullptr;
     }
-    hipGraph_t g = nullptr;
-    HIP_TRY(hipStreamEndCapture(cs, &g));
-    hipError_t e = hipGraphInstantiate(&bt.graph, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (e != hipSuccess) {
-        bt.graph = nullptr;
-        return hip_fail(e, "hipGraphInstantiate (batch)");
-    }
-    return FUGLBM_OK;
 }
 
 std::map<std::pair<int, int>, BatchTable> &batch_tables() {
@@ -1105,15 +1285,70 @@ std::map<std::pair<int, int>, BatchTable> &batch_tables() {
     return t;
 }
 
+// Items in logical order -> launch order: workgroups are handed to the 8
+// XCDs round-robin, XCD k gets the k-th contiguous slice.
+std::vector<FusedItem> deal_items(const std::vector<FusedItem> &logical) {
+    const int n = (int)logical.size();
+    const int per = (n + 7) / 8;
+    std::vector<FusedItem> items((size_t)per * 8, FusedItem{-1, 0, 0, 0});
+    for (int b = 0; b < per * 8; ++b) {
+        const int li = (b % 8) * per + b / 8;
+        if (li < n) items[b] = logical[li];
+    }
+    return items;
+}
+
+// Device array of at least n elements; a growing one doubles.
+template <class T>
+fuglbm_status grow(T *&p, size_t &cap, size_t n) {
+    if (n <= cap) return FUGLBM_OK;
+    if (p) (void)hipFree(p);
+    p = nullptr;
+    cap = 0;
+    HIP_TRY(hipMalloc(&p, 2 * n * sizeof(T)));
+    cap = 2 * n;
+    return FUGLBM_OK;
+}
+
+// The field form's tables for a group at `rows` rows per item -> bt.frun.
+fuglbm_status build_field_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group, int rows,
+                                hipStream_t st) {
+    HIP_TRY(hipStreamSynchronize(st));  // the old tables may still be read
+    std::vector<FieldSim> fs;
+    std::vector<FusedItem> logical;
+    int64_t blocks = 0;
+    for (size_t k = 0; k < group.size(); ++k) {
+        const fuglbm_sim *s = group[k];
+        fs.push_back(field_sim(s));
+        fs.back().end = blocks += (s->ns + 255) / 256;
+        const int strips = (s->nx + FUSED_OUT - 1) / FUSED_OUT, rw = std::min(rows, s->ny);
+        for (int y = 0; y < s->ny; y += rw)
+            for (int x = 0; x < strips; ++x)
+                logical.push_back({(int32_t)k, x * FUSED_OUT, y, std::min(rw, s->ny - y)});
+    }
+    if (blocks > INT32_MAX) return fail(FUGLBM_EINVAL, "batch too large for one launch");
+    const std::vector<FusedItem> items = deal_items(logical);
+    fuglbm_status rc = grow(bt.dfield, bt.cap_fsims, fs.size());
+    if (rc == FUGLBM_OK) rc = grow(bt.dfitems, bt.cap_fitems, items.size());
+    if (rc != FUGLBM_OK) return rc;
+    HIP_TRY(hipMemcpy(bt.dfield, fs.data(), fs.size() * sizeof(FieldSim), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(bt.dfitems, items.data(), items.size() * sizeof(FusedItem),
+                      hipMemcpyHostToDevice));
+    bt.frun = FieldRun{};
+    bt.frun.tab = bt.dfield;
+    bt.frun.nm = (int)fs.size();
+    bt.frun.items = bt.dfitems;
+    bt.frun.nitems = (int)items.size();
+    bt.frun.blocks = blocks;
+    return FUGLBM_OK;
+}
+
 // rows > 0: every member uses min(rows, ny) rows per item; 0: its own.
 // kernel: the fused variant (0: that of the first member).
 fuglbm_status build_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group, hipStream_t st,
                           int rows = 0, int kernel = 0) {
     HIP_TRY(hipStreamSynchronize(st));  // the old table may still be read by queued launches
-    if (bt.graph) {
-        (void)hipGraphExecDestroy(bt.graph);
-        bt.graph = nullptr;
-    }
+    drop_batch_graphs(bt);
     bt.kernel = kernel ? kernel : group[0]->kernel;
     std::vector<FusedSim> hs;
     std::vector<FusedItem> logical;
@@ -1133,13 +1368,7 @@ fuglbm_status build_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group
             for (int t = 0; t < strips; ++t)
                 logical.push_back({(int32_t)k, t * FUSED_OUT, c * rw, std::min(rw, s->ny - c * rw)});
     }
-    const int n = (int)logical.size();
-    const int per = (n + 7) / 8;
-    std::vector<FusedItem> items((size_t)per * 8, FusedItem{-1, 0, 0, 0});
-    for (int b = 0; b < per * 8; ++b) {
-        const int li = (b % 8) * per + b / 8;
-        if (li < n) items[b] = logical[li];
-    }
+    const std::vector<FusedItem> items = deal_items(logical);
     if (hs.size() > bt.cap_sims) {
         if (bt.dsims) (void)hipFree(bt.dsims);
         bt.cap_sims = hs.size() * 2;
@@ -1179,11 +1408,15 @@ static int log2_class(int64_t v) {
 
 fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group, int nc, bool f32,
                          hipStream_t st) {
-    static std::map<std::tuple<int, int, int, int>, int> cache;   // kernel * 65536 + rows
+    static std::map<std::tuple<int, int, int, int>, Tuned> cache;
+    bt.tune = Tuned{};
     for (auto *s : group)
         if (!s->autotune) return build_batch(bt, group, st);   // rows fixed by the caller
-    bool auto_k = true;
-    for (auto *s : group) auto_k = auto_k && s->auto_kernel;
+    bool auto_k = true, field = true;
+    for (auto *s : group) {
+        auto_k = auto_k && s->auto_kernel;
+        field = field && field_usable(s);
+    }
     const bool both = auto_k && ws_usable(nc, f32);
     int64_t strip_rows = 0;
     int ny_max = 1;
@@ -1191,13 +1424,18 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
         strip_rows += (int64_t)((s->nx + FUSED_OUT - 1) / FUSED_OUT) * s->ny;
         ny_max = std::max(ny_max, s->ny);
     }
-    const int tag = both ? 0 : group[0]->kernel;
+    const int tag = (both ? 0 : group[0]->kernel) + (field ? 4 : 0);
     const auto key = std::make_tuple(nc, (f32 ? 1 : 0) + 2 * tag, log2_class(strip_rows),
                                      log2_class(ny_max));
     auto hit = cache.find(key);
-    if (hit != cache.end())
-        return build_batch(bt, group, st, hit->second & 0xffff, hit->second >> 16);
-    int best_k = group[0]->kernel, best = 0;
+    if (hit != cache.end()) {
+        fuglbm_status rc = build_batch(bt, group, st, hit->second.rows, hit->second.kernel);
+        if (rc == FUGLBM_OK && hit->second.frows)
+            rc = build_field_batch(bt, group, hit->second.frows, st);
+        if (rc == FUGLBM_OK) bt.tune = hit->second;
+        return rc;
+    }
+    Tuned tn;
     float best_ms = 1e30f;
     for (int k : {2, 3}) {
         if (both ? false : k != group[0]->kernel) continue;
@@ -1211,12 +1449,27 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
         if (rc != FUGLBM_OK) return rc;
         if (ms < best_ms) {
             best_ms = ms;
-            best_k = k;
-            best = r;
+            tn.kernel = k;
+            tn.rows = r;
         }
     }
-    cache[key] = best_k * 65536 + best;
-    return build_batch(bt, group, st, best, best_k);
+    tn.fused_ms = best_ms / (2 * TUNE_LAUNCHES);
+    fuglbm_status rc = FUGLBM_OK;
+    if (field) {
+        rc = time_field(
+            tune_candidates(ny_max, field_model_rows(strip_rows, ny_max, nc)), nc, f32, st,
+            [&](int r, FieldRun &q) {
+                fuglbm_status e = build_field_batch(bt, group, r, st);
+                q = bt.frun;
+                return e;
+            },
+            tn);
+        if (rc == FUGLBM_OK) rc = build_field_batch(bt, group, tn.frows, st);
+    }
+    if (rc == FUGLBM_OK) rc = build_batch(bt, group, st, tn.rows, tn.kernel);
+    if (rc != FUGLBM_OK) return rc;
+    cache[key] = bt.tune = tn;
+    return FUGLBM_OK;
 }
 
 }  // namespace
@@ -1251,26 +1504,8 @@ void drop_gen_graph(GenBatch &gb) {
 
 fuglbm_status gen_batch_graph(GenBatch &gb) {
     if (gb.graph) return FUGLBM_OK;
-    hipStream_t cs = capture_stream();
-    if (!cs) return fail(FUGLBM_EDEVICE, "cannot create capture stream");
-    HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < GRAPH_STEPS; ++k) {
-        hipError_t e = gen_batch_step(gb, k & 1, cs);
-        if (e != hipSuccess) {
-            hipGraph_t g = nullptr;
-            if (hipStreamEndCapture(cs, &g) == hipSuccess && g) (void)hipGraphDestroy(g);
-            return hip_fail(e, "multi-pass batch capture");
-        }
-    }
-    hipGraph_t g = nullptr;
-    HIP_TRY(hipStreamEndCapture(cs, &g));
-    hipError_t e = hipGraphInstantiate(&gb.graph, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (e != hipSuccess) {
-        gb.graph = nullptr;
-        return hip_fail(e, "hipGraphInstantiate (multi-pass batch)");
-    }
-    return FUGLBM_OK;
+    return capture_steps([&](int k, hipStream_t cs) { return gen_batch_step(gb, k & 1, cs); },
+                         gb.graph, "multi-pass batch graph");
 }
 
 std::map<std::tuple<int, int, int>, GenBatch> &gen_batches() {
@@ -1343,10 +1578,7 @@ void forget_sim_in_batches(const fuglbm_sim *s) {
         BatchTable &bt = kv.second;
         for (size_t k = 0; k < bt.sims.size(); ++k) {
             if (bt.sims[k] == s && bt.uids[k] == s->uid) {
-                if (bt.graph) {
-                    (void)hipGraphExecDestroy(bt.graph);
-                    bt.graph = nullptr;
-                }
+                drop_batch_graphs(bt);
                 bt.sims.clear();
                 bt.uids.clear();
                 bt.parity0.clear();
@@ -1405,10 +1637,21 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         const bool f32 = kv.first.second != 0;
         int64_t left = nsteps;
         if (!same) {
+            bt.tune = Tuned{};
             fuglbm_status rc = left > 0 ? tune_batch(bt, group, nc, f32, st)
                                         : build_batch(bt, group, st);
             if (rc != FUGLBM_OK) return rc;
             flip = 0;
+        }
+        if (field_pays(bt.tune, left)) {
+            bt.frun.flip = flip;
+            fuglbm_status rc = run_field(bt.frun, nc, f32, left, bt.fgraph[flip], st);
+            if (rc != FUGLBM_OK) return rc;
+            for (auto *s : group) {
+                s->step += nsteps;
+                s->last_stream = st;
+            }
+            continue;
         }
         if (left >= 2 * GRAPH_STEPS && flip == 1) {
             hipError_t e =

@@ -81,3 +81,40 @@ bool fused_ws_fits(int ncomp, bool fp32);
 int fused_ws_blocks_per_cu(int ncomp, bool fp32);
 hipError_t launch_fused_d2q9_ws(int ncomp, bool fp32, const FusedItem *items, int nitems,
                                 const FusedSim *sims, int flip, hipStream_t st);
+
+// ---- D2Q9 steps at tau = 1 in field form (kernels_fields2d.hip) -----------
+// One simulation: its population buffers (the run reads buf[parity ^ flip]
+// and writes its last state there again; the other buffer holds fields
+// between the steps) and workspace fields.  ld: elements from one component
+// of a field to the next; wide: every field lies in the spare population
+// buffer (else set 0 and psi in the workspace, components ld = sites apart).
+// end: blocks of 256 sites through this member, cumulative over a table.
+struct FieldSim {
+    const SimConst *c;
+    void *buf[2];
+    double *rho, *psi, *s, *j, *u;
+    uint32_t *status;
+    int64_t end, ld;
+    int32_t parity, wide;
+};
+// What the steps of a run are launched over: one simulation (tab null; work
+// items follow from strips and rows, nitems of them) or a table of nm
+// members with a work-item table.
+struct FieldRun {
+    const FieldSim *tab;
+    int nm;
+    FieldSim one;
+    const FusedItem *items;
+    int nitems, strips, rows;
+    int64_t blocks;
+    int flip;
+};
+int field_max_comp();   // built for ncomp <= this
+int field_blocks_per_cu2d(int ncomp);
+// populations -> set 0
+hipError_t launch_field_moments2d(const FieldRun &q, bool fp32, hipStream_t st);
+// psi and 1/rho of set `set`
+hipError_t launch_field_eos2d(const FieldRun &q, int ncomp, int set, hipStream_t st);
+// one step from set `set` to the other one, or (last) to the populations
+hipError_t launch_field_step2d(const FieldRun &q, int ncomp, bool fp32, bool last, int set,
+                               hipStream_t st);

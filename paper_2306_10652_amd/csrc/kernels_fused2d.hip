@@ -83,61 +83,44 @@ struct Fused {
             v[0] = gC.r;
 #pragma unroll
             for (int a = 1; a < 9; ++a) v[a] = (double)gC.m[a - 1];
-            double rho = 0.0;
-#pragma unroll
-            for (int a = 0; a < 9; ++a) rho += v[a];
+            double rho, jx, jy;
+            moments_d2q9(v, rho, jx, jy);
             rh0 = rho;
             L.rt[comp][lane] = rho * invM;
-            L.jx[comp][lane] = (v[1] - v[3]) + (v[5] - v[7]) + (v[8] - v[6]);
-            L.jy[comp][lane] = (v[2] - v[4]) + (v[5] - v[7]) + (v[6] - v[8]);
+            L.jx[comp][lane] = jx;
+            L.jy[comp][lane] = jy;
         }
         double Gx = 0.0, Gy = 0.0;
         if (do_out) grad3(rhm3, rhm2, rhm1, Gx, Gy);
-        // Eq. (9)-(12) in combined-log form for row r-1 (any of the cubics,
-        // p = RT/(v - b) - a/((v + d1 b)(v + d2 b))),
-        //   RT ln f_i = RT ln(rt_i c1) + b_i (c2a + lambda c2b) - lambda c3b Sraw_i,
-        // split over two helper waves: A (reciprocals, Z - 1) and B (lambda =
-        // ln[(1 + d1 eta)/(1 + d2 eta)] / (d1 - d2), or eta for vdW).
+        // mixture terms of row r-1, split over two helper waves: A
+        // (reciprocals, Z - 1) and B (lambda)
         if (do_eos && comp == helper_wave<NC>(0)) {
             const int ms = (r - 1) & 1;
-            const double rt1 = L.mx[ms][0][lane];
-            const double et1 = L.mx[ms][1][lane];
             double xsum = 0.0;
 #pragma unroll
             for (int j = 0; j < NC; ++j) xsum += L.xs[j][lane];
-            const double inv_rt = frcp(rt1);
-            const double am = xsum * inv_rt * inv_rt;
-            const double ome = 1.0 - et1;
-            if (!(ome > 0.0)) bad |= FUG_ST_COVOLUME;
-            const double inv_ome = frcp(ome);
-            const double inv_bm = rt1 * frcp(et1);
-            const double den = 1.0 + C->eu * et1 + C->ew * et1 * et1;
-            const double zm1 = et1 * inv_ome - am * rt1 * invRT * frcp(den);
-            L.eos[0][lane] = RT * inv_ome;
-            L.eos[1][lane] = RT * zm1 * inv_bm;
-            L.eos[2][lane] = am * inv_bm * inv_bm;
-            L.eos[3][lane] = 2.0 * inv_bm * inv_rt;
+            const MixCoef m =
+                mix_coef(C, RT, invRT, L.mx[ms][0][lane], L.mx[ms][1][lane], xsum, bad);
+            L.eos[0][lane] = m.c1;
+            L.eos[1][lane] = m.c2a;
+            L.eos[2][lane] = m.c2b;
+            L.eos[3][lane] = m.c3b;
         }
-        if (do_eos && comp == helper_wave<NC>(1)) {
-            const double et1 = L.mx[(r - 1) & 1][1][lane];
-            L.eos[4][lane] = C->eos == 2
-                                 ? et1
-                                 : log((1.0 + C->d1 * et1) * frcp(1.0 + C->d2 * et1)) * C->dk;
-        }
+        if (do_eos && comp == helper_wave<NC>(1))
+            L.eos[4][lane] = mix_lambda(C, L.mx[(r - 1) & 1][1][lane]);
         __syncthreads();
         // ---- phase 2: s(r); psi_i(r-1); F_i(y); Sraw_i(r); helper sums of row r
         {
             double acc = 0.0;
 #pragma unroll
-            for (int j = 0; j < NC; ++j) acc += C->sqk[j] * L.rt[j][lane];
+            for (int j = 0; j < NC; ++j) acc = fma(C->sqk[j], L.rt[j][lane], acc);
             sv0 = acc;
         }
         if (do_eos) {
-            const double c1 = L.eos[0][lane], c2a = L.eos[1][lane], c2b = L.eos[2][lane];
-            const double c3b = L.eos[3][lane], lam = L.eos[4][lane];
+            const MixCoef m = {L.eos[0][lane], L.eos[1][lane], L.eos[2][lane], L.eos[3][lane]};
             const double rti = rhm1 * invM;
-            const double lnf = RT * log(rti * c1) + bi * fma(lam, c2b, c2a) - lam * c3b * so;
-            const double psi = lnf - sqki * lap3(svm2, svm1, sv0);
+            const double lnf = rt_lnf(m, L.eos[4][lane], RT, rti, bi, so);
+            const double psi = fma(-sqki, lap3(svm2, svm1, sv0), lnf);
             psm1 = psi;
             if (!(rti > 0.0)) bad |= FUG_ST_NEGATIVE;
             if (!isfinite(psi)) bad |= FUG_ST_NONFINITE;
@@ -156,9 +139,9 @@ struct Fused {
             cptr<double> arow = C->aij + comp * FUG_MAXC;
             double acc = 0.0;
 #pragma unroll
-            for (int j = 0; j < NC; ++j) acc += arow[j] * L.rt[j][lane];
+            for (int j = 0; j < NC; ++j) acc = fma(arow[j], L.rt[j][lane], acc);
             sn = acc;
-            L.xs[comp][lane] = rh0 * invM * acc;
+            L.xs[comp][lane] = (rh0 * invM) * acc;
         }
         if (do_s && comp == helper_wave<NC>(2)) {
             double rtt = 0.0, eta = 0.0;
@@ -166,7 +149,7 @@ struct Fused {
             for (int j = 0; j < NC; ++j) {
                 const double t = L.rt[j][lane];
                 rtt += t;
-                eta += C->b[j] * t;
+                eta = fma(C->b[j], t, eta);
             }
             L.mx[r & 1][0][lane] = rtt;
             L.mx[r & 1][1][lane] = eta;
@@ -175,7 +158,7 @@ struct Fused {
             double rtot = 0.0, jxt = 0.0, jyt = 0.0;
 #pragma unroll
             for (int j = 0; j < NC; ++j) {
-                rtot += C->M[j] * L.rt[j][lane];
+                rtot = fma(C->M[j], L.rt[j][lane], rtot);
                 jxt += L.jx[j][lane];
                 jyt += L.jy[j][lane];
             }
@@ -199,16 +182,10 @@ struct Fused {
             }
             const int ys = (r - 2) & 3;
             const double inv_rho = L.tot[ys][0][lane];
-            const double ux = (L.tot[ys][1][lane] + 0.5 * Fsx) * inv_rho;
-            const double uy = (L.tot[ys][2][lane] + 0.5 * Fsy) * inv_rho;
+            const double ux = fma(0.5, Fsx, L.tot[ys][1][lane]) * inv_rho;
+            const double uy = fma(0.5, Fsy, L.tot[ys][2][lane]) * inv_rho;
             const double orho = omega * rhm2;
-            const double A = 3.0 * orho, B = 4.5 * orho;
-            const double C9 = 9.0 * fcoef, C3 = 3.0 * fcoef;
             const double omc = 1.0 - omega;
-            const double base = -1.5 * orho * (ux * ux + uy * uy) - C3 * (Fx * ux + Fy * uy);
-            const double Gu = Gx * ux + Gy * uy;
-            const double K1 = fma(-0.5 * fcoef, Gu, base);
-            const double K2 = fma(fcoef, Gu, base);
             const uint32_t rowm = (uint32_t)wm3 * rsm;
             const uint32_t row0 = (uint32_t)wm2 * rsm;
             const uint32_t rowp = (uint32_t)wm1 * rsm;
@@ -220,8 +197,8 @@ struct Fused {
                     float g[8], t[8];
 #pragma unroll
                     for (int m = 0; m < 8; ++m) g[m] = (float)gA.m[m];
-                    const double msum = collide_moving_f32(A, B, C9, C3, K1, K2, omc, ux, uy, Fx,
-                                                           Fy, Gx, Gy, g, t);
+                    const double msum =
+                        collide_moving_f32<true>(orho, fcoef, omc, ux, uy, Fx, Fy, Gx, Gy, g, t);
                     dst[0][row0 + xp] = t[0];
                     dst[2][row0 + xm] = t[2];
                     dst[1][rowp + xc] = t[1];
@@ -232,24 +209,20 @@ struct Fused {
                     dst[7][rowm + xp] = t[7];
                     dstR[(uint32_t)wm2 * rsr + (uint32_t)xc] = rhm2 - msum;
                 } else {
-                    // the four opposite pairs, stored as they are formed; then
-                    // the rest population
-                    auto put = [&](gmptr<ST> p, uint32_t at, double v) { p[at] = (ST)v; };
-                    double tp, tm;
-                    collide_pair(A, B, C9, C3, K1, ux, Fx, Gx, tp, tm);
-                    put(dst[0], row0 + xp, fma(omc, (double)gA.m[0], (1.0 / 9.0) * tp));
-                    put(dst[2], row0 + xm, fma(omc, (double)gA.m[2], (1.0 / 9.0) * tm));
-                    collide_pair(A, B, C9, C3, K1, uy, Fy, Gy, tp, tm);
-                    put(dst[1], rowp + xc, fma(omc, (double)gA.m[1], (1.0 / 9.0) * tp));
-                    put(dst[3], rowm + xc, fma(omc, (double)gA.m[3], (1.0 / 9.0) * tm));
-                    collide_pair(A, B, C9, C3, K2, ux + uy, Fx + Fy, Gx + Gy, tp, tm);
-                    put(dst[4], rowp + xp, fma(omc, (double)gA.m[4], (1.0 / 36.0) * tp));
-                    put(dst[6], rowm + xm, fma(omc, (double)gA.m[6], (1.0 / 36.0) * tm));
-                    collide_pair(A, B, C9, C3, K2, uy - ux, Fy - Fx, Gy - Gx, tp, tm);
-                    put(dst[5], rowp + xm, fma(omc, (double)gA.m[5], (1.0 / 36.0) * tp));
-                    put(dst[7], rowm + xp, fma(omc, (double)gA.m[7], (1.0 / 36.0) * tm));
-                    dstR[(uint32_t)wm2 * rsr + (uint32_t)xc] =
-                        fma(omc, gA.r, fma(4.0 / 9.0, fma(-2.0 * fcoef, Gu, base), orho));
+                    double w[8], rest;
+                    collide_d2q9(orho, fcoef, ux, uy, Fx, Fy, Gx, Gy, w, rest);
+                    auto put = [&](int m, uint32_t at) {
+                        dst[m][at] = (ST)fma(omc, (double)gA.m[m], w[m]);
+                    };
+                    put(0, row0 + xp);
+                    put(2, row0 + xm);
+                    put(1, rowp + xc);
+                    put(3, rowm + xc);
+                    put(4, rowp + xp);
+                    put(6, rowm + xm);
+                    put(5, rowp + xm);
+                    put(7, rowm + xp);
+                    dstR[(uint32_t)wm2 * rsr + (uint32_t)xc] = fma(omc, gA.r, rest);
                 }
             }
         }

@@ -94,13 +94,12 @@ struct Comp {
             v[0] = gC.r;
 #pragma unroll
             for (int a = 1; a < 9; ++a) v[a] = (double)gC.m[a - 1];
-            double rho = 0.0;
-#pragma unroll
-            for (int a = 0; a < 9; ++a) rho += v[a];
+            double rho, jx, jy;
+            moments_d2q9(v, rho, jx, jy);
             rh0 = rho;
             L.rt[comp][lane] = rho * invM;
-            L.jx[comp][lane] = (v[1] - v[3]) + (v[5] - v[7]) + (v[8] - v[6]);
-            L.jy[comp][lane] = (v[2] - v[4]) + (v[5] - v[7]) + (v[6] - v[8]);
+            L.jx[comp][lane] = jx;
+            L.jy[comp][lane] = jy;
         }
         Gx = 0.0;
         Gy = 0.0;
@@ -118,15 +117,14 @@ struct Comp {
         {
             double acc = 0.0;
 #pragma unroll
-            for (int j = 0; j < NC; ++j) acc += C->sqk[j] * L.rt[j][lane];
+            for (int j = 0; j < NC; ++j) acc = fma(C->sqk[j], L.rt[j][lane], acc);
             sv0 = acc;
         }
         if (do_eos) {
-            const double c1 = L.eos[0][lane], c2a = L.eos[1][lane], c2b = L.eos[2][lane];
-            const double c3b = L.eos[3][lane], lam = L.eos[4][lane];
+            const MixCoef m = {L.eos[0][lane], L.eos[1][lane], L.eos[2][lane], L.eos[3][lane]};
             const double rti = rhm1 * invM;
-            const double lnf = RT * log(rti * c1) + bi * fma(lam, c2b, c2a) - lam * c3b * so;
-            const double psi = lnf - sqki * lap3(svm2, svm1, sv0);
+            const double lnf = rt_lnf(m, L.eos[4][lane], RT, rti, bi, so);
+            const double psi = fma(-sqki, lap3(svm2, svm1, sv0), lnf);
             psm1 = psi;
             if (!(rti > 0.0)) bad |= FUG_ST_NEGATIVE;
             if (!isfinite(psi)) bad |= FUG_ST_NONFINITE;
@@ -146,9 +144,9 @@ struct Comp {
             cptr<double> arow = C->aij + comp * FUG_MAXC;
             double acc = 0.0;
 #pragma unroll
-            for (int j = 0; j < NC; ++j) acc += arow[j] * L.rt[j][lane];
+            for (int j = 0; j < NC; ++j) acc = fma(arow[j], L.rt[j][lane], acc);
             sn = acc;
-            L.xs[comp][lane] = rh0 * invM * acc;
+            L.xs[comp][lane] = (rh0 * invM) * acc;
         }
     }
 
@@ -166,42 +164,26 @@ struct Comp {
         }
         const int ys = (r - 2) & 3;
         const double inv_rho = L.tot[ys][0][lane];
-        const double ux = (L.tot[ys][1][lane] + 0.5 * Fsx) * inv_rho;
-        const double uy = (L.tot[ys][2][lane] + 0.5 * Fsy) * inv_rho;
+        const double ux = fma(0.5, Fsx, L.tot[ys][1][lane]) * inv_rho;
+        const double uy = fma(0.5, Fsy, L.tot[ys][2][lane]) * inv_rho;
         const double orho = omega * rhm2;
-        const double A = 3.0 * orho, B = 4.5 * orho;
-        const double C9 = 9.0 * fcoef, C3 = 3.0 * fcoef;
         const double omc = 1.0 - omega;
-        const double base = -1.5 * orho * (ux * ux + uy * uy) - C3 * (Fx * ux + Fy * uy);
-        const double Gu = Gx * ux + Gy * uy;
-        const double K1 = fma(-0.5 * fcoef, Gu, base);
-        const double K2 = fma(fcoef, Gu, base);
         if constexpr (sizeof(ST) == 4) {
             float g[8], t[8];
 #pragma unroll
             for (int m = 0; m < 8; ++m) g[m] = (float)gA.m[m];
-            const double msum = collide_moving_f32(A, B, C9, C3, K1, K2, omc, ux, uy, Fx, Fy, Gx,
-                                                   Gy, g, t);
+            const double msum =
+                collide_moving_f32<true>(orho, fcoef, omc, ux, uy, Fx, Fy, Gx, Gy, g, t);
 #pragma unroll
             for (int m = 0; m < 8; ++m) W.ogM[comp][m][lane] = (ST)t[m];
             W.ogR[comp][lane] = rhm2 - msum;
             return;
         }
-        auto put = [&](int a, double v) { W.ogM[comp][a][lane] = (ST)v; };
-        double tp, tm;
-        collide_pair(A, B, C9, C3, K1, ux, Fx, Gx, tp, tm);
-        put(0, fma(omc, (double)gA.m[0], (1.0 / 9.0) * tp));
-        put(2, fma(omc, (double)gA.m[2], (1.0 / 9.0) * tm));
-        collide_pair(A, B, C9, C3, K1, uy, Fy, Gy, tp, tm);
-        put(1, fma(omc, (double)gA.m[1], (1.0 / 9.0) * tp));
-        put(3, fma(omc, (double)gA.m[3], (1.0 / 9.0) * tm));
-        collide_pair(A, B, C9, C3, K2, ux + uy, Fx + Fy, Gx + Gy, tp, tm);
-        put(4, fma(omc, (double)gA.m[4], (1.0 / 36.0) * tp));
-        put(6, fma(omc, (double)gA.m[6], (1.0 / 36.0) * tm));
-        collide_pair(A, B, C9, C3, K2, uy - ux, Fy - Fx, Gy - Gx, tp, tm);
-        put(5, fma(omc, (double)gA.m[5], (1.0 / 36.0) * tp));
-        put(7, fma(omc, (double)gA.m[7], (1.0 / 36.0) * tm));
-        W.ogR[comp][lane] = fma(omc, gA.r, fma(4.0 / 9.0, fma(-2.0 * fcoef, Gu, base), orho));
+        double w[8], rest;
+        collide_d2q9(orho, fcoef, ux, uy, Fx, Fy, Gx, Gy, w, rest);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) W.ogM[comp][m][lane] = (ST)fma(omc, (double)gA.m[m], w[m]);
+        W.ogR[comp][lane] = fma(omc, gA.r, rest);
     }
 
     // Row r-1 from the stash into gA (it is row r-2 of the next lead row),
@@ -281,26 +263,18 @@ struct Store {
         const int lane = threadIdx.x & 63;
         const double et1 = L.mx[(r - 1) & 1][1][lane];
         if (sw == 0) {
-            const double rt1 = L.mx[(r - 1) & 1][0][lane];
             double xsum = 0.0;
 #pragma unroll
             for (int j = 0; j < NC; ++j) xsum += L.xs[j][lane];
-            const double inv_rt = frcp(rt1);
-            const double am = xsum * inv_rt * inv_rt;
-            const double ome = 1.0 - et1;
-            if (!(ome > 0.0) && r <= last) bad |= FUG_ST_COVOLUME;
-            const double inv_ome = frcp(ome);
-            const double inv_bm = rt1 * frcp(et1);
-            const double den = 1.0 + C->eu * et1 + C->ew * et1 * et1;
-            const double zm1 = et1 * inv_ome - am * rt1 * invRT * frcp(den);
-            L.eos[0][lane] = RT * inv_ome;
-            L.eos[1][lane] = RT * zm1 * inv_bm;
-            L.eos[2][lane] = am * inv_bm * inv_bm;
-            L.eos[3][lane] = 2.0 * inv_bm * inv_rt;
+            uint32_t b = 0;
+            const MixCoef m = mix_coef(C, RT, invRT, L.mx[(r - 1) & 1][0][lane], et1, xsum, b);
+            if (r <= last) bad |= b;
+            L.eos[0][lane] = m.c1;
+            L.eos[1][lane] = m.c2a;
+            L.eos[2][lane] = m.c2b;
+            L.eos[3][lane] = m.c3b;
         } else {
-            L.eos[4][lane] = C->eos == 2
-                                 ? et1
-                                 : log((1.0 + C->d1 * et1) * frcp(1.0 + C->d2 * et1)) * C->dk;
+            L.eos[4][lane] = mix_lambda(C, et1);
         }
     }
 
@@ -316,7 +290,7 @@ struct Store {
             for (int j = 0; j < NC; ++j) {
                 const double t = L.rt[j][lane];
                 rtt += t;
-                eta += C->b[j] * t;
+                eta = fma(C->b[j], t, eta);
             }
             L.mx[r & 1][0][lane] = rtt;
             L.mx[r & 1][1][lane] = eta;
@@ -324,7 +298,7 @@ struct Store {
             double rtot = 0.0, jxt = 0.0, jyt = 0.0;
 #pragma unroll
             for (int j = 0; j < NC; ++j) {
-                rtot += C->M[j] * L.rt[j][lane];
+                rtot = fma(C->M[j], L.rt[j][lane], rtot);
                 jxt += L.jx[j][lane];
                 jyt += L.jy[j][lane];
             }

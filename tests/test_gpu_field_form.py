@@ -1,0 +1,78 @@
+"""Runs of steps in field form (D2Q9 at tau = 1: populations read at a run's
+start and written at its end, only rho_i, j and s between the steps) against
+the fused kernels, which keep them in memory at every step.
+
+Both add up the same rounded populations in the same order, so the bar is
+bitwise, over widths either side of the 60-column strips, heights either
+side of the rows per item, component counts 1 ... 10, run lengths that use
+plain launches, a captured graph and both, runs continued from either
+population buffer, and batches.  The grids are large enough for the
+autotuner to take the field form.
+"""
+import numpy as np
+import pytest
+
+from tests import workloads as W
+from tests.test_gpu_parity import _capi
+
+pytestmark = pytest.mark.gpu
+
+
+def make(capi, wl, precision, kernel=0, rows=0):
+    mix = wl.gpu_mixture()
+    s = capi.Simulation(mix, 0, precision, wl.shape, wl.rho)
+    s._mix = mix
+    if kernel:
+        s.set_tuning(kernel, rows)
+    return s
+
+
+def field(N, shape, seed):
+    """N = 1: a C1 slab; up to 4: a drop; more components: the first N of the
+    ten-component field's mixture, uniform with noise (the oracle advances
+    each over these runs without leaving the EOS domain)."""
+    if N == 1:
+        from inputs import fields as Fi
+        wl = W.vle(1, *shape)
+        wl.rho = Fi.add_noise(wl.rho, 1e-3, seed)
+        return wl
+    if N <= 4:
+        return W.random_droplet(N, shape, seed=seed)
+    from inputs import components as C, fields as Fi
+    st = W.states()["spinodal10"]
+    rho = Fi.add_noise(Fi.uniform(shape[0], shape[1], st["rho_uniform"][:N]), 1e-2, seed)
+    return W.Workload(C.N_ALKANES[:N], 325.0, rho, shape, kij=np.array(st["kij"])[:N, :N])
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("N,shape,seed", [
+    (1, (1021, 1019), 9), (2, (541, 600), 11), (3, (479, 361), 31), (4, (659, 240), 11),
+    (6, (361, 181), 4), (9, (239, 211), 4), (10, (181, 300), 4), (10, (420, 97), 5)])
+def test_field_form_matches_fused_bitwise(N, shape, seed, precision):
+    capi = _capi()
+    wl = field(N, shape, seed)
+    a = make(capi, wl, precision, 2, 16)
+    b = make(capi, wl, precision)
+    for n in (9, 1, 40, 101):         # one step swaps the buffers (fused)
+        a.step_n(n)
+        b.step_n(n)
+        assert np.array_equal(a.read_populations(), b.read_populations()), n
+        assert b.diagnostics()["status"] == 0
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_field_form_batch_matches_alone_bitwise(precision):
+    capi = _capi()
+    wls = [W.random_droplet(3, s, seed=31) for s in ((301, 240), (59, 33), (61, 400), (180, 7))]
+    ref = [make(capi, wl, precision, 3, 5) for wl in wls]
+    got = [make(capi, wl, precision) for wl in wls]
+    for n in (12, 1, 120):
+        for s in ref:
+            s.step_n(n)
+        capi.step_many(got, n)
+        for a, b in zip(ref, got):
+            assert np.array_equal(a.read_populations(), b.read_populations()), n
+    for s in ref + got:
+        s.close()
