@@ -114,10 +114,16 @@ int blocks_per_cu(int kernel, int ncomp, bool fp32) {
     return kernel == 3 ? fused_ws_blocks_per_cu(ncomp, fp32) : fused_blocks_per_cu(ncomp, fp32);
 }
 
-hipError_t launch_fused(int kernel, int ncomp, bool fp32, const FusedItem *items, int nitems,
-                        const FusedSim *sims, int flip, hipStream_t st) {
-    return kernel == 3 ? launch_fused_d2q9_ws(ncomp, fp32, items, nitems, sims, flip, st)
-                       : launch_fused_d2q9(ncomp, fp32, items, nitems, sims, flip, st);
+// Variant 2 takes items of one or two rows with the block kernel (all rows
+// of an item at once instead of marching): small grids, where a step is a
+// chain of latencies.
+hipError_t launch_fused(int kernel, int ncomp, bool fp32, const FusedTable &t, int flip,
+                        hipStream_t st) {
+    if (kernel == 3)
+        return launch_fused_d2q9_ws(ncomp, fp32, t.items, t.nitems, t.sims, flip, st);
+    if (t.rows <= FUSED_BLOCK_ROWS && ncomp <= FUSED_BLOCK_COMP)
+        return launch_fused_block(ncomp, fp32, t, flip, st);
+    return launch_fused_d2q9(ncomp, fp32, t.items, t.nitems, t.sims, flip, st);
 }
 
 // The fused variant used before (or without) timing: the store-wave kernel
@@ -278,6 +284,10 @@ static int default_kernel(const fuglbm_sim *s) {
     return fused_fits(s) ? default_fused(s->N, s->fp32) : 1;
 }
 
+static FusedSim fused_sim(const fuglbm_sim *s) {
+    return {s->dc, {s->buf[0], s->buf[1]}, s->status, s->parity, s->nx, s->ny, 0};
+}
+
 // Steps in field form (kernels_fields2d.hip): D2Q9 on the fused kernels, at
 // tau = 1, with variant and rows left to the library.
 static bool field_usable(const fuglbm_sim *s) {
@@ -310,6 +320,8 @@ static FieldSim field_sim(const fuglbm_sim *s) {
     f.wide = (3 * s->N + 3 + 2 * s->D) * f.ld * 8 <= pop_bytes(s);
     if (!f.wide) f.ld = s->ns;
     f.parity = s->parity;
+    f.nx = s->nx;
+    f.ny = s->ny;
     return f;
 }
 
@@ -380,8 +392,8 @@ void drop_graph(fuglbm_sim *s) {
 
 hipError_t launch_one_step(fuglbm_sim *s, int flip_parity, hipStream_t st) {
     if (is_fused(s->kernel))
-        return launch_fused(s->kernel, s->N, s->fp32, s->items, s->nitems, s->fsim, flip_parity,
-                            st);
+        return launch_fused(s->kernel, s->N, s->fp32,
+                            {s->items, s->nitems, s->fsim, 1, s->rows}, flip_parity, st);
     return launch_step_generic(s->lattice, s->fp32, s->dc, s->N, s->nx, s->ny, s->nz, s->buf[flip_parity],
                                s->buf[flip_parity ^ 1], s->rho_f, s->psi_f, s->s_f, s->j_f,
                                s->u_f, s->status, s->hc.omega != 1.0, st);
@@ -667,8 +679,8 @@ fuglbm_status autotune_rows(fuglbm_sim *s, hipStream_t st) {
         // the trial launches read the current state and write the spare
         // buffer (parity unchanged): the state does not move
         auto launch = [&](const Cand &c) {
-            return launch_fused(c.kernel, s->N, s->fp32, dev + c.off, (int)c.n, s->fsim, s->parity,
-                                st);
+            return launch_fused(c.kernel, s->N, s->fp32,
+                                {dev + c.off, (int)c.n, s->fsim, 1, c.rows}, s->parity, st);
         };
         for (size_t i = 0; i < cand.size(); ++i)   // first launch of each variant: not timed
             if (i == 0 || cand[i].kernel != cand[i - 1].kernel) HIP_TRY(launch(cand[i]));
@@ -902,6 +914,7 @@ fuglbm_status fuglbm_init_fields(const fuglbm_mixture *mix, fuglbm_lattice latti
     c.omega = 1.0 / mix->tau;
     c.fcoef = 1.0 - 1.0 / (2.0 * mix->tau);
     c.RT = mix->RT;
+    c.invRT = 1.0 / mix->RT;
     {
         const CubicEos E = cubic_eos(mix->eos);
         c.eos = mix->eos;
@@ -937,12 +950,7 @@ fuglbm_status fuglbm_init_fields(const fuglbm_mixture *mix, fuglbm_lattice latti
     e = hipStreamSynchronize(st);
     if (e != hipSuccess) return bail(hip_fail(e, "init sync"));
     // fused-kernel tables (D2Q9)
-    FusedSim fs{};
-    fs.c = s->dc;
-    fs.buf[0] = s->buf[0];
-    fs.buf[1] = s->buf[1];
-    fs.status = s->status;
-    fs.parity = 0;
+    const FusedSim fs = fused_sim(s);
     e = hipMemcpy(s->fsim, &fs, sizeof(FusedSim), hipMemcpyHostToDevice);
     if (e != hipSuccess) return bail(hip_fail(e, "upload fused sim"));
     const bool fused = fused_fits(s);
@@ -1251,6 +1259,7 @@ struct BatchTable {
     size_t cap_sims = 0, cap_items = 0;
     int nitems = 0;
     int kernel = 2;                   // fused variant of the launches
+    int rows = 0;                     // most rows of an item
     hipGraphExec_t graph = nullptr;   // GRAPH_STEPS launches starting at flip 0
     // field form: its member and item tables, what the tuner measured, and a
     // graph per flip
@@ -1262,13 +1271,15 @@ struct BatchTable {
     hipGraphExec_t fgraph[2] = {nullptr, nullptr};
     hipStream_t last_stream = nullptr;
     bool used = false;                // last_stream is meaningful
+
+    FusedTable table() const { return {ditems, nitems, dsims, (int)sims.size(), rows}; }
 };
 
 fuglbm_status batch_graph(BatchTable &bt, int ncomp, bool fp32) {
     if (bt.graph) return FUGLBM_OK;
     return capture_steps(
         [&](int k, hipStream_t cs) {
-            return launch_fused(bt.kernel, ncomp, fp32, bt.ditems, bt.nitems, bt.dsims, k & 1, cs);
+            return launch_fused(bt.kernel, ncomp, fp32, bt.table(), k & 1, cs);
         },
         bt.graph, "batch graph");
 }
@@ -1350,19 +1361,15 @@ fuglbm_status build_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group
     HIP_TRY(hipStreamSynchronize(st));  // the old table may still be read by queued launches
     drop_batch_graphs(bt);
     bt.kernel = kernel ? kernel : group[0]->kernel;
+    bt.rows = 0;
     std::vector<FusedSim> hs;
     std::vector<FusedItem> logical;
     for (size_t k = 0; k < group.size(); ++k) {
         fuglbm_sim *s = group[k];
-        FusedSim fs{};
-        fs.c = s->dc;
-        fs.buf[0] = s->buf[0];
-        fs.buf[1] = s->buf[1];
-        fs.status = s->status;
-        fs.parity = s->parity;
-        hs.push_back(fs);
+        hs.push_back(fused_sim(s));
         const int strips = (s->nx + FUSED_OUT - 1) / FUSED_OUT;
         const int rw = rows > 0 ? std::min(rows, s->ny) : s->rows;
+        bt.rows = std::max(bt.rows, rw);
         const int chunks = (s->ny + rw - 1) / rw;
         for (int c = 0; c < chunks; ++c)
             for (int t = 0; t < strips; ++t)
@@ -1444,7 +1451,7 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
         float ms = 0.f;
         fuglbm_status rc = time_candidates(
             tune_candidates(ny_max, 0), st, [&](int rr) { return build_batch(bt, group, st, rr, k); },
-            [&]() { return launch_fused(k, nc, f32, bt.ditems, bt.nitems, bt.dsims, 0, st); }, r,
+            [&]() { return launch_fused(k, nc, f32, bt.table(), 0, st); }, r,
             &ms);
         if (rc != FUGLBM_OK) return rc;
         if (ms < best_ms) {
@@ -1655,7 +1662,7 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         }
         if (left >= 2 * GRAPH_STEPS && flip == 1) {
             hipError_t e =
-                launch_fused(bt.kernel, nc, f32, bt.ditems, bt.nitems, bt.dsims, flip, st);
+                launch_fused(bt.kernel, nc, f32, bt.table(), flip, st);
             if (e != hipSuccess) return hip_fail(e, "batched step launch");
             flip = 0;
             --left;
@@ -1671,7 +1678,7 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         }
         for (; left > 0; --left) {
             hipError_t e =
-                launch_fused(bt.kernel, nc, f32, bt.ditems, bt.nitems, bt.dsims, flip, st);
+                launch_fused(bt.kernel, nc, f32, bt.table(), flip, st);
             if (e != hipSuccess) return hip_fail(e, "batched step launch");
             flip ^= 1;
         }
@@ -1796,6 +1803,8 @@ __global__ void k_na_members(NaChunk a, FusedSim *sims, int4 *geom) {
     fs.buf[1] = m.buf1;
     fs.status = m.status;
     fs.parity = m.parity;
+    fs.nx = m.nx;
+    fs.ny = m.ny;
     fs.pad = 0;
     sims[a.base + t] = fs;
     geom[a.base + t] = make_int4(m.nx, m.ny, m.rows, a.first[t]);
@@ -1933,9 +1942,12 @@ extern "C" fuglbm_status fuglbm_step_many_noalloc(fuglbm_sim *const *sims, int32
         const int ncomp = first->N;
         const bool f32 = first->fp32;
         const int kern = first->kernel == 3 && ws_usable(ncomp, f32) ? 3 : 2;
+        int rows = 0;
+        for (int k = 0; k < count; ++k)
+            if (cls[k] == g) rows = std::max(rows, sims[k]->rows);
         for (int64_t t = 0; t < nsteps; ++t) {
-            hipError_t e = launch_fused(kern, ncomp, f32, ditems + item_off, nitems,
-                                        dsims + mem_off, (int)(t & 1), st);
+            const FusedTable tab{ditems + item_off, nitems, dsims + mem_off, nmem, rows};
+            hipError_t e = launch_fused(kern, ncomp, f32, tab, (int)(t & 1), st);
             if (e != hipSuccess) return hip_fail(e, "batched step launch");
         }
         mem_off += nmem;

@@ -16,7 +16,18 @@ struct FusedSim {
     void *buf[2];
     uint32_t *status;
     int32_t parity;
+    int32_t nx, ny;
     int32_t pad;
+};
+
+// What a fused step is launched over: items of at most `rows` rows, nsims
+// simulations.
+struct FusedTable {
+    const FusedItem *items;
+    int nitems;
+    const FusedSim *sims;
+    int nsims;
+    int rows;
 };
 
 constexpr int FUSED_LANES = 64;
@@ -73,6 +84,12 @@ int fused_blocks_per_cu(int ncomp, bool fp32);
 hipError_t launch_fused_d2q9(int ncomp, bool fp32, const FusedItem *items, int nitems,
                              const FusedSim *sims, int flip, hipStream_t st);
 
+// The same step for tables whose items have at most `rows` (1 or 2) rows,
+// built for ncomp <= 10 (kernels_fused2d_block.hip).
+constexpr int FUSED_BLOCK_ROWS = 2;
+constexpr int FUSED_BLOCK_COMP = 10;
+hipError_t launch_fused_block(int ncomp, bool fp32, const FusedTable &t, int flip, hipStream_t st);
+
 // Store-wave variant of the fused D2Q9 step (component waves only load;
 // two extra waves per workgroup store; rows requested three ahead).  Same
 // items, same results bit for bit.  Built for ncomp <= fused_ws_max_comp().
@@ -96,6 +113,7 @@ struct FieldSim {
     uint32_t *status;
     int64_t end, ld;
     int32_t parity, wide;
+    int32_t nx, ny;
 };
 // What the steps of a run are launched over: one simulation (tab null; work
 // items follow from strips and rows, nitems of them) or a table of nm

@@ -82,6 +82,8 @@ __device__ __forceinline__ FieldSim load_sim(const FieldSim *tab, int k) {
     f.ld = p->ld;
     f.parity = p->parity;
     f.wide = p->wide;
+    f.nx = p->nx;
+    f.ny = p->ny;
     return f;
 }
 
@@ -102,16 +104,6 @@ __device__ __forceinline__ FieldSim block_sim(const FieldSim *tab, int nm, const
     return load_sim(tab, lo);
 }
 
-// Status bits of a wavefront's lanes: one atomic, not one per lane (a state
-// that has left the domain sets them at every site).
-__device__ __forceinline__ void flag_status(uint32_t *status, uint32_t bad) {
-    uint32_t all = 0;
-#pragma unroll
-    for (uint32_t b : {FUG_ST_NONFINITE, FUG_ST_COVOLUME, FUG_ST_NEGATIVE})
-        if (__ballot(bad & b)) all |= b;
-    if (all && (threadIdx.x & 63) == 0) atomicOr(status, all);
-}
-
 // rho_i, j and s of the populations in memory -> set 0.  Bound by the
 // population reads (each once).
 template <typename ST>
@@ -120,13 +112,13 @@ __global__ __launch_bounds__(TPB) void k_field_moments(const FieldSim *tab, int 
     int64_t blk = blockIdx.x;
     const FieldSim f = block_sim(tab, nm, one, blk);
     cptr<SimConst> C = (cptr<SimConst>)f.c;
-    const int N = C->N, nx = C->nx;
-    const uint32_t ns = (uint32_t)C->nsites;
+    const int N = C->N, nx = f.nx;
+    const uint32_t ns = (uint32_t)nx * (uint32_t)f.ny;
     const uint32_t s = (uint32_t)blk * TPB + threadIdx.x;
     if (s >= ns) return;
     const View v = field_view(f, flip, N, 2);
     const void *g = ((f.parity ^ flip) & 1) ? f.buf[1] : f.buf[0];
-    const PopLayout<ST> P(N, 9, nx, C->ny);
+    const PopLayout<ST> P(N, 9, nx, f.ny);
     const uint32_t row = s / (uint32_t)nx;
     const int x = (int)(s - row * (uint32_t)nx);
     double jxt = 0.0, jyt = 0.0, sv = 0.0;
@@ -157,10 +149,10 @@ __global__ __launch_bounds__(TPB) void k_field_eos(const FieldSim *tab, int nm, 
     int64_t blk = blockIdx.x;
     const FieldSim f = block_sim(tab, nm, one, blk);
     cptr<SimConst> C = (cptr<SimConst>)f.c;
-    const uint32_t ns = (uint32_t)C->nsites;
+    const int nx = f.nx, ny = f.ny;
+    const uint32_t ns = (uint32_t)nx * (uint32_t)ny;
     const uint32_t s = (uint32_t)blk * TPB + threadIdx.x;
     if (s >= ns) return;
-    const int nx = C->nx, ny = C->ny;
     const View v = field_view(f, flip, NC, 2);
     const double *rho = set ? v.rho[1] : v.rho[0];
     const double *sf = set ? v.s[1] : v.s[0];
@@ -198,7 +190,7 @@ __global__ __launch_bounds__(TPB) void k_field_eos(const FieldSim *tab, int nm, 
         xsum += rt[i] * acc;
     }
     const double RT = C->RT;
-    const MixCoef m = mix_coef(C, RT, 1.0 / RT, rtt, eta, xsum, bad);
+    const MixCoef m = mix_coef(C, RT, C->invRT, rtt, eta, xsum, bad);
     const double lam = mix_lambda(C, eta);
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
@@ -262,13 +254,12 @@ __global__ __launch_bounds__(64 * (NC + HELPERS)) void k_field_step(
         const int per = gridDim.x / 8;
         const int li = (blockIdx.x % 8) * per + blockIdx.x / 8;
         if (li >= nitems) return;
-        const int ny = ((cptr<SimConst>)f.c)->ny;
         it.x0 = (li % strips) * FUSED_OUT;
         it.y0 = (li / strips) * rows_;
-        it.rows = min(rows_, ny - it.y0);
+        it.rows = min(rows_, f.ny - it.y0);
     }
     cptr<SimConst> C = (cptr<SimConst>)f.c;
-    const int nx = C->nx, ny = C->ny;
+    const int nx = f.nx, ny = f.ny;
     const View v = field_view(f, flip, NC, 2);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;

@@ -269,7 +269,7 @@ __global__ __launch_bounds__(64 * NC) void k_fused_d2q9(const FusedItem *__restr
     f.bi = C->b[f.comp];
     f.sqki = C->sqk[f.comp];
     f.RT = C->RT;
-    f.invRT = 1.0 / C->RT;
+    f.invRT = C->invRT;
     f.omega = C->omega;
     f.fcoef = C->fcoef;
     f.bad = 0;
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(64 * NC) void k_fused_d2q9(const FusedItem *__restr
         s2 = s0;
         qo = qn;
     }
-    if (f.bad) atomicOr(sm->status, f.bad);
+    flag_status(sm->status, f.bad);
 }
 
 template <int NC>

@@ -337,7 +337,7 @@ __global__ __launch_bounds__(64 * (NC + STORE_WAVES)) void k_fused_d2q9_ws(
     if (wave >= NC) {
         Store<NC, ST> s{lds, lds.f, C, bdst, P, (uint32_t)P.rest_row_stride(),
                         (uint32_t)P.move_row_stride(), wave - NC, nx, ny, it.y0, {0, 0, 0},
-                        false, C->RT, 1.0 / C->RT, 0u};
+                        false, C->RT, C->invRT, 0u};
         s.xsh[0] = xc == 0 ? nx - 1 : xc - 1;
         s.xsh[1] = xc;
         s.xsh[2] = xc == nx - 1 ? 0 : xc + 1;
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(64 * (NC + STORE_WAVES)) void k_fused_d2q9_ws(
                 __syncthreads();
             }
         }
-        if (s.bad) atomicOr(sm->status, s.bad);
+        flag_status(sm->status, s.bad);
         return;
     }
 
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(64 * (NC + STORE_WAVES)) void k_fused_d2q9_ws(
         lead(r0 + 1, Y);
         lead(r0 + 2, Z);
     }
-    if (f.bad) atomicOr(sm->status, f.bad);
+    flag_status(sm->status, f.bad);
 }
 
 template <int NC>

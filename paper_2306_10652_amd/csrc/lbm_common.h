@@ -24,7 +24,7 @@ struct SimConst {
     int64_t nsites;
     double omega;         // 1 / tau
     double fcoef;         // 1 - 1 / (2 tau)
-    double RT;
+    double RT, invRT;
     // cubic p = RT/(v - b) - a alpha/((v + d1 b)(v + d2 b)):  d1, d2,
     // u = d1 + d2, w = d1 d2 (exact per EOS) and dk = 1/(d1 - d2) (0 for vdW)
     double d1, d2, eu, ew, dk;
