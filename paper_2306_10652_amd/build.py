@@ -17,7 +17,7 @@ LIB = os.path.join(HERE, "libfuglbm.so")
 ROOT = os.path.dirname(HERE)
 
 SOURCES = ["kernels_generic.hip", "kernels_fused2d.hip", "kernels_fused2d_ws.hip",
-           "kernels_fused2d_block.hip", "kernels_fields2d.hip", "fuglbm_host.cpp"]
+           "fuglbm_host.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("FUGLBM_ARCH", "gfx950")

@@ -20,9 +20,11 @@
 // (FP32 storage: 100 in the same unit).  All terms come from the functions
 // the fused kernels use, and the populations enter the sums rounded to the
 // storage type and in direction order: the state is bitwise theirs.
+#pragma once
+
 #include "fused_common.h"
 
-namespace {
+namespace fields {
 
 using namespace fused;
 
@@ -515,16 +517,16 @@ int occ_nc() {
     return e == hipSuccess && nb > 0 ? nb : 1;
 }
 
-}  // namespace
+}  // namespace fields
 
 int field_max_comp() { return 10; }
 
 hipError_t launch_field_moments2d(const FieldRun &q, bool fp32, hipStream_t st) {
     if (fp32)
-        hipLaunchKernelGGL((k_field_moments<float>), dim3((unsigned)q.blocks), dim3(TPB), 0, st,
+        hipLaunchKernelGGL((fields::k_field_moments<float>), dim3((unsigned)q.blocks), dim3(fields::TPB), 0, st,
                            q.tab, q.nm, q.one, q.flip);
     else
-        hipLaunchKernelGGL((k_field_moments<double>), dim3((unsigned)q.blocks), dim3(TPB), 0, st,
+        hipLaunchKernelGGL((fields::k_field_moments<double>), dim3((unsigned)q.blocks), dim3(fields::TPB), 0, st,
                            q.tab, q.nm, q.one, q.flip);
     return hipGetLastError();
 }
@@ -544,7 +546,7 @@ hipError_t launch_field_moments2d(const FieldRun &q, bool fp32, hipStream_t st) 
     }
 
 hipError_t launch_field_eos2d(const FieldRun &q, int ncomp, int set, hipStream_t st) {
-#define EOS(n) eos_nc<n>(q, set, st)
+#define EOS(n) fields::eos_nc<n>(q, set, st)
     FIELD_BY_N(EOS)
 #undef EOS
     return hipErrorInvalidValue;
@@ -552,14 +554,14 @@ hipError_t launch_field_eos2d(const FieldRun &q, int ncomp, int set, hipStream_t
 
 hipError_t launch_field_step2d(const FieldRun &q, int ncomp, bool fp32, bool last, int set,
                                hipStream_t st) {
-#define STEP(n) step_sel<n>(q, fp32, last, set, st)
+#define STEP(n) fields::step_sel<n>(q, fp32, last, set, st)
     FIELD_BY_N(STEP)
 #undef STEP
     return hipErrorInvalidValue;
 }
 
 int field_blocks_per_cu2d(int ncomp) {
-#define OCC(n) occ_nc<n>()
+#define OCC(n) fields::occ_nc<n>()
     FIELD_BY_N(OCC)
 #undef OCC
     return 1;

@@ -23,9 +23,11 @@
 // helper wavefront per row that needs the EOS.  Terms, orders of summation
 // and work-item tables are those of the marching kernels: bitwise the same
 // state.
+#pragma once
+
 #include "fused_common.h"
 
-namespace {
+namespace block {
 
 using namespace fused;
 
@@ -259,20 +261,20 @@ hipError_t launch_nc(bool fp32, const FusedTable &t, int flip, hipStream_t st) {
     return fp32 ? launch_t<NC, float, 2>(t, flip, st) : launch_t<NC, double, 2>(t, flip, st);
 }
 
-}  // namespace
+}  // namespace block
 
 hipError_t launch_fused_block(int ncomp, bool fp32, const FusedTable &t, int flip, hipStream_t st) {
     switch (ncomp) {
-        case 1: return launch_nc<1>(fp32, t, flip, st);
-        case 2: return launch_nc<2>(fp32, t, flip, st);
-        case 3: return launch_nc<3>(fp32, t, flip, st);
-        case 4: return launch_nc<4>(fp32, t, flip, st);
-        case 5: return launch_nc<5>(fp32, t, flip, st);
-        case 6: return launch_nc<6>(fp32, t, flip, st);
-        case 7: return launch_nc<7>(fp32, t, flip, st);
-        case 8: return launch_nc<8>(fp32, t, flip, st);
-        case 9: return launch_nc<9>(fp32, t, flip, st);
-        case 10: return launch_nc<10>(fp32, t, flip, st);
+        case 1: return block::launch_nc<1>(fp32, t, flip, st);
+        case 2: return block::launch_nc<2>(fp32, t, flip, st);
+        case 3: return block::launch_nc<3>(fp32, t, flip, st);
+        case 4: return block::launch_nc<4>(fp32, t, flip, st);
+        case 5: return block::launch_nc<5>(fp32, t, flip, st);
+        case 6: return block::launch_nc<6>(fp32, t, flip, st);
+        case 7: return block::launch_nc<7>(fp32, t, flip, st);
+        case 8: return block::launch_nc<8>(fp32, t, flip, st);
+        case 9: return block::launch_nc<9>(fp32, t, flip, st);
+        case 10: return block::launch_nc<10>(fp32, t, flip, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -65,16 +65,6 @@ __device__ __forceinline__ double lap3(double S, double C, double N) {
     return lap3(row3(S), row3(C), row3(N));
 }
 
-// Status bits of a wavefront's lanes: one atomic, not one per lane (a state
-// that has left the domain sets them at every site).
-__device__ __forceinline__ void flag_status(uint32_t *status, uint32_t bad) {
-    uint32_t all = 0;
-#pragma unroll
-    for (uint32_t b : {FUG_ST_NONFINITE, FUG_ST_COVOLUME, FUG_ST_NEGATIVE})
-        if (__ballot(bad & b)) all |= b;
-    if (all && (threadIdx.x & 63) == 0) atomicOr(status, all);
-}
-
 // Wave that computes part p (0..3) of the per-site sums.  Waves of a
 // workgroup are dealt to the 4 SIMDs of a CU in turn, so with NC % 4 != 0
 // the SIMDs s >= NC % 4 hold one wave fewer; the parts go to their waves.

@@ -22,6 +22,7 @@
 // the 4 warm-up rows of a work item are re-reads that neighbouring items
 // issue at about the same time (the item order keeps them on one XCD).
 #include "fused_common.h"
+#include "fused2d_block.h"
 
 namespace {
 

@@ -37,6 +37,7 @@
 //   3  (component waves) u(y), collision of row y -> LDS staging; row
 //      r-1 stash -> registers, row r -> stash, request row r+3
 // One extra pass of the loop flushes the last staged row.
+#include "fields2d.h"
 #include "fused_common.h"
 
 namespace {

@@ -35,6 +35,23 @@ struct SimConst {
     double aij[FUG_MAXC * FUG_MAXC];  // (a alpha)_ij, row-major, stride FUG_MAXC
 };
 
+// Status bits of a wavefront's lanes into the simulation's word: one atomic
+// per wavefront, and none for bits that are there already.  A state that has
+// left the domain sets them at every site of every step, and thousands of
+// atomics on one address cost more than the step (131 x 75 x 5: 28 against
+// 8 us).  Status bits only ever get set, so a stale read costs an atomic.
+__device__ __forceinline__ void flag_status(uint32_t *status, uint32_t bad) {
+    uint32_t all = 0;
+#pragma unroll
+    for (uint32_t b : {FUG_ST_NONFINITE, FUG_ST_COVOLUME, FUG_ST_NEGATIVE})
+        if (__ballot(bad & b)) all |= b;
+    if (all == 0) return;
+    const uint32_t seen = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t act = __ballot(true);
+    if ((all & ~seen) && (int)(threadIdx.x & 63) == __ffsll((unsigned long long)act) - 1)
+        atomicOr(status, all);
+}
+
 // ---------------------------------------------------------------------------
 // Velocity sets.  D2Q9 order: rest, +x, +y, -x, -y, (+,+), (-,+), (-,-), (+,-).
 // D3Q19 order: rest, 6 faces, 12 edges; opposite pairs at (a, a+1) for a odd.
