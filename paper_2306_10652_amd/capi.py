@@ -222,9 +222,9 @@ class Simulation:
         check(lib().fuglbm_step_n(self.handle, int(n), _stream_ptr(stream or self.stream)))
 
     def read_moments(self, velocity=True, diag=False):
-        rho = np.zeros(self.N * self.sites)
+        rho = np.empty(self.N * self.sites)
         D = 2 if self.lattice == D2Q9 else 3
-        u = np.zeros(D * self.sites) if velocity else None
+        u = np.empty(D * self.sites) if velocity else None
         dg = Diag() if diag else None
         st = lib().fuglbm_read_moments(self.handle, _dp(rho), _dp(u),
                                        ctypes.byref(dg) if dg is not None else None)
@@ -249,7 +249,7 @@ class Simulation:
 
     def read_populations(self):
         Q = 9 if self.lattice == D2Q9 else 19
-        g = np.zeros(self.N * Q * self.sites)
+        g = np.empty(self.N * Q * self.sites)
         check(lib().fuglbm_read_populations(self.handle, _dp(g)))
         return g.reshape(self.N, Q, self.sites)
 

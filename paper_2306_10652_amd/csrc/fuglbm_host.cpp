@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <climits>
 #include <cmath>
 #include <cstring>
@@ -10,6 +11,7 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -209,6 +211,10 @@ struct Tuned {
     float fused_ms = 0.f, field_ms = 0.f, moments_ms = 0.f;
 };
 
+namespace {
+struct Stage;
+}
+
 struct fuglbm_sim {
     const fuglbm_mixture *mix;
     int lattice;
@@ -244,6 +250,7 @@ struct fuglbm_sim {
     GraphCache graph;
     Tuned tune;            // valid with `tuned`
     hipGraphExec_t fgraph[2];   // field form, by the parity it was captured at
+    Stage *stage;          // pinned staging of its device
     uint64_t uid;          // never reused; batch tables key on it, not on the address
 };
 
@@ -288,7 +295,7 @@ static FusedSim fused_sim(const fuglbm_sim *s) {
     return {s->dc, {s->buf[0], s->buf[1]}, s->status, s->parity, s->nx, s->ny, 0};
 }
 
-// Steps in field form (kernels_fields2d.hip): D2Q9 on the fused kernels, at
+// Steps in field form (fields2d.h): D2Q9 on the fused kernels, at
 // tau = 1, with variant and rows left to the library.
 static bool field_usable(const fuglbm_sim *s) {
     return is_fused(s->kernel) && s->auto_kernel && s->autotune && s->hc.omega == 1.0 &&
@@ -725,11 +732,212 @@ fuglbm_status autotune_rows(fuglbm_sim *s, hipStream_t st) {
     return set_rows(s, tn.rows, st);
 }
 
-fuglbm_status sync_status(fuglbm_sim *s) {
-    HIP_TRY(hipStreamSynchronize(s->last_stream));
-    uint32_t st = 0;
-    HIP_TRY(hipMemcpy(&st, s->status, sizeof(uint32_t), hipMemcpyDeviceToHost));
-    s->sticky |= st;
+// ---- copies between device and caller memory ------------------------------
+// Pinned staging shared by the read-outs and checkpoints of the process: a
+// small block for totals and status words, and a ring of slots that bulk
+// copies go through while a few threads move finished slots to (from) the
+// caller's pages, whose first touch is what a plain copy spends most of its
+// time on.  Held while any simulation exists; a call that finds it in use by
+// another thread copies without it.
+constexpr size_t STAGE_SMALL = 4096, STAGE_SLOT = (size_t)4 << 20;
+constexpr int STAGE_SLOTS = 8, STAGE_THREADS = 6;
+
+struct Stage {
+    std::mutex use;             // held by the call that copies through it
+    char *mem = nullptr;        // STAGE_SMALL + STAGE_SLOTS * STAGE_SLOT, pinned
+    hipEvent_t ev[STAGE_SLOTS] = {};
+    std::mutex life;
+    int sims = 0;               // live simulations
+
+    char *slot(int64_t k) const { return mem + STAGE_SMALL + (k % STAGE_SLOTS) * STAGE_SLOT; }
+    // with `use` held
+    bool ready() {
+        if (mem) return true;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, STAGE_SMALL + STAGE_SLOTS * STAGE_SLOT, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        for (hipEvent_t &e : ev)
+            if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+                e = nullptr;
+                (void)hipHostFree(p);
+                return false;
+            }
+        mem = (char *)p;
+        return true;
+    }
+    void add_sim() {
+        std::lock_guard<std::mutex> g(life);
+        ++sims;
+    }
+    void drop_sim() {
+        std::lock_guard<std::mutex> g(life);
+        if (--sims > 0) return;
+        std::lock_guard<std::mutex> u(use);
+        if (mem) (void)hipHostFree(mem);
+        mem = nullptr;
+        for (hipEvent_t &e : ev) {
+            if (e) (void)hipEventDestroy(e);
+            e = nullptr;
+        }
+    }
+};
+
+// That of the current device (one never destroyed, as simulations may outlive
+// static objects).
+Stage &device_stage() {
+    static Stage *all = new Stage[64];
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    return all[dev & 63];
+}
+
+// Moves `bytes` between the device (dev) and the caller (host) on st, to the
+// caller if `out`; done when it returns.  Slots are handed to the threads in
+// order; none waits for anything but its own slot's turn, and all leave when
+// the last slot is taken or a copy fails.
+hipError_t staged_copy(Stage &g, char *host, char *dev, size_t bytes, bool out, hipStream_t st) {
+    const int64_t n = (int64_t)((bytes + STAGE_SLOT - 1) / STAGE_SLOT);
+    auto size = [&](int64_t k) { return std::min(STAGE_SLOT, bytes - (size_t)k * STAGE_SLOT); };
+    auto host_at = [&](int64_t k) { return host + (size_t)k * STAGE_SLOT; };
+    auto dev_at = [&](int64_t k) { return dev + (size_t)k * STAGE_SLOT; };
+    auto dma = [&](int64_t k) {
+        return out ? hipMemcpyAsync(g.slot(k), dev_at(k), size(k), hipMemcpyDeviceToHost, st)
+                   : hipMemcpyAsync(dev_at(k), g.slot(k), size(k), hipMemcpyHostToDevice, st);
+    };
+    auto move = [&](int64_t k) {
+        if (out)
+            std::memcpy(host_at(k), g.slot(k), size(k));
+        else
+            std::memcpy(g.slot(k), host_at(k), size(k));
+    };
+    hipError_t err = hipSuccess;
+    if (n <= 1) {
+        if (!out) move(0);
+        err = dma(0);
+        if (err == hipSuccess) err = hipStreamSynchronize(st);
+        if (out && err == hipSuccess) move(0);
+        return err;
+    }
+    // a thread may take slot k once `open` > k; `moved` of the ring position
+    // counts the slots that it has finished there
+    std::atomic<int64_t> open{0}, next{0};
+    std::atomic<int64_t> moved[STAGE_SLOTS];
+    for (auto &m : moved) m.store(0);
+    std::atomic<bool> stop{false};
+    auto work = [&] {
+        for (;;) {
+            const int64_t k = next.fetch_add(1);
+            if (k >= n) return;
+            while (open.load(std::memory_order_acquire) <= k) {
+                if (stop.load()) return;
+                std::this_thread::yield();
+            }
+            move(k);
+            moved[k % STAGE_SLOTS].fetch_add(1, std::memory_order_release);
+        }
+    };
+    std::thread th[STAGE_THREADS];
+    int nth = 0;
+    try {
+        for (; nth < STAGE_THREADS && nth < n; ++nth) th[nth] = std::thread(work);
+    } catch (...) {
+    }
+    if (nth == 0) {                        // no thread to be had
+        for (int64_t k = 0; k < n && err == hipSuccess; ++k) {
+            if (!out) move(k);
+            err = dma(k);
+            if (err == hipSuccess) err = hipStreamSynchronize(st);
+            if (out && err == hipSuccess) move(k);
+        }
+        return err;
+    }
+    auto finished = [&](int64_t k) {       // slot k's move is done
+        return moved[k % STAGE_SLOTS].load(std::memory_order_acquire) > k / STAGE_SLOTS;
+    };
+    if (out) {
+        int64_t issued = 0, landed = 0;
+        while (landed < n && err == hipSuccess) {
+            while (issued < n && issued < landed + STAGE_SLOTS && err == hipSuccess &&
+                   (issued < STAGE_SLOTS || finished(issued - STAGE_SLOTS))) {
+                err = dma(issued);
+                if (err == hipSuccess) err = hipEventRecord(g.ev[issued % STAGE_SLOTS], st);
+                ++issued;
+            }
+            if (err == hipSuccess && landed < issued) {
+                err = hipEventSynchronize(g.ev[landed % STAGE_SLOTS]);
+                ++landed;
+                if (err == hipSuccess) open.store(landed, std::memory_order_release);
+            } else {
+                std::this_thread::yield();
+            }
+        }
+    } else {
+        open.store(std::min<int64_t>(n, STAGE_SLOTS));
+        for (int64_t k = 0; k < n && err == hipSuccess; ++k) {
+            while (!finished(k)) std::this_thread::yield();
+            err = dma(k);
+            if (err == hipSuccess) err = hipEventRecord(g.ev[k % STAGE_SLOTS], st);
+            // the slot of the copy issued half a ring ago may be filled again
+            const int64_t old = k - STAGE_SLOTS / 2;
+            if (old >= 0 && err == hipSuccess) {
+                err = hipEventSynchronize(g.ev[old % STAGE_SLOTS]);
+                open.store(std::min<int64_t>(n, old + 1 + STAGE_SLOTS), std::memory_order_release);
+            }
+        }
+        if (err == hipSuccess) err = hipStreamSynchronize(st);
+    }
+    if (err != hipSuccess) stop.store(true);
+    for (int k = 0; k < nth; ++k) th[k].join();
+    if (err != hipSuccess) (void)hipStreamSynchronize(st);
+    return err;
+}
+
+// One part of a read-out: device to caller.
+struct Part {
+    void *host;
+    const void *dev;
+    size_t bytes;
+};
+
+// Copies the parts and the status word to the caller after the work queued
+// on the simulation's stream; one wait in all where they are small.
+fuglbm_status read_parts(fuglbm_sim *s, std::initializer_list<Part> parts) {
+    hipStream_t st = s->last_stream;
+    Stage &g = *s->stage;
+    std::unique_lock<std::mutex> lk(g.use, std::try_to_lock);
+    uint32_t word = 0;
+    if (!lk.owns_lock() || !g.ready()) {
+        HIP_TRY(hipStreamSynchronize(st));
+        for (const Part &p : parts)
+            if (p.host) HIP_TRY(hipMemcpy(p.host, p.dev, p.bytes, hipMemcpyDeviceToHost));
+        HIP_TRY(hipMemcpy(&word, s->status, sizeof(word), hipMemcpyDeviceToHost));
+        s->sticky |= word;
+        return FUGLBM_OK;
+    }
+    HIP_TRY(hipMemcpyAsync(g.mem, s->status, sizeof(word), hipMemcpyDeviceToHost, st));
+    // small parts share slot 0 and the final wait; the others go through the
+    // ring first
+    size_t used = 0;
+    auto small = [&](const Part &p) { return p.bytes <= STAGE_SLOT / 4; };
+    for (const Part &p : parts)
+        if (p.host && !small(p))
+            HIP_TRY(staged_copy(g, (char *)p.host, (char *)p.dev, p.bytes, true, st));
+    for (const Part &p : parts)
+        if (p.host && small(p)) {
+            HIP_TRY(hipMemcpyAsync(g.slot(0) + used, p.dev, p.bytes, hipMemcpyDeviceToHost, st));
+            used += p.bytes;
+        }
+    HIP_TRY(hipStreamSynchronize(st));
+    used = 0;
+    for (const Part &p : parts)
+        if (p.host && small(p)) {
+            std::memcpy(p.host, g.slot(0) + used, p.bytes);
+            used += p.bytes;
+        }
+    std::memcpy(&word, g.mem, sizeof(word));
+    s->sticky |= word;
     return FUGLBM_OK;
 }
 
@@ -969,6 +1177,8 @@ fuglbm_status fuglbm_init_fields(const fuglbm_mixture *mix, fuglbm_lattice latti
     s->tuned = false;
     s->fgraph[0] = s->fgraph[1] = nullptr;
     s->uid = next_sim_uid();
+    s->stage = &device_stage();
+    s->stage->add_sim();
     *out = s;
     return FUGLBM_OK;
 }
@@ -1072,16 +1282,11 @@ fuglbm_status fuglbm_read_moments(fuglbm_sim *s, double *rho_out, double *u_out,
     const TraceRange trace_range("fuglbm_read_moments");
     if (!s) return fail(FUGLBM_EINVAL, "null sim");
     hipStream_t st = s->last_stream;
-    HIP_TRY(hipStreamSynchronize(st));
     HIP_TRY(launch_fields(s->lattice, s->fp32, s->dc, s->nx, s->ny, s->nz, s->buf[s->parity],
                           s->rho_f, s->psi_f, s->s_f, s->j_f, u_out ? s->u_f : nullptr, s->status,
                           st));
-    HIP_TRY(hipStreamSynchronize(st));
-    if (rho_out)
-        HIP_TRY(hipMemcpy(rho_out, s->rho_f, (size_t)s->N * s->ns * 8, hipMemcpyDeviceToHost));
-    if (u_out)
-        HIP_TRY(hipMemcpy(u_out, s->u_f, (size_t)s->D * s->ns * 8, hipMemcpyDeviceToHost));
-    fuglbm_status rc = sync_status(s);
+    fuglbm_status rc = read_parts(s, {{rho_out, s->rho_f, (size_t)s->N * s->ns * 8},
+                                      {u_out, s->u_f, (size_t)s->D * s->ns * 8}});
     if (rc != FUGLBM_OK) return rc;
     if (diag) {
         rc = fuglbm_diagnostics(s, diag);
@@ -1106,9 +1311,8 @@ fuglbm_status fuglbm_diagnostics(fuglbm_sim *s, fuglbm_diag *diag) {
     HIP_TRY(launch_diag(s->D, N, s->ns, s->rho_f, s->j_f, s->u_f, s->snap, s->part, nblk, fin,
                         s->have_snap ? 1 : 0, st));
     double tot[(FUGLBM_MAX_COMP + 1) * DIAG_QUANT];
-    HIP_TRY(hipMemcpyAsync(tot, fin, sizeof(double) * (N + 1) * DIAG_QUANT, hipMemcpyDeviceToHost,
-                           st));
-    HIP_TRY(hipStreamSynchronize(st));
+    fuglbm_status rc = read_parts(s, {{tot, fin, sizeof(double) * (N + 1) * DIAG_QUANT}});
+    if (rc != FUGLBM_OK) return rc;
     std::memset(diag, 0, sizeof(*diag));
     diag->step = s->step;
     for (int i = 0; i < N; ++i) diag->mass[i] = tot[i * DIAG_QUANT];
@@ -1124,8 +1328,6 @@ fuglbm_status fuglbm_diagnostics(fuglbm_sim *s, fuglbm_diag *diag) {
     diag->residual = res;
     s->have_snap = true;
     s->snap_step = s->step;
-    fuglbm_status rc = sync_status(s);
-    if (rc != FUGLBM_OK) return rc;
     diag->status = s->sticky;
     if (s->sticky) return fail(FUGLBM_ENONFINITE, "device status bits set");
     return FUGLBM_OK;
@@ -1137,67 +1339,71 @@ static int host_pop_col(const fuglbm_sim *s, int a, int x) {
     return s->lattice == FUGLBM_D3Q19 ? pop_col<D3Q19>(a, x, s->nx) : pop_col<D2Q9>(a, x, s->nx);
 }
 
-// Host copy of one buffer <-> [N][Q][sites] FP64 (the layout is PopLayout,
-// the moving populations' columns pop_col).
-template <typename ST>
-void unpack_pops(const fuglbm_sim *s, const char *buf, double *g) {
-    const PopLayout<ST> P(s->N, s->Q, s->nx, (int64_t)s->ny * s->nz);
-    const int64_t rows = (int64_t)s->ny * s->nz;
-    for (int i = 0; i < s->N; ++i)
-        for (int a = 0; a < s->Q; ++a)
-            for (int64_t r = 0; r < rows; ++r) {
-                double *o = g + ((size_t)i * s->Q + a) * s->ns + (size_t)r * s->nx;
-                if (a == 0) {
-                    const double *src = (const double *)(buf + P.rest(r, i, 0));
-                    for (int x = 0; x < s->nx; ++x) o[x] = src[x];
-                } else {
-                    const ST *src = (const ST *)(buf + P.move(r, i, a, 0));
-                    for (int x = 0; x < s->nx; ++x) o[x] = (double)src[host_pop_col(s, a, x)];
-                }
-            }
-}
+}  // extern "C++"
 
-template <typename ST>
-void pack_pops(const fuglbm_sim *s, const double *g, char *buf) {
-    const PopLayout<ST> P(s->N, s->Q, s->nx, (int64_t)s->ny * s->nz);
-    const int64_t rows = (int64_t)s->ny * s->nz;
-    for (int i = 0; i < s->N; ++i)
-        for (int a = 0; a < s->Q; ++a)
-            for (int64_t r = 0; r < rows; ++r) {
-                const double *in = g + ((size_t)i * s->Q + a) * s->ns + (size_t)r * s->nx;
-                if (a == 0) {
-                    double *dst = (double *)(buf + P.rest(r, i, 0));
-                    for (int x = 0; x < s->nx; ++x) dst[x] = in[x];
-                } else {
-                    ST *dst = (ST *)(buf + P.move(r, i, a, 0));
-                    for (int x = 0; x < s->nx; ++x) dst[host_pop_col(s, a, x)] = (ST)in[x];
-                }
-            }
+// Checkpoint and restore: the device orders the populations as the host
+// array has them (planes [N][Q][sites] FP64, as many at a time as fit the
+// scratch buffer: all of them in FP64, at least five of FP32 storage), and
+// whole planes are copied.
+extern "C++" {
+template <class Fn>
+static fuglbm_status for_planes(const fuglbm_sim *s, Fn fn) {
+    const int total = s->N * s->Q;
+    const int most = (int)std::min<int64_t>(total, pop_bytes(s) / (s->ns * 8));
+    for (int p = 0; p < total; p += most) {
+        const fuglbm_status rc = fn(p, std::min(most, total - p));
+        if (rc != FUGLBM_OK) return rc;
+    }
+    return FUGLBM_OK;
 }
 }  // extern "C++"
 
 fuglbm_status fuglbm_read_populations(fuglbm_sim *s, double *g_out) {
     if (!s || !g_out) return fail(FUGLBM_EINVAL, "null argument");
-    HIP_TRY(hipStreamSynchronize(s->last_stream));
-    std::vector<char> tmp((size_t)pop_bytes(s));
-    HIP_TRY(hipMemcpy(tmp.data(), s->buf[s->parity], tmp.size(), hipMemcpyDeviceToHost));
-    if (s->fp32)
-        unpack_pops<float>(s, tmp.data(), g_out);
-    else
-        unpack_pops<double>(s, tmp.data(), g_out);
-    return FUGLBM_OK;
+    hipStream_t st = s->last_stream;
+    // the spare buffer is what the next step overwrites
+    char *scratch = (char *)s->buf[s->parity ^ 1];
+    Stage &g = *s->stage;
+    std::unique_lock<std::mutex> lk(g.use, std::try_to_lock);
+    const bool staged = lk.owns_lock() && g.ready();
+    return for_planes(s, [&](int p, int n) -> fuglbm_status {
+        char *host = (char *)(g_out + (size_t)p * s->ns);
+        const size_t bytes = (size_t)n * s->ns * 8;
+        HIP_TRY(launch_planes(s->lattice, s->fp32, true, s->N, s->nx, s->ny, s->nz, p, n,
+                              s->buf[s->parity], scratch, st));
+        if (staged) {
+            HIP_TRY(staged_copy(g, host, scratch, bytes, true, st));
+        } else {
+            HIP_TRY(hipStreamSynchronize(st));
+            HIP_TRY(hipMemcpy(host, scratch, bytes, hipMemcpyDeviceToHost));
+        }
+        return FUGLBM_OK;
+    });
 }
 
 fuglbm_status fuglbm_write_populations(fuglbm_sim *s, const double *g_in, int64_t step) {
     if (!s || !g_in) return fail(FUGLBM_EINVAL, "null argument");
     if (step < 0) return fail(FUGLBM_EINVAL, "step must be >= 0");
-    HIP_TRY(hipStreamSynchronize(s->last_stream));
-    std::vector<char> tmp((size_t)pop_bytes(s));
-    if (s->fp32)
-        pack_pops<float>(s, g_in, tmp.data());
-    else
-        pack_pops<double>(s, g_in, tmp.data());
-    HIP_TRY(hipMemcpy(s->buf[0], tmp.data(), tmp.size(), hipMemcpyHostToDevice));
+    hipStream_t st = s->last_stream;
+    char *scratch = (char *)s->buf[1];
+    Stage &g = *s->stage;
+    std::unique_lock<std::mutex> lk(g.use, std::try_to_lock);
+    const bool staged = lk.owns_lock() && g.ready();
+    HIP_TRY(hipStreamSynchronize(st));
+    fuglbm_status rc = for_planes(s, [&](int p, int n) -> fuglbm_status {
+        char *host = (char *)(g_in + (size_t)p * s->ns);
+        const size_t bytes = (size_t)n * s->ns * 8;
+        if (staged) {
+            HIP_TRY(staged_copy(g, host, scratch, bytes, false, st));
+        } else {
+            HIP_TRY(hipMemcpy(scratch, host, bytes, hipMemcpyHostToDevice));
+        }
+        HIP_TRY(launch_planes(s->lattice, s->fp32, false, s->N, s->nx, s->ny, s->nz, p, n,
+                              s->buf[0], scratch, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        return FUGLBM_OK;
+    });
+    if (rc != FUGLBM_OK) return rc;
     s->parity = 0;
     s->step = step;
     s->have_snap = false;
@@ -1237,6 +1443,7 @@ void fuglbm_destroy_sim(fuglbm_sim *s) {
     drop_graph(s);
     if (s->done) (void)hipEventDestroy(s->done);
     if (s->owned) (void)hipFree(s->base);
+    s->stage->drop_sim();
     delete s;
 }
 

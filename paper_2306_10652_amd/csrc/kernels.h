@@ -40,6 +40,11 @@ hipError_t launch_step_generic(int lattice, bool fp32, const SimConst *c, int nc
                                int nz, const void *gs, void *gd, double *rho_f, double *psi_f,
                                double *s_f, double *j_f, double *u_f, uint32_t *status,
                                bool keep_old, hipStream_t st);
+// Planes [p0, p0 + n) of a state's populations in host order (plane i Q + a:
+// population a of component i, [sites] FP64) <-> a population buffer:
+// out, buffer to planes; else planes to buffer (FP32 storage rounds).
+hipError_t launch_planes(int lattice, bool fp32, bool out, int ncomp, int nx, int ny, int nz,
+                         int p0, int n, void *buf, void *planes, hipStream_t st);
 // One member of a batched multi-pass step (fuglbm_step_many for simulations
 // on the multi-pass kernels).  A launch reads buf[parity ^ flip] and writes
 // the other buffer.  end[p]: work units of pass p through this member,
@@ -61,8 +66,8 @@ void generic_units(int lattice, int ncomp, int nx, int ny, int nz, int64_t units
 hipError_t launch_step_generic_batch(int lattice, bool fp32, bool keep_old,
                                      const GenMember *members, int nmembers,
                                      const int64_t total[3], int flip, hipStream_t st);
-// Macroscopic fields of a state: rho_i, RT ln f_i -> psi_i, s, j and (u_f
-// non-null) the force-corrected velocity.
+// Macroscopic fields of a state: rho_i, RT ln f_i (in psi_f), s, j and (u_f
+// non-null) psi_i and the force-corrected velocity.
 hipError_t launch_fields(int lattice, bool fp32, const SimConst *c, int nx, int ny, int nz,
                          const void *g, double *rho_f, double *psi_f, double *s_f, double *j_f,
                          double *u_f, uint32_t *status, hipStream_t st);
@@ -85,7 +90,7 @@ hipError_t launch_fused_d2q9(int ncomp, bool fp32, const FusedItem *items, int n
                              const FusedSim *sims, int flip, hipStream_t st);
 
 // The same step for tables whose items have at most `rows` (1 or 2) rows,
-// built for ncomp <= 10 (kernels_fused2d_block.hip).
+// built for ncomp <= 10 (fused2d_block.h).
 constexpr int FUSED_BLOCK_ROWS = 2;
 constexpr int FUSED_BLOCK_COMP = 10;
 hipError_t launch_fused_block(int ncomp, bool fp32, const FusedTable &t, int flip, hipStream_t st);
@@ -99,7 +104,7 @@ int fused_ws_blocks_per_cu(int ncomp, bool fp32);
 hipError_t launch_fused_d2q9_ws(int ncomp, bool fp32, const FusedItem *items, int nitems,
                                 const FusedSim *sims, int flip, hipStream_t st);
 
-// ---- D2Q9 steps at tau = 1 in field form (kernels_fields2d.hip) -----------
+// ---- D2Q9 steps at tau = 1 in field form (fields2d.h) -----------
 // One simulation: its population buffers (the run reads buf[parity ^ flip]
 // and writes its last state there again; the other buffer holds fields
 // between the steps) and workspace fields.  ld: elements from one component

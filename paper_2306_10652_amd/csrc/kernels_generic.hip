@@ -40,6 +40,41 @@ __global__ __launch_bounds__(TPB) void k_init(const SimConst *__restrict__ c,
     }
 }
 
+// Host order of the populations (launch_planes): one thread per site of one
+// plane; columns by pop_col.
+template <class L, typename ST, bool OUT>
+__global__ __launch_bounds__(TPB) void k_planes(int N, int nx, int64_t rows, int p0,
+                                                char *__restrict__ buf,
+                                                double *__restrict__ planes) {
+    const int64_t ns = (int64_t)nx * rows;
+    const int64_t s = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (s >= ns) return;
+    const int p = p0 + (int)blockIdx.y, i = p / L::Q, a = p % L::Q;
+    const int64_t row = s / nx;
+    const int x = (int)(s - row * nx);
+    const PopLayout<ST> P(N, L::Q, nx, rows);
+    double *q = planes + (int64_t)blockIdx.y * ns + s;
+    if (a == 0) {
+        double *g = (double *)(buf + P.rest(row, i, x));
+        if (OUT)
+            *q = *g;
+        else
+            *g = *q;
+    } else {
+        int xx = x;
+        // a is not a constant: the column of pop_col by direction
+        if (L::PULL_X) {
+            xx = x - L::ex(a);
+            xx = xx < 0 ? xx + nx : (xx >= nx ? xx - nx : xx);
+        }
+        ST *g = (ST *)(buf + P.move(row, i, a, xx));
+        if (OUT)
+            *q = (double)*g;
+        else
+            *g = (ST)*q;
+    }
+}
+
 // Each pass is a device function over one work unit (a block of TPB sites,
 // or a tile), called by the kernel of one simulation and by the batched
 // kernel, which finds the unit's simulation in a member table.
@@ -113,7 +148,7 @@ __device__ __forceinline__ void moments_eos_body(const SimConst *__restrict__ c,
     j_f[s] = jx;
     j_f[ns + s] = jy;
     if (L::D == 3) j_f[2 * ns + s] = jz;
-    if (bad) atomicOr(status, bad);
+    flag_status(status, bad);
 }
 
 template <class L, typename ST>
@@ -471,8 +506,8 @@ hipError_t fields_generic_t(const SimConst *c, int nx, int ny, int nz, const voi
     const unsigned nb = nblocks((int64_t)nx * ny * nz);
     hipLaunchKernelGGL((k_moments_eos<L, ST>), dim3(nb), dim3(TPB), 0, st, c, g, rho_f, psi_f,
                        s_f, j_f, status);
-    hipLaunchKernelGGL((k_interface<L>), dim3(nb), dim3(TPB), 0, st, c, s_f, psi_f);
     if (u_f) {
+        hipLaunchKernelGGL((k_interface<L>), dim3(nb), dim3(TPB), 0, st, c, s_f, psi_f);
         const unsigned vb = unit_blocks(TileGeom<L, TileV<L>>::count(nx, ny, nz));
         hipLaunchKernelGGL((k_velocity_t<L>), dim3(vb), dim3(TPB), 0, st, c, rho_f, psi_f, j_f,
                            u_f);
@@ -493,6 +528,29 @@ hipError_t launch_init(int lattice, bool fp32, const SimConst *c, int64_t ns, co
         else hipLaunchKernelGGL((k_init<D3Q19, double>), dim3(nb), dim3(TPB), 0, st, c, rho, g);
     }
     return hipGetLastError();
+}
+
+template <class L, typename ST>
+hipError_t planes_t(bool out, int N, int nx, int64_t rows, int p0, int n, void *buf, void *planes,
+                    hipStream_t st) {
+    const dim3 grid(nblocks((int64_t)nx * rows), n);
+    if (out)
+        hipLaunchKernelGGL((k_planes<L, ST, true>), grid, dim3(TPB), 0, st, N, nx, rows, p0,
+                           (char *)buf, (double *)planes);
+    else
+        hipLaunchKernelGGL((k_planes<L, ST, false>), grid, dim3(TPB), 0, st, N, nx, rows, p0,
+                           (char *)buf, (double *)planes);
+    return hipGetLastError();
+}
+
+hipError_t launch_planes(int lattice, bool fp32, bool out, int ncomp, int nx, int ny, int nz,
+                         int p0, int n, void *buf, void *planes, hipStream_t st) {
+    const int64_t rows = (int64_t)ny * nz;
+    if (lattice == 0)
+        return fp32 ? planes_t<D2Q9, float>(out, ncomp, nx, rows, p0, n, buf, planes, st)
+                    : planes_t<D2Q9, double>(out, ncomp, nx, rows, p0, n, buf, planes, st);
+    return fp32 ? planes_t<D3Q19, float>(out, ncomp, nx, rows, p0, n, buf, planes, st)
+                : planes_t<D3Q19, double>(out, ncomp, nx, rows, p0, n, buf, planes, st);
 }
 
 hipError_t launch_step_generic(int lattice, bool fp32, const SimConst *c, int ncomp, int nx, int ny,
