@@ -342,6 +342,41 @@ static FieldRun field_run(const fuglbm_sim *s, int rows) {
     return q;
 }
 
+// D3Q19 steps in field form (fields3d.h): tau = 1, planes within 32-bit byte
+// offsets.
+static bool field3_usable(const fuglbm_sim *s) {
+    return s->lattice == FUGLBM_D3Q19 && s->kernel == 1 && s->hc.omega == 1.0 && s->N <= field_max_comp() &&
+           (int64_t)s->nx * s->ny < ((int64_t)1 << 29) && s->ns < ((int64_t)1 << 31);
+}
+
+// The fields of set `set` of a run that reads buf[parity]: all in the spare
+// population buffer where they fit (else set 0, psi and u in the workspace).
+static GenMember field3_member(const fuglbm_sim *s, int parity, int set) {
+    GenMember g{};
+    g.c = s->dc;
+    g.buf[0] = s->buf[0];
+    g.buf[1] = s->buf[1];
+    g.status = s->status;
+    g.parity = parity;
+    const int64_t ns = s->ns, N = s->N;
+    double *b = (double *)s->buf[parity ^ 1];
+    if ((3 * N + 11) * ns * 8 <= pop_bytes(s)) {
+        g.rho_f = b + set * N * ns;
+        g.psi_f = b + 2 * N * ns;
+        b += 3 * N * ns;
+        g.u_f = b;
+        g.s_f = b + (3 + set) * ns;
+        g.j_f = b + (5 + 3 * set) * ns;
+    } else {
+        g.rho_f = set ? b : s->rho_f;
+        g.s_f = set ? b + N * ns : s->s_f;
+        g.j_f = set ? b + (N + 1) * ns : s->j_f;
+        g.psi_f = s->psi_f;
+        g.u_f = s->u_f;
+    }
+    return g;
+}
+
 static uint64_t next_sim_uid() {
     static uint64_t n = 0;
     return ++n;
@@ -454,29 +489,118 @@ hipError_t launch_field(const FieldRun &q, int ncomp, bool fp32, bool last, int 
     return e != hipSuccess ? e : launch_field_step2d(q, ncomp, fp32, last, set, st);
 }
 
-// n >= 1 steps in field form.  The populations end in the buffer they
-// started from (the other one held the fields), so no parity changes.
-// graph: a captured run of GRAPH_STEPS steps for this q (set 0 to set 0),
-// made when it is first needed.
-fuglbm_status run_field(const FieldRun &q, int ncomp, bool fp32, int64_t n, hipGraphExec_t &graph,
-                        hipStream_t st) {
-    HIP_TRY(launch_field_moments2d(q, fp32, st));
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
+}
+
+// n >= 1 steps in field form: first() makes set 0 from the populations,
+// step(set, stream) takes a set to the other one, last(set) to the
+// populations.  They end in the buffer they started from (the other one held
+// the fields), so no parity changes.  graph: a captured run of GRAPH_STEPS
+// steps (set 0 to set 0), made when it is first needed; a caller that
+// captures the stream gets plain launches up to the run length at which the
+// steps of the other forms come from a graph.
+template <class First, class Step, class Last>
+fuglbm_status field_steps(First first, Step step, Last last, int64_t n, hipGraphExec_t &graph,
+                          hipStream_t st) {
+    HIP_TRY(first());
     int64_t left = n - 1;
-    if (left >= 2 * GRAPH_STEPS || (graph && left >= GRAPH_STEPS)) {
+    if (left >= 2 * GRAPH_STEPS || (graph && left >= GRAPH_STEPS && !capturing(st))) {
         if (!graph) {
-            fuglbm_status rc = capture_steps(
-                [&](int k, hipStream_t cs) {
-                    return launch_field(q, ncomp, fp32, false, k & 1, cs);
-                },
-                graph, "field step graph");
+            fuglbm_status rc = capture_steps([&](int k, hipStream_t cs) { return step(k & 1, cs); },
+                                             graph, "field step graph");
             if (rc != FUGLBM_OK) return rc;
         }
         for (; left >= GRAPH_STEPS; left -= GRAPH_STEPS) HIP_TRY(hipGraphLaunch(graph, st));
     }
     int set = 0;
-    for (; left > 0; --left, set ^= 1) HIP_TRY(launch_field(q, ncomp, fp32, false, set, st));
-    HIP_TRY(launch_field(q, ncomp, fp32, true, set, st));
+    for (; left > 0; --left, set ^= 1) HIP_TRY(step(set, st));
+    HIP_TRY(last(set));
     return FUGLBM_OK;
+}
+
+fuglbm_status run_field(const FieldRun &q, int ncomp, bool fp32, int64_t n, hipGraphExec_t &graph,
+                        hipStream_t st) {
+    return field_steps([&] { return launch_field_moments2d(q, fp32, st); },
+                       [&](int set, hipStream_t to) {
+                           return launch_field(q, ncomp, fp32, false, set, to);
+                       },
+                       [&](int set) { return launch_field(q, ncomp, fp32, true, set, st); }, n,
+                       graph, st);
+}
+
+// ---- D3Q19 in field form --------------------------------------------------
+// Tiles of the stream kernel.  A workgroup collides W x R sites a plane for
+// (W - 4) x (R - 2) of output and zc + 2 planes for zc, so wide, tall and
+// long tiles waste least; but all of them should be resident at once, and a
+// SIMD works through its wavefronts one after another.  The cheapest of the
+// widths, heights and chunk lengths by
+//   cost = rounds x (zc + 2) x wavefronts per SIMD (at least 2: latency)
+//          x components,
+// planes of one wavefront that a SIMD works through.  Measured steps take
+// 12 us + 1.45 us x cost (N >= 5, 40^3 ... 128^3, both precisions, within 8 %).
+struct Shape3 {
+    int W, waves, zc;
+    double cost;
+};
+Shape3 field3_shape(const fuglbm_sim *s) {
+    const int most = s->fp32 ? 12 : 8, cus = compute_units();
+    Shape3 best{32, most, 1, 1e300};
+    for (int waves = 4; waves <= most; waves += 4)
+        for (int W = 16; W <= 64; W *= 2) {
+            const int R = 64 * waves / W, slots = cus * (12 / waves);
+            const int64_t cols = (int64_t)((s->nx + W - 5) / (W - 4)) * ((s->ny + R - 3) / (R - 2));
+            for (int zc = 1; zc <= s->nz; ++zc) {
+                const int64_t items = cols * ((s->nz + zc - 1) / zc);
+                const double rounds = (double)((items + slots - 1) / slots);
+                const int resident = (int)std::min<int64_t>(12 / waves, (items + cus - 1) / cus);
+                const double per_simd = std::max(2.0, waves * resident / 4.0);
+                const double cost = rounds * (zc + 2) * per_simd * s->N;
+                if (cost < best.cost) best = {W, waves, zc, cost};
+            }
+        }
+    return best;
+}
+
+// The field form moves a third of the bytes but collides the rims of its
+// tiles twice, and a chip of one or two short tiles per CU does little else.
+// The multi-pass step takes about 75 ps per site and component in FP64 and
+// 54 ps in FP32 storage (64^3, N = 10: 197 and 142 us), 100 and 70 ps where
+// rows are not whole 64-byte lines, so that it writes parts of them, and the
+// field step takes 1.45 us per unit of cost: it pays from ns N / cost =
+// 1.45 us / 75 ps = 19 300 (FP32: 26 900; parts of lines: 14 500, 20 700) on.
+bool field3_pays(const fuglbm_sim *s, int64_t n) {
+    if (n < 2 || !field3_usable(s)) return false;
+    const bool lines = s->nx % (s->fp32 ? 16 : 8) == 0;
+    const double from = s->fp32 ? (lines ? 26900.0 : 20700.0) : (lines ? 19300.0 : 14500.0);
+    return (double)s->ns * s->N >= from * field3_shape(s).cost;
+}
+
+FieldRun3 field3_run(const fuglbm_sim *s) {
+    FieldRun3 q{};
+    const Shape3 h = field3_shape(s);
+    const int R = 64 * h.waves / h.W;
+    q.f[0] = field3_member(s, s->parity, 0);
+    q.f[1] = field3_member(s, s->parity, 1);
+    q.ns = s->ns;
+    q.waves = h.waves;
+    q.tiles = {h.W, h.zc, (s->nx + h.W - 5) / (h.W - 4), (s->ny + R - 3) / (R - 2),
+               (s->nz + h.zc - 1) / h.zc};
+    q.nitems = (q.tiles.tx * q.tiles.ty * q.tiles.tz + 7) / 8 * 8;
+    generic_units(1, s->N, s->nx, s->ny, s->nz, q.total);
+    return q;
+}
+
+fuglbm_status run_field3(fuglbm_sim *s, int64_t n, hipStream_t st) {
+    const FieldRun3 q = field3_run(s);
+    const fuglbm_status rc = field_steps(
+        [&] { return launch_field_moments3(q, s->fp32, st); },
+        [&](int set, hipStream_t to) { return launch_field_step3(q, s->N, s->fp32, set, to); },
+        [&](int set) { return launch_field_last3(q, s->fp32, set, st); }, n,
+        s->fgraph[s->parity], st);
+    if (rc == FUGLBM_OK) s->step += n;
+    return rc;
 }
 
 // ---- rows-per-item autotuner ---------------------------------------------
@@ -1251,6 +1375,11 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *s, int64_t nsteps, void *hip_stream) {
         s->step += left;
         return mark_done(s, st);
     }
+    if (field3_pays(s, left)) {
+        fuglbm_status rc = run_field3(s, left, st);
+        if (rc != FUGLBM_OK) return rc;
+        return mark_done(s, st);
+    }
     // odd parity first so that graph replays start from buffer 0
     if (left > 0 && s->parity == 1 && left >= 2 * GRAPH_STEPS) {
         hipError_t e = launch_one_step(s, s->parity, st);
@@ -1901,6 +2030,16 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         ggroups[{s->lattice, s->fp32 ? 1 : 0, s->hc.omega != 1.0 ? 1 : 0}].push_back(s);
     for (auto &kv : ggroups) {
         auto &group = kv.second;
+        // members that each pay in field form fill the chip one by one
+        if (std::all_of(group.begin(), group.end(),
+                        [&](const fuglbm_sim *s) { return field3_pays(s, nsteps); })) {
+            for (auto *s : group) {
+                fuglbm_status rc = run_field3(s, nsteps, st);
+                if (rc != FUGLBM_OK) return rc;
+                s->last_stream = st;
+            }
+            continue;
+        }
         GenBatch &gb = gen_batches()[kv.first];
         // the table is shared state: launches queued on another stream must
         // finish before this call rebuilds or reuses it

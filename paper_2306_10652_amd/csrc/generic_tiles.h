@@ -196,53 +196,43 @@ __device__ __forceinline__ void put_pop(T *p, T v) {
 // the direction loop: g^eq_a - w_a rho = w_a rho sq_a and
 // F_a / w_a = 3 eF + 9 eu eF + 3 eu eG + K, where K depends on |e_a|^2 only
 // (weight classes |e|^2 = 1 and 2); the dot products with e_a add only its
-// non-zero components (0 * u is not folded away).  The moving populations
-// are pushed to x + e_a (periodic; in y and z only where pop_col says so),
-// the rest one stays.  In FP32 storage the moving populations are computed
+// non-zero components (0 * u is not folded away).  put(a, value) takes the
+// moving populations in direction order; the rest one is returned.  In FP32
+// storage the moving populations are computed
 // in FP32 arithmetic from the per-site terms rounded once (as in the fused
 // D2Q9 kernels), and the rest population is rho minus the FP64 sum of the
 // stored moving values (in direction order): the collision conserves each
-// component's mass, so this keeps it to FP64 rounding.  The FP32 loop
-// stores each direction before computing the next (a scheduling barrier):
-// left free, the compiler computes every direction first and holds them
-// all (109 VGPRs with FP64 arithmetic; 63 in order with FP32 arithmetic,
-// eight wavefronts per SIMD).
-template <class L, typename ST>
-__device__ __forceinline__ void collide_push_tau1(const PopLayout<ST> &P, char *gdb, int i, int x,
-                                                  int y, int z, int nx, int ny, int nz, double r,
-                                                  double ux, double uy, double uz, double Fx,
-                                                  double Fy, double Fz, double Gx, double Gy,
-                                                  double Gz, double omega, double fcoef) {
-    // the inputs as plain register values (empty register constraints, no
-    // instruction): otherwise a caller that has just computed F_i as a
-    // product lets the compiler fuse that product into e_a.F, and the
-    // rounding would depend on the caller
+// component's mass, so this keeps it to FP64 rounding.
+template <class L, typename ST, class Put>
+__device__ __forceinline__ double collide_tau1(double r, double ux, double uy, double uz, double Fx,
+                                               double Fy, double Fz, double Gx, double Gy,
+                                               double Gz, Put put) {
+    // every rounding written out, so that none depends on the caller: no
+    // contraction by the compiler, and the inputs as plain register values
+    // (empty register constraints, no instruction)
+#pragma clang fp contract(off)
     asm volatile("" : "+v"(r), "+v"(ux), "+v"(uy), "+v"(uz), "+v"(Fx), "+v"(Fy), "+v"(Fz),
                  "+v"(Gx), "+v"(Gy), "+v"(Gz));
-    const double uu = ux * ux + uy * uy + uz * uz;
-    const double Fu = Fx * ux + Fy * uy + Fz * uz;
-    const double Gu = Gx * ux + Gy * uy + Gz * uz;
+    double uu = fma(ux, ux, uy * uy), Fu = fma(Fx, ux, Fy * uy), Gu = fma(Gx, ux, Gy * uy);
+    if constexpr (L::D == 3) {
+        uu = fma(uz, uz, uu);
+        Fu = fma(Fz, uz, Fu);
+        Gu = fma(Gz, uz, Gu);
+    }
     const double c0 = -1.5 * uu;
-    const double K1 = -3.0 * Fu - Gu + 0.5 * (3.0 - (double)L::D) * Gu;
-    const double K2 = -3.0 * Fu - Gu + 0.5 * (6.0 - (double)L::D) * Gu;
-    const double A1 = omega * L::w(1) * r, A2 = omega * L::w(L::Q - 1) * r;
-    const double B1 = fcoef * L::w(1), B2 = fcoef * L::w(L::Q - 1);
+    const double K0 = fma(-3.0, Fu, -Gu);
+    const double K1 = fma(0.5 * (3.0 - (double)L::D), Gu, K0);
+    const double K2 = fma(0.5 * (6.0 - (double)L::D), Gu, K0);
+    const double A1 = L::w(1) * r, A2 = L::w(L::Q - 1) * r;
+    const double B1 = 0.5 * L::w(1), B2 = 0.5 * L::w(L::Q - 1);   // c = 1 - 1/(2 tau)
     auto edot = [](int a, auto ex, auto ey, auto ez) {
         const int cx = L::ex(a), cy = L::ey(a), cz = L::ez(a);
         const auto tx = cx > 0 ? ex : -ex, ty = cy > 0 ? ey : -ey, tz = cz > 0 ? ez : -ez;
         if (cx != 0) return cy != 0 ? tx + ty : (cz != 0 ? tx + tz : tx);
         return cy != 0 ? (cz != 0 ? ty + tz : ty) : tz;
     };
-    // push; in x only where the layout does (pop_col)
-    auto store = [&](int a, ST v) {
-        int xx = L::PULL_X ? x : x + L::ex(a), yy = y + L::ey(a), zz = z + L::ez(a);
-        xx = xx < 0 ? xx + nx : (xx >= nx ? xx - nx : xx);
-        yy = yy < 0 ? yy + ny : (yy >= ny ? yy - ny : yy);
-        zz = zz < 0 ? zz + nz : (zz >= nz ? zz - nz : zz);
-        put_pop<L>((ST *)(gdb + P.move((int64_t)yy + (int64_t)ny * zz, i, a, xx)), v);
-    };
-    // no loads: unrolled, the lattice vectors, weights and destination rows
-    // fold to constants per direction
+    // no loads: unrolled, the lattice vectors, weights and destinations fold
+    // to constants per direction
     if constexpr (sizeof(ST) == 4) {
         const float fux = (float)ux, fuy = (float)uy, fuz = (float)uz;
         const float fFx = (float)Fx, fFy = (float)Fy, fFz = (float)Fz;
@@ -260,10 +250,9 @@ __device__ __forceinline__ void collide_push_tau1(const PopLayout<ST> &P, char *
             const float q = fmaf(eF, fmaf(9.0f, eu, 3.0f), fmaf(3.0f * eu, eG, e1 ? fK1 : fK2));
             const float v = fmaf(e1 ? fA1 : fA2, sq, (e1 ? fB1 : fB2) * q);
             msum += (double)v;
-            store(a, (ST)v);
-            __builtin_amdgcn_sched_barrier(0);
+            put(a, (ST)v);
         }
-        put_pop<L>((double *)(gdb + P.rest((int64_t)y + (int64_t)ny * z, i, x)), r - msum);
+        return r - msum;
     } else {
 #pragma unroll
         for (int a = 1; a < L::Q; ++a) {
@@ -273,12 +262,34 @@ __device__ __forceinline__ void collide_push_tau1(const PopLayout<ST> &P, char *
             const bool e1 = L::ex(a) * L::ex(a) + L::ey(a) * L::ey(a) + L::ez(a) * L::ez(a) == 1;
             const double sq = fma(eu, fma(4.5, eu, 3.0), c0);
             const double q = fma(eF, fma(9.0, eu, 3.0), fma(3.0 * eu, eG, e1 ? K1 : K2));
-            store(a, (ST)fma(e1 ? A1 : A2, sq, (e1 ? B1 : B2) * q));
+            put(a, (ST)fma(e1 ? A1 : A2, sq, (e1 ? B1 : B2) * q));
         }
-        put_pop<L>((double *)(gdb + P.rest((int64_t)y + (int64_t)ny * z, i, x)),
-                   collide_one<L>(0, 0.0, r, ux, uy, uz, Fx, Fy, Fz, Gx, Gy, Gz, uu, Fu, Gu, omega,
-                                  fcoef));
+        // g^eq_0 + c F_0
+        return fma(0.5 * L::w(0), fma(-0.5 * (double)L::D, Gu, K0), fma(L::w(0) * r, c0, r));
     }
+}
+
+// The same with the populations pushed to x + e_a (periodic; in y and z only
+// where pop_col says so).  FP32 storage stores each direction before
+// computing the next (a scheduling barrier): left free, the compiler computes
+// every direction first and holds them all (109 VGPRs with FP64 arithmetic;
+// 63 in order with FP32 arithmetic, eight wavefronts per SIMD).
+template <class L, typename ST>
+__device__ __forceinline__ void collide_push_tau1(const PopLayout<ST> &P, char *gdb, int i, int x,
+                                                  int y, int z, int nx, int ny, int nz, double r,
+                                                  double ux, double uy, double uz, double Fx,
+                                                  double Fy, double Fz, double Gx, double Gy,
+                                                  double Gz) {
+    auto store = [&](int a, ST v) {
+        int xx = L::PULL_X ? x : x + L::ex(a), yy = y + L::ey(a), zz = z + L::ez(a);
+        xx = xx < 0 ? xx + nx : (xx >= nx ? xx - nx : xx);
+        yy = yy < 0 ? yy + ny : (yy >= ny ? yy - ny : yy);
+        zz = zz < 0 ? zz + nz : (zz >= nz ? zz - nz : zz);
+        put_pop<L>((ST *)(gdb + P.move((int64_t)yy + (int64_t)ny * zz, i, a, xx)), v);
+        if constexpr (sizeof(ST) == 4) __builtin_amdgcn_sched_barrier(0);
+    };
+    const double rest = collide_tau1<L, ST>(r, ux, uy, uz, Fx, Fy, Fz, Gx, Gy, Gz, store);
+    put_pop<L>((double *)(gdb + P.rest((int64_t)y + (int64_t)ny * z, i, x)), rest);
 }
 
 // Collision of component i at one site at tau != 1 (Eq. (1a)-(1c)): reads

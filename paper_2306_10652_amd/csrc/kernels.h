@@ -141,3 +141,25 @@ hipError_t launch_field_eos2d(const FieldRun &q, int ncomp, int set, hipStream_t
 // one step from set `set` to the other one, or (last) to the populations
 hipError_t launch_field_step2d(const FieldRun &q, int ncomp, bool fp32, bool last, int set,
                                hipStream_t st);
+
+// ---- D3Q19 steps at tau = 1 in field form (fields3d.h) --------------------
+// Tiles of the stream kernel: W - 4 columns, (threads / W) - 2 rows, zc planes;
+// how many of them there are along x, y, z.
+struct Tiles3 {
+    int32_t W, zc, tx, ty, tz;
+};
+// What the steps of a run are launched over: the two sets of fields.
+struct FieldRun3 {
+    GenMember f[2];
+    int64_t ns;
+    int nitems;           // workgroups of the stream kernel
+    int waves;            // wavefronts of one (FP32 storage: at most 12, else 8)
+    Tiles3 tiles;
+    int64_t total[3];     // work units as of GenMember::end
+};
+// populations -> set 0 with its psi
+hipError_t launch_field_moments3(const FieldRun3 &q, bool fp32, hipStream_t st);
+// one step from set `set` to the other one with its psi
+hipError_t launch_field_step3(const FieldRun3 &q, int ncomp, bool fp32, int set, hipStream_t st);
+// the last step: from set `set` to the populations
+hipError_t launch_field_last3(const FieldRun3 &q, bool fp32, int set, hipStream_t st);

@@ -281,7 +281,7 @@ __device__ __forceinline__ void collide_body(const SimConst *__restrict__ c,
         uy = u_f[ns + s];
         uz = (L::D == 3) ? u_f[2 * ns + s] : 0.0;
     }
-    const double omega = c->omega, fcoef = c->fcoef;
+    [[maybe_unused]] const double omega = c->omega, fcoef = c->fcoef;
     const char *gsb = (const char *)gs;
     char *gdb = (char *)gd;
     {
@@ -300,7 +300,7 @@ __device__ __forceinline__ void collide_body(const SimConst *__restrict__ c,
                                      Fy, Fz, Gx, Gy, Gz, omega, fcoef);
         else
             collide_push_tau1<L, ST>(P, gdb, i, T.x, T.y, T.z, nx, ny, nz, r, ux, uy, uz, Fx, Fy,
-                                     Fz, Gx, Gy, Gz, omega, fcoef);
+                                     Fz, Gx, Gy, Gz);
     }
 }
 
@@ -516,6 +516,8 @@ hipError_t fields_generic_t(const SimConst *c, int nx, int ny, int nz, const voi
 }
 
 }  // namespace
+
+#include "fields3d.h"
 
 hipError_t launch_init(int lattice, bool fp32, const SimConst *c, int64_t ns, const double *rho,
                        void *g, hipStream_t st) {
