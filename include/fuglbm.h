@@ -190,7 +190,9 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *sim, int64_t nsteps, void *hip_stream);
  * into one member table per group (each of the four multi-pass kernels
  * launched once per step for the whole group).  Results are bitwise those
  * of stepping each simulation alone.  Handles must be distinct.
- * Asynchronous on hip_stream. */
+ * Asynchronous on hip_stream.  Several groups may run beside each other on
+ * streams of the library, which wait for hip_stream's earlier work and which
+ * its later work waits for. */
 fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count, int64_t nsteps,
                                void *hip_stream);
 

@@ -7,6 +7,7 @@
 #include <climits>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -491,7 +492,11 @@ hipError_t launch_field(const FieldRun &q, int ncomp, bool fp32, bool last, int 
 
 bool capturing(hipStream_t st) {
     hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(st, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return c != hipStreamCaptureStatusNone;
 }
 
 // n >= 1 steps in field form: first() makes set 0 from the populations,
@@ -856,6 +861,49 @@ fuglbm_status autotune_rows(fuglbm_sim *s, hipStream_t st) {
     return set_rows(s, tn.rows, st);
 }
 
+// ---- side streams of a batch ----------------------------------------------
+// The groups of a batch (fuglbm_step_many) do not depend on each other, and
+// one of a few small grids leaves most of the chip idle: beside the caller's
+// stream they run on LANES - 1 side streams, which wait for what the caller's
+// stream holds and which it waits for in turn before the call's work counts
+// as done.  Four in all, the hardware queues of a process.  Held while any
+// simulation exists; a call that finds them in use by another thread runs
+// its groups one after another.
+constexpr int LANES = 4;
+
+struct Lanes {
+    std::mutex use;             // held by the call that enqueues on them
+    hipStream_t st[LANES] = {};   // st[0] unused: the caller's
+    hipEvent_t fork = nullptr, join[LANES] = {};
+
+    // with `use` held
+    bool ready() {
+        if (!fork && hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess)
+            fork = nullptr;
+        bool ok = fork != nullptr;
+        for (int k = 1; k < LANES && ok; ++k) {
+            if (!st[k] && hipStreamCreateWithFlags(&st[k], hipStreamNonBlocking) != hipSuccess)
+                st[k] = nullptr;
+            if (!join[k] && hipEventCreateWithFlags(&join[k], hipEventDisableTiming) != hipSuccess)
+                join[k] = nullptr;
+            ok = st[k] && join[k];
+        }
+        if (!ok) (void)hipGetLastError();
+        return ok;
+    }
+    void release() {
+        std::lock_guard<std::mutex> g(use);
+        for (int k = 1; k < LANES; ++k) {
+            if (st[k]) (void)hipStreamDestroy(st[k]);
+            if (join[k]) (void)hipEventDestroy(join[k]);
+            st[k] = nullptr;
+            join[k] = nullptr;
+        }
+        if (fork) (void)hipEventDestroy(fork);
+        fork = nullptr;
+    }
+};
+
 // ---- copies between device and caller memory ------------------------------
 // Pinned staging shared by the read-outs and checkpoints of the process: a
 // small block for totals and status words, and a ring of slots that bulk
@@ -872,6 +920,7 @@ struct Stage {
     hipEvent_t ev[STAGE_SLOTS] = {};
     std::mutex life;
     int sims = 0;               // live simulations
+    Lanes lanes;
 
     char *slot(int64_t k) const { return mem + STAGE_SMALL + (k % STAGE_SLOTS) * STAGE_SLOT; }
     // with `use` held
@@ -898,6 +947,7 @@ struct Stage {
     void drop_sim() {
         std::lock_guard<std::mutex> g(life);
         if (--sims > 0) return;
+        lanes.release();
         std::lock_guard<std::mutex> u(use);
         if (mem) (void)hipHostFree(mem);
         mem = nullptr;
@@ -1931,6 +1981,153 @@ void forget_sim_in_batches(const fuglbm_sim *s) {
     }
 }
 
+// ---- the groups of a batch ------------------------------------------------
+namespace {
+
+// nsteps steps of a group on the fused kernels (its table, at parity flip).
+fuglbm_status step_group(BatchTable &bt, const std::vector<fuglbm_sim *> &group, int nc, bool f32,
+                         int flip, int64_t nsteps, hipStream_t st) {
+    int64_t left = nsteps;
+    if (field_pays(bt.tune, left)) {
+        bt.frun.flip = flip;
+        fuglbm_status rc = run_field(bt.frun, nc, f32, left, bt.fgraph[flip], st);
+        if (rc != FUGLBM_OK) return rc;
+        for (auto *s : group) s->step += nsteps;
+        return FUGLBM_OK;
+    }
+    if (left >= 2 * GRAPH_STEPS && flip == 1) {
+        hipError_t e = launch_fused(bt.kernel, nc, f32, bt.table(), flip, st);
+        if (e != hipSuccess) return hip_fail(e, "batched step launch");
+        flip = 0;
+        --left;
+    }
+    if (left >= GRAPH_STEPS && flip == 0) {
+        // replay a captured run of GRAPH_STEPS launches (even: parity returns)
+        fuglbm_status rc = batch_graph(bt, nc, f32);
+        if (rc != FUGLBM_OK) return rc;
+        while (left >= GRAPH_STEPS) {
+            HIP_TRY(hipGraphLaunch(bt.graph, st));
+            left -= GRAPH_STEPS;
+        }
+    }
+    for (; left > 0; --left) {
+        hipError_t e = launch_fused(bt.kernel, nc, f32, bt.table(), flip, st);
+        if (e != hipSuccess) return hip_fail(e, "batched step launch");
+        flip ^= 1;
+    }
+    for (auto *s : group) {
+        s->parity ^= (int)(nsteps & 1);
+        s->step += nsteps;
+    }
+    return FUGLBM_OK;
+}
+
+// The same on the multi-pass kernels.
+fuglbm_status step_gen_group(GenBatch &gb, const std::vector<fuglbm_sim *> &group, int flip,
+                             int64_t nsteps, hipStream_t st) {
+    int64_t left = nsteps;
+    if (left >= 2 * GRAPH_STEPS && flip == 1) {
+        hipError_t e = gen_batch_step(gb, flip, st);
+        if (e != hipSuccess) return hip_fail(e, "batched multi-pass step launch");
+        flip = 0;
+        --left;
+    }
+    if (left >= GRAPH_STEPS && flip == 0) {
+        // replay a captured run of GRAPH_STEPS steps (even: parity returns)
+        fuglbm_status rc = gen_batch_graph(gb);
+        if (rc != FUGLBM_OK) return rc;
+        while (left >= GRAPH_STEPS) {
+            HIP_TRY(hipGraphLaunch(gb.graph, st));
+            left -= GRAPH_STEPS;
+        }
+    }
+    for (; left > 0; --left) {
+        hipError_t e = gen_batch_step(gb, flip, st);
+        if (e != hipSuccess) return hip_fail(e, "batched multi-pass step launch");
+        flip ^= 1;
+    }
+    for (auto *s : group) {
+        s->parity ^= (int)(nsteps & 1);
+        s->step += nsteps;
+    }
+    return FUGLBM_OK;
+}
+
+// Steps of a group on a stream, and about how long one takes (us).
+struct GroupTask {
+    double cost;
+    std::function<fuglbm_status(hipStream_t)> run;
+};
+
+double group_cost(const std::vector<fuglbm_sim *> &group) {
+    double c = 0.0, least = 0.0;
+    for (auto *s : group) {
+        const bool d3 = s->lattice == FUGLBM_D3Q19;
+        c += (d3 ? 60e-6 : 15e-6) * (double)s->ns * s->N;
+        least = std::max(least, d3 ? 30.0 : 8.0);
+    }
+    return least + c;
+}
+
+// Every task once, on st or beside it, done as far as st is concerned when st
+// has done what this call enqueued on it.  The tasks go longest first to the
+// lane with the least to do.
+//
+// A step of a small group is launch and barrier latency that leaves the chip
+// idle, so groups beside each other cost little more than the longest: us a
+// step at 200 steps, one after another / in lanes: 8 requests of 104^2 ...
+// 240^2 and 40^3, N = 3 ... 9, FP32 storage 108 / 61; the same at 62^2 ...
+// 144^2 and 24^3, FP64 85 / 45; 20 requests 254 / 185, at twice the size
+// 866 / 762; 62^2 x 6 and 72^2 x 8 FP64 14.6 / 9.5.  Handing over to the
+// side streams and back takes 25 to 30 us once: at one step the pair takes
+// 31 / 56 us, at eight 17.3 / 17.2 us a step.  So lanes are taken where what
+// they hide is estimated at twice that.
+constexpr double LANE_US = 60.0;
+
+fuglbm_status run_tasks(std::vector<GroupTask> &tasks, int64_t nsteps, hipStream_t st) {
+    Lanes &L = device_stage().lanes;
+    std::unique_lock<std::mutex> lock(L.use, std::defer_lock);
+    double all = 0.0, longest = 0.0;
+    for (auto &t : tasks) {
+        all += t.cost;
+        longest = std::max(longest, t.cost);
+    }
+    const bool side = (all - longest) * (double)nsteps >= LANE_US && !capturing(st) &&
+                      lock.try_lock() && L.ready();
+    if (!side) {
+        for (auto &t : tasks) {
+            fuglbm_status rc = t.run(st);
+            if (rc != FUGLBM_OK) return rc;
+        }
+        return FUGLBM_OK;
+    }
+    std::stable_sort(tasks.begin(), tasks.end(),
+                     [](const GroupTask &a, const GroupTask &b) { return a.cost > b.cost; });
+    const int n = std::min<int>(LANES, (int)tasks.size());
+    HIP_TRY(hipEventRecord(L.fork, st));
+    for (int k = 1; k < n; ++k) HIP_TRY(hipStreamWaitEvent(L.st[k], L.fork, 0));
+    double load[LANES] = {};
+    fuglbm_status rc = FUGLBM_OK;
+    for (auto &t : tasks) {
+        const int k = (int)(std::min_element(load, load + n) - load);
+        load[k] += t.cost;
+        rc = t.run(k ? L.st[k] : st);
+        if (rc != FUGLBM_OK) break;
+    }
+    // also after an error: nothing may be left running beside st
+    for (int k = 1; k < n; ++k) {
+        hipError_t e = hipEventRecord(L.join[k], L.st[k]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(st, L.join[k], 0);
+        if (e != hipSuccess) {
+            (void)hipStreamSynchronize(L.st[k]);
+            if (rc == FUGLBM_OK) rc = hip_fail(e, "joining a side stream");
+        }
+    }
+    return rc;
+}
+
+}  // namespace
+
 extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count, int64_t nsteps,
                                           void *hip_stream) {
     const TraceRange trace_range("fuglbm_step_many");
@@ -1959,6 +2156,9 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         fuglbm_status rc = order_after(sims[k], st);
         if (rc != FUGLBM_OK) return rc;
     }
+    // what each group still needs of the host (tables, tuning) on st, and its
+    // steps as a task
+    std::vector<GroupTask> tasks;
     for (auto &kv : groups) {
         auto &group = kv.second;
         BatchTable &bt = batch_tables()[kv.first];
@@ -1978,51 +2178,16 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         }
         const int nc = kv.first.first;
         const bool f32 = kv.first.second != 0;
-        int64_t left = nsteps;
         if (!same) {
             bt.tune = Tuned{};
-            fuglbm_status rc = left > 0 ? tune_batch(bt, group, nc, f32, st)
-                                        : build_batch(bt, group, st);
+            fuglbm_status rc = nsteps > 0 ? tune_batch(bt, group, nc, f32, st)
+                                          : build_batch(bt, group, st);
             if (rc != FUGLBM_OK) return rc;
             flip = 0;
         }
-        if (field_pays(bt.tune, left)) {
-            bt.frun.flip = flip;
-            fuglbm_status rc = run_field(bt.frun, nc, f32, left, bt.fgraph[flip], st);
-            if (rc != FUGLBM_OK) return rc;
-            for (auto *s : group) {
-                s->step += nsteps;
-                s->last_stream = st;
-            }
-            continue;
-        }
-        if (left >= 2 * GRAPH_STEPS && flip == 1) {
-            hipError_t e =
-                launch_fused(bt.kernel, nc, f32, bt.table(), flip, st);
-            if (e != hipSuccess) return hip_fail(e, "batched step launch");
-            flip = 0;
-            --left;
-        }
-        if (left >= GRAPH_STEPS && flip == 0) {
-            // replay a captured run of GRAPH_STEPS launches (even: parity returns)
-            fuglbm_status rc = batch_graph(bt, nc, f32);
-            if (rc != FUGLBM_OK) return rc;
-            while (left >= GRAPH_STEPS) {
-                HIP_TRY(hipGraphLaunch(bt.graph, st));
-                left -= GRAPH_STEPS;
-            }
-        }
-        for (; left > 0; --left) {
-            hipError_t e =
-                launch_fused(bt.kernel, nc, f32, bt.table(), flip, st);
-            if (e != hipSuccess) return hip_fail(e, "batched step launch");
-            flip ^= 1;
-        }
-        for (auto *s : group) {
-            s->parity ^= (int)(nsteps & 1);
-            s->step += nsteps;
-            s->last_stream = st;
-        }
+        tasks.push_back({group_cost(group), [&bt, &group, nc, f32, flip, nsteps](hipStream_t to) {
+                             return step_group(bt, group, nc, f32, flip, nsteps, to);
+                         }});
     }
     // multi-pass members: one table per (lattice, precision, tau != 1)
     std::map<std::tuple<int, int, int>, std::vector<fuglbm_sim *>> ggroups;
@@ -2033,11 +2198,13 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         // members that each pay in field form fill the chip one by one
         if (std::all_of(group.begin(), group.end(),
                         [&](const fuglbm_sim *s) { return field3_pays(s, nsteps); })) {
-            for (auto *s : group) {
-                fuglbm_status rc = run_field3(s, nsteps, st);
-                if (rc != FUGLBM_OK) return rc;
-                s->last_stream = st;
-            }
+            tasks.push_back({group_cost(group), [&group, nsteps](hipStream_t to) {
+                                 for (auto *s : group) {
+                                     fuglbm_status rc = run_field3(s, nsteps, to);
+                                     if (rc != FUGLBM_OK) return rc;
+                                 }
+                                 return FUGLBM_OK;
+                             }});
             continue;
         }
         GenBatch &gb = gen_batches()[kv.first];
@@ -2063,32 +2230,13 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
             if (rc != FUGLBM_OK) return rc;
             flip = 0;
         }
-        int64_t left = nsteps;
-        if (left >= 2 * GRAPH_STEPS && flip == 1) {
-            hipError_t e = gen_batch_step(gb, flip, st);
-            if (e != hipSuccess) return hip_fail(e, "batched multi-pass step launch");
-            flip = 0;
-            --left;
-        }
-        if (left >= GRAPH_STEPS && flip == 0) {
-            // replay a captured run of GRAPH_STEPS steps (even: parity returns)
-            fuglbm_status rc = gen_batch_graph(gb);
-            if (rc != FUGLBM_OK) return rc;
-            while (left >= GRAPH_STEPS) {
-                HIP_TRY(hipGraphLaunch(gb.graph, st));
-                left -= GRAPH_STEPS;
-            }
-        }
-        for (; left > 0; --left) {
-            hipError_t e = gen_batch_step(gb, flip, st);
-            if (e != hipSuccess) return hip_fail(e, "batched multi-pass step launch");
-            flip ^= 1;
-        }
-        for (auto *s : group) {
-            s->parity ^= (int)(nsteps & 1);
-            s->step += nsteps;
-            s->last_stream = st;
-        }
+        tasks.push_back({group_cost(group), [&gb, &group, flip, nsteps](hipStream_t to) {
+                             return step_gen_group(gb, group, flip, nsteps, to);
+                         }});
+    }
+    {
+        fuglbm_status rc = run_tasks(tasks, nsteps, st);
+        if (rc != FUGLBM_OK) return rc;
     }
     for (int k = 0; k < count; ++k) {
         if (sims[k]->sticky) continue;
