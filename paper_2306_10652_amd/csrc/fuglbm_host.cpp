@@ -693,13 +693,20 @@ std::map<std::tuple<int, int, int, int>, Tuned> &tune_cache() {
 }
 
 // Rows per item of the field form whose rounds over the resident workgroups
-// cost least (a workgroup takes rows + 6 lead rows).
-int field_model_rows(int64_t strip_rows, int ny, int ncomp) {
-    const int64_t slots = (int64_t)compute_units() * field_blocks_per_cu2d(ncomp);
+// cost least (a workgroup takes rows + 6 lead rows), with the items of each
+// simulation counted as they are cut: 1024^2, N = 10 on 256 slots takes 74
+// rows (252 items in one round, us a step), where strip rows in total would
+// give 72 (270 items, two rounds).
+int field_model_rows(const std::vector<const fuglbm_sim *> &sims) {
+    int ny = 1;
+    for (auto *s : sims) ny = std::max(ny, s->ny);
+    const int64_t slots = (int64_t)compute_units() * field_blocks_per_cu2d(sims[0]->N);
     int best = 1;
     int64_t best_cost = INT64_MAX;
     for (int rows = 1; rows <= ny; ++rows) {
-        const int64_t items = (strip_rows + rows - 1) / rows;
+        int64_t items = 0;
+        for (auto *s : sims)
+            items += (int64_t)((s->nx + FUSED_OUT - 1) / FUSED_OUT) * ((s->ny + rows - 1) / rows);
         const int64_t cost = (items + slots - 1) / slots * (rows + 6);
         if (cost < best_cost) {
             best_cost = cost;
@@ -842,10 +849,8 @@ fuglbm_status autotune_rows(fuglbm_sim *s, hipStream_t st) {
         }
         tn.fused_ms = best_ms / (2 * TUNE_LAUNCHES);
         if (field_usable(s)) {
-            const int64_t strips = (s->nx + FUSED_OUT - 1) / FUSED_OUT;
             fuglbm_status rc = time_field(
-                tune_candidates(s->ny, field_model_rows(strips * s->ny, s->ny, s->N)), s->N,
-                s->fp32, st,
+                tune_candidates(s->ny, field_model_rows({s})), s->N, s->fp32, st,
                 [&](int r, FieldRun &q) {
                     q = field_run(s, r);
                     return FUGLBM_OK;
@@ -1850,7 +1855,7 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
     fuglbm_status rc = FUGLBM_OK;
     if (field) {
         rc = time_field(
-            tune_candidates(ny_max, field_model_rows(strip_rows, ny_max, nc)), nc, f32, st,
+            tune_candidates(ny_max, field_model_rows({group.begin(), group.end()})), nc, f32, st,
             [&](int r, FieldRun &q) {
                 fuglbm_status e = build_field_batch(bt, group, r, st);
                 q = bt.frun;
