@@ -18,13 +18,18 @@
 // bitwise the same state.
 //
 // Measured on 128^3, N = 10 (us a step, multi-pass before): FP64 1875 ->
-// 1023 (velocity 125, k_stream3 790, k_eos3 110), FP32 storage 1209 -> 930
-// (128, 690, 113); 100^3: 966 -> 484 and 704 -> 465.  What bounds k_stream3
-// is VALU work (64 % busy with 2 to 3 wavefronts a SIMD, 2.7 GB at 3.4 TB/s):
-// 490 instructions a plane of a wavefront, of which its tiles' rims waste
-// 30 to 40 %.  Taken back: the plane loop unrolled by three to spare the
-// copies of the ring of planes (FP64 232 registers, FP32 55 spills).
+// 992 (velocity 125, k_stream3 750, k_eos3 110), FP32 storage 1211 -> 914
+// (128, 670, 113); 75 64 50, N = 9: 256 -> 130 and 153 -> 122.  What bounds
+// k_stream3 is VALU work (64 % busy with 2 to 3 wavefronts a SIMD, 2.7 GB at
+// 3.6 TB/s): 430 to 490 instructions a plane of a wavefront, of which the
+// rims of its tiles waste a quarter to a third.  The rim planes, which only
+// hand five populations into the chunk, once took all of that (75 64 50 FP32
+// storage 139 us, 50 120 24 FP64 129 -> 109).  Taken back: the plane loop
+// unrolled by three to spare the copies of the ring of planes (FP64 232
+// registers, FP32 55 spills).
 #pragma once
+
+#include <type_traits>
 
 #include "fused_common.h"
 #include "generic_tiles.h"
@@ -220,20 +225,23 @@ __global__ __launch_bounds__(64 * WAVES, sizeof(ST) == 4 ? 3 : 2) void k_stream3
         double r5 = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
         ST v7 = 0, v8 = 0, v9 = 0, v10 = 0, v11 = 0, v14 = 0, v15 = 0, v18 = 0;
         ST u5 = 0, u11 = 0, u14 = 0, u15 = 0, u18 = 0;
-        for (int z = z0 - 1; z <= z0 + nzc; ++z) {
+        // the rim planes (z0 - 1, below, and z0 + nzc, above) give the
+        // chunk the five populations that move into it and nothing else
+        auto step = [&](int z, auto below, auto above) {
+            constexpr bool BELOW = decltype(below)::value, ABOVE = decltype(above)::value;
             const Plane ht = plane_of(q.hs, q.hc, q.hn), pt = plane_of(q.ps, q.pc, q.pn);
             const int64_t zo = plane * zwrap(z);
             const double ux = at(gc.u_f + zo, oc), uy = at(gc.u_f + ns + zo, oc),
                          uz = at(gc.u_f + 2 * ns + zo, oc);
-            if (z < z0 + nzc) q = load(z + 2);
+            if constexpr (!ABOVE) q = load(z + 2);
             // j of the components before, and s for plane z - 1
             double Jx = 0.0, Jy = 0.0, Jz = 0.0, sv = 0.0;
-            if (i > 0 && z >= z0 && z < z0 + nzc) {
+            if (!BELOW && !ABOVE && i > 0) {
                 Jx = at(gn.j_f + zo, oc);
                 Jy = at(gn.j_f + ns + zo, oc);
                 Jz = at(gn.j_f + 2 * ns + zo, oc);
             }
-            if (i > 0 && z > z0) sv = at(gn.s_f + plane * (z - 1), oc);
+            if (!BELOW && i > 0 && z > z0) sv = at(gn.s_f + plane * (z - 1), oc);
             double gx, gy, gz, Gx, Gy, Gz;
             grad19(pb, po, pt, gx, gy, gz);
             grad19(hb, ho, ht, Gx, Gy, Gz);
@@ -246,12 +254,14 @@ __global__ __launch_bounds__(64 * WAVES, sizeof(ST) == 4 ? 3 : 2) void k_stream3
             ho = ht;
             pb = po;
             po = pt;
-            // the populations that move in y, by direction
+            // the populations that move in y, by direction (those of them
+            // that move into the chunk)
             ST *e = ex[buf][0];
             buf ^= 1;
-            constexpr int dir[10] = {3, 4, 7, 8, 9, 10, 15, 16, 17, 18};
+            constexpr int dir[10] = {3, 4, 7, 8, 9, 10, 15, 18, 16, 17};
+            constexpr int from = BELOW ? 6 : (ABOVE ? 8 : 0), to = BELOW ? 8 : 10;
 #pragma unroll
-            for (int d = 0; d < 10; ++d) e[d * nth + t] = A[dir[d]];
+            for (int d = from; d < to; ++d) e[d * nth + t] = A[dir[d]];
             A[1] = shx(A[1], true);
             A[2] = shx(A[2], false);
             A[11] = shx(A[11], true);
@@ -261,10 +271,10 @@ __global__ __launch_bounds__(64 * WAVES, sizeof(ST) == 4 ? 3 : 2) void k_stream3
             __syncthreads();
             if (outv) {
 #pragma unroll
-                for (int d = 0; d < 10; ++d)
+                for (int d = from; d < to; ++d)
                     A[dir[d]] = e[d * nth + t - D3Q19::ey(dir[d]) * W - D3Q19::ex(dir[d])];
             }
-            if (z > z0 && active) {
+            if (!BELOW && z > z0 && active) {
                 double rn = r5;
                 rn += (double)A[6];
                 rn += (double)v7;
@@ -292,33 +302,40 @@ __global__ __launch_bounds__(64 * WAVES, sizeof(ST) == 4 ? 3 : 2) void k_stream3
                 put(gn.j_f + ns + zd, oc, jy);
                 put(gn.j_f + 2 * ns + zd, oc, jz);
             }
-            r5 = rest;
-            r5 += (double)A[1];
-            r5 += (double)A[2];
-            r5 += (double)A[3];
-            r5 += (double)A[4];
-            r5 += (double)u5;
-            jx = ((Jx + (double)A[1]) - (double)A[2]) + (double)A[7];
-            jx = ((jx - (double)A[8]) + (double)A[9]) - (double)A[10];
-            jx += (double)u11;
-            jy = ((Jy + (double)A[3]) - (double)A[4]) + (double)A[7];
-            jy = ((jy - (double)A[8]) - (double)A[9]) + (double)A[10];
-            jy += (double)u15;
-            jz = Jz + (double)u5;
-            v7 = A[7];
-            v8 = A[8];
-            v9 = A[9];
-            v10 = A[10];
-            v11 = u11;
-            v14 = u14;
-            v15 = u15;
-            v18 = u18;
-            u5 = A[5];
-            u11 = A[11];
-            u14 = A[14];
-            u15 = A[15];
-            u18 = A[18];
-        }
+            if constexpr (!BELOW && !ABOVE) {
+                r5 = rest;
+                r5 += (double)A[1];
+                r5 += (double)A[2];
+                r5 += (double)A[3];
+                r5 += (double)A[4];
+                r5 += (double)u5;
+                jx = ((Jx + (double)A[1]) - (double)A[2]) + (double)A[7];
+                jx = ((jx - (double)A[8]) + (double)A[9]) - (double)A[10];
+                jx += (double)u11;
+                jy = ((Jy + (double)A[3]) - (double)A[4]) + (double)A[7];
+                jy = ((jy - (double)A[8]) - (double)A[9]) + (double)A[10];
+                jy += (double)u15;
+                jz = Jz + (double)u5;
+                v7 = A[7];
+                v8 = A[8];
+                v9 = A[9];
+                v10 = A[10];
+                v11 = u11;
+                v14 = u14;
+                v15 = u15;
+                v18 = u18;
+            }
+            if constexpr (!ABOVE) {
+                u5 = A[5];
+                u11 = A[11];
+                u14 = A[14];
+                u15 = A[15];
+                u18 = A[18];
+            }
+        };
+        step(z0 - 1, std::true_type{}, std::false_type{});
+        for (int z = z0; z < z0 + nzc; ++z) step(z, std::false_type{}, std::false_type{});
+        step(z0 + nzc, std::false_type{}, std::true_type{});
     }
 }
 

@@ -537,14 +537,15 @@ fuglbm_status run_field(const FieldRun &q, int ncomp, bool fp32, int64_t n, hipG
 
 // ---- D3Q19 in field form --------------------------------------------------
 // Tiles of the stream kernel.  A workgroup collides W x R sites a plane for
-// (W - 4) x (R - 2) of output and zc + 2 planes for zc, so wide, tall and
-// long tiles waste least; but all of them should be resident at once, and a
-// SIMD works through its wavefronts one after another.  The cheapest of the
-// widths, heights and chunk lengths by
-//   cost = rounds x (zc + 2) x wavefronts per SIMD (at least 2: latency)
+// (W - 4) x (R - 2) of output, and its two rim planes cost 0.9 of a plane,
+// so wide, tall and long tiles waste least; but all of them should be
+// resident at once, and a SIMD works through its wavefronts one after
+// another.  The cheapest of the widths, heights and chunk lengths by
+//   cost = rounds x (zc + 0.9) x wavefronts per SIMD (at least 2: latency)
 //          x components,
 // planes of one wavefront that a SIMD works through.  Measured steps take
-// 12 us + 1.45 us x cost (N >= 5, 40^3 ... 128^3, both precisions, within 8 %).
+// 12 us + 1.35 ... 1.8 us x cost (N = 9 and 10, 36^3 ... 128^3, both
+// precisions).
 struct Shape3 {
     int W, waves, zc;
     double cost;
@@ -561,7 +562,7 @@ Shape3 field3_shape(const fuglbm_sim *s) {
                 const double rounds = (double)((items + slots - 1) / slots);
                 const int resident = (int)std::min<int64_t>(12 / waves, (items + cus - 1) / cus);
                 const double per_simd = std::max(2.0, waves * resident / 4.0);
-                const double cost = rounds * (zc + 2) * per_simd * s->N;
+                const double cost = rounds * (zc + 0.9) * per_simd * s->N;
                 if (cost < best.cost) best = {W, waves, zc, cost};
             }
         }
@@ -571,14 +572,20 @@ Shape3 field3_shape(const fuglbm_sim *s) {
 // The field form moves a third of the bytes but collides the rims of its
 // tiles twice, and a chip of one or two short tiles per CU does little else.
 // The multi-pass step takes about 75 ps per site and component in FP64 and
-// 54 ps in FP32 storage (64^3, N = 10: 197 and 142 us), 100 and 70 ps where
-// rows are not whole 64-byte lines, so that it writes parts of them, and the
-// field step takes 1.45 us per unit of cost: it pays from ns N / cost =
-// 1.45 us / 75 ps = 19 300 (FP32: 26 900; parts of lines: 14 500, 20 700) on.
+// 57 ps in FP32 storage, 115 and 72 ps where rows are not whole 64-byte
+// lines, so that it writes parts of them; the field step goes by its cost.
+// Measured either side of each line, ns N / cost and multi-pass / field us a
+// step, N = 10:
+//   FP64          48^3 (19 400) 102 / 108     64^3 (26 700) 198 / 160
+//     part lines  36^3 (12 300) 71 / 73       90 50 50 (23 000) 252 / 160
+//   FP32          64^3 (26 700) 146 / 150     128^3 (41 400) 1211 / 914
+//     part lines  50 120 24 (24 800) 103.5 / 104.1   90 50 50 (25 900) 170 / 135
+// A run of three steps gains what its first and last cost (64^3 FP64: 206
+// multi-pass, 184).
 bool field3_pays(const fuglbm_sim *s, int64_t n) {
-    if (n < 2 || !field3_usable(s)) return false;
+    if (n < 3 || !field3_usable(s)) return false;
     const bool lines = s->nx % (s->fp32 ? 16 : 8) == 0;
-    const double from = s->fp32 ? (lines ? 26900.0 : 20700.0) : (lines ? 19300.0 : 14500.0);
+    const double from = s->fp32 ? (lines ? 28000.0 : 25000.0) : (lines ? 22000.0 : 15000.0);
     return (double)s->ns * s->N >= from * field3_shape(s).cost;
 }
 
