@@ -487,6 +487,180 @@ __global__ __launch_bounds__(64 * (NC + HELPERS)) void k_field_step(
     }
 }
 
+// The same for few components by single wavefronts: lanes and rows of a work
+// item as above, every component in one wavefront, which collides row r - 1
+// as soon as row r is there.  No exchange between wavefronts and none that
+// only helps (two of the five that three components take above); two to four
+// of them to a SIMD, bound by memory where the grid fills them (1024^2 x 3:
+// 160 MB with its halos in 30 us).  Rows are held without their lane shifts,
+// which are taken where they are used: 220 registers instead of 276 for three
+// components in FP64.  Which of the two is faster depends on how the rows
+// divide, so the tuner times both.  Step kernel above / this, us a step with
+// the EOS kernel: 48 grids of 64^2 ... 256^2 x 3 in FP32 storage 84 / 76,
+// 512^2 x 1 16.1 / 14.5, 1024^2 x 3 52 / 50.6, 512^2 x 3 22.9 / 23.5,
+// 1024^2 x 2 38.5 / 42; with four components 56 / 78.  Taken back: the EOS
+// in the same wavefront (no psi_i in memory, one launch): 48 grids 77,
+// 1024^2 x 3 slower than both.
+template <int NC, typename ST>
+__global__ __launch_bounds__(64, NC == 1 ? 4 : NC == 2 ? 3 : 2) void k_field_single(const FieldSim *tab, FieldSim one,
+                                                   const FusedItem *items, int nitems, int strips,
+                                                   int rows_, int flip, int set) {
+    FusedItem it;
+    FieldSim f;
+    if (items) {
+        cptr<FusedItem> p = (cptr<FusedItem>)items + blockIdx.x;
+        it = {p->sim, p->x0, p->y0, p->rows};
+        if (it.sim < 0) return;
+        f = load_sim(tab, it.sim);
+    } else {
+        f = one;
+        const int per = gridDim.x / 8;
+        const int li = (blockIdx.x % 8) * per + blockIdx.x / 8;
+        if (li >= nitems) return;
+        it.x0 = (li % strips) * FUSED_OUT;
+        it.y0 = (li / strips) * rows_;
+        it.rows = min(rows_, f.ny - it.y0);
+    }
+    cptr<SimConst> C = (cptr<SimConst>)f.c;
+    const int nx = f.nx, ny = f.ny;
+    const View v = field_view(f, flip, NC, 2);
+    const int lane = threadIdx.x;
+    int xc = (it.x0 - 2 + lane) % nx;
+    if (xc < 0) xc += nx;
+    const bool outl = lane >= 2 && lane < 62 && (it.x0 + lane - 2) < nx;
+    const int y0 = it.y0, rbeg = y0 - 2, rend = y0 + it.rows + 1;
+    auto wrap = [&](int q) {
+        q %= ny;
+        return q < 0 ? q + ny : q;
+    };
+    auto next = [&](int w) { return w + 1 == ny ? 0 : w + 1; };
+    const uint32_t xb = (uint32_t)xc * 8u;
+    auto at = [&](gptr<double> row) { return *(gptr<double>)((gptr<char>)row + xb); };
+    auto put = [&](double *row, double q) { *(gmptr<double>)((gmptr<char>)row + xb) = q; };
+    gptr<double> rho = (gptr<double>)(set ? v.rho[1] : v.rho[0]), psi = (gptr<double>)v.psi;
+    gptr<double> jx = (gptr<double>)(set ? v.j[1] : v.j[0]), ir = (gptr<double>)v.ir;
+    double *rhod = set ? v.rho[0] : v.rho[1];
+    double *jd = set ? v.j[0] : v.j[1];
+    double *sd = set ? v.s[0] : v.s[1];
+
+    // row r of rho_i and psi_i, row r - 1 of j and 1/rho
+    struct In {
+        double h[NC], p[NC], jx, jy, ir;
+    } X, Y, Z;
+    int lr = rbeg, lw = wrap(rbeg), lv = wrap(rbeg - 1);
+    auto load = [&](In &q) {
+        // in program order, so every wait on a row counts the rows after it
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        const int64_t o = (int64_t)lw * nx, m = (int64_t)lv * nx;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            q.h[i] = at(rho + (int64_t)i * v.ld + o);
+            q.p[i] = at(psi + (int64_t)i * v.ld + o);
+        }
+        q.jx = at(jx + m);
+        q.jy = at(jx + v.ld + m);
+        q.ir = at(ir + m);
+        if (lr < rend) {                // past the item's last row: that row again
+            ++lr;
+            lv = lw;
+            lw = next(lw);
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load(X);
+    load(Y);
+    load(Z);
+
+    auto shl = [](ST q, bool left) -> ST {   // value of the west / east lane
+        if constexpr (sizeof(ST) == 4) {
+            const int b = __float_as_int(q);
+            return __int_as_float(left ? __builtin_amdgcn_mov_dpp(b, 0x138, 0xf, 0xf, true)
+                                       : __builtin_amdgcn_mov_dpp(b, 0x130, 0xf, 0xf, true));
+        } else {
+            return left ? from_left(q) : from_right(q);
+        }
+    };
+    struct Rows {
+        double h[NC], p[NC];
+    } R0 = {}, R1 = {}, R2 = {};
+    // sums on their way, as above
+    double part[NC] = {}, d13[NC] = {};
+    ST n2[NC] = {}, n5[NC] = {}, n6[NC] = {}, m2[NC] = {}, m5[NC] = {}, m6[NC] = {};
+    int64_t o = (int64_t)y0 * nx;
+
+    auto lead = [&](int r, In &cur, const Rows &S, const Rows &M, Rows &T) {
+        double jxr = cur.jx, jyr = cur.jy, irr = cur.ir;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            T.h[i] = cur.h[i];
+            T.p[i] = cur.p[i];
+        }
+        load(cur);
+        if (r < rbeg + 2) return;
+        double Fx[NC], Fy[NC], Gx[NC], Gy[NC], sx = 0.0, sy = 0.0;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            double gx, gy;
+            grad3(S.p[i], M.p[i], T.p[i], gx, gy);
+            grad3(S.h[i], M.h[i], T.h[i], Gx[i], Gy[i]);
+            const double rty = M.h[i] * C->invM[i];
+            Fx[i] = -rty * gx;
+            Fy[i] = -rty * gy;
+            sx += Fx[i];
+            sy += Fy[i];
+        }
+        const double ux = fma(0.5, sx, jxr) * irr, uy = fma(0.5, sy, jyr) * irr;
+        double rn[NC], jxt = 0.0, jyt = 0.0, sv = 0.0;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const double h = M.h[i];
+            ST t[8];
+            double rest;
+            if constexpr (sizeof(ST) == 4) {
+                rest = h - collide_moving_f32<false>(h, 0.5, 0.0, ux, uy, Fx[i], Fy[i], Gx[i],
+                                                     Gy[i], t, t);
+            } else {
+                collide_d2q9(h, 0.5, ux, uy, Fx[i], Fy[i], Gx[i], Gy[i], t, rest);
+            }
+            const ST v1 = shl(t[0], true), v3 = shl(t[2], false), v7 = shl(t[6], false),
+                     v8 = shl(t[7], true);
+            const double d4 = (double)t[3], d5 = (double)n5[i], d6 = (double)n6[i],
+                         d7 = (double)v7, d8 = (double)v8;
+            rn[i] = (((part[i] + d4) + d5) + d6) + d7 + d8;
+            const double e57 = d5 - d7;
+            jxt += (d13[i] + e57) + (d8 - d6);
+            jyt += (((double)n2[i] - d4) + e57) + (d6 - d8);
+            sv = fma(C->sqk[i], rn[i] * C->invM[i], sv);
+            part[i] = ((rest + (double)v1) + (double)m2[i]) + (double)v3;
+            d13[i] = (double)v1 - (double)v3;
+            n2[i] = m2[i];
+            n5[i] = m5[i];
+            n6[i] = m6[i];
+            m2[i] = t[1];
+            m5[i] = shl(t[4], true);
+            m6[i] = shl(t[5], false);
+        }
+        if (r < y0 + 2) return;
+        if (outl) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) put(rhod + (int64_t)i * v.ld + o, rn[i]);
+            put(sd + o, sv);
+            put(jd + o, jxt);
+            put(jd + v.ld + o, jyt);
+        }
+        o += nx;
+    };
+    for (int r = rbeg; r <= rend; r += 3) {
+        lead(r, X, R0, R1, R2);
+        if (r + 1 > rend) break;
+        lead(r + 1, Y, R1, R2, R0);
+        if (r + 2 > rend) break;
+        lead(r + 2, Z, R2, R0, R1);
+    }
+}
+
 template <int NC>
 hipError_t eos_nc(const FieldRun &q, int set, hipStream_t st) {
     hipLaunchKernelGGL((k_field_eos<NC>), dim3((unsigned)q.blocks), dim3(TPB), 0, st, q.tab, q.nm,
@@ -502,18 +676,35 @@ hipError_t step_nc(const FieldRun &q, int set, hipStream_t st) {
     return hipGetLastError();
 }
 
+// Components up to which a step may be taken by single wavefronts.
+constexpr int SINGLE_COMP = 3;
+
+template <int NC, typename ST>
+hipError_t single_nc(const FieldRun &q, int set, hipStream_t st) {
+    const int grid = q.items ? q.nitems : (q.nitems + 7) / 8 * 8;
+    hipLaunchKernelGGL((k_field_single<NC, ST>), dim3(grid), dim3(64), 0, st, q.tab, q.one,
+                       q.items, q.nitems, q.strips, q.rows, q.flip, set);
+    return hipGetLastError();
+}
+
 template <int NC>
 hipError_t step_sel(const FieldRun &q, bool fp32, bool last, int set, hipStream_t st) {
+    if constexpr (NC <= SINGLE_COMP)
+        if (q.single && !last)
+            return fp32 ? single_nc<NC, float>(q, set, st) : single_nc<NC, double>(q, set, st);
     if (fp32)
         return last ? step_nc<NC, float, true>(q, set, st) : step_nc<NC, float, false>(q, set, st);
     return last ? step_nc<NC, double, true>(q, set, st) : step_nc<NC, double, false>(q, set, st);
 }
 
 template <int NC>
-int occ_nc() {
+int occ_nc(bool single) {
+    const void *k = (const void *)k_field_step<NC, double, false>;
+    if constexpr (NC <= SINGLE_COMP)
+        if (single) k = (const void *)k_field_single<NC, double>;
     int nb = 0;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &nb, (const void *)k_field_step<NC, double, false>, 64 * (NC + HELPERS), 0);
+        &nb, k, single ? 64 : 64 * (NC + HELPERS), 0);
     return e == hipSuccess && nb > 0 ? nb : 1;
 }
 
@@ -560,8 +751,10 @@ hipError_t launch_field_step2d(const FieldRun &q, int ncomp, bool fp32, bool las
     return hipErrorInvalidValue;
 }
 
-int field_blocks_per_cu2d(int ncomp) {
-#define OCC(n) fields::occ_nc<n>()
+int field_single_comp() { return fields::SINGLE_COMP; }
+
+int field_blocks_per_cu2d(int ncomp, bool single) {
+#define OCC(n) fields::occ_nc<n>(single)
     FIELD_BY_N(OCC)
 #undef OCC
     return 1;

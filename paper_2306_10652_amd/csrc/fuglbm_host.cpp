@@ -209,6 +209,7 @@ struct GraphCache {
 // and the field form's read of the populations took (ms).
 struct Tuned {
     int kernel = 0, rows = 0, frows = 0;
+    bool single = false;
     float fused_ms = 0.f, field_ms = 0.f, moments_ms = 0.f;
 };
 
@@ -333,13 +334,14 @@ static FieldSim field_sim(const fuglbm_sim *s) {
     return f;
 }
 
-static FieldRun field_run(const fuglbm_sim *s, int rows) {
+static FieldRun field_run(const fuglbm_sim *s, int rows, bool single) {
     FieldRun q{};
     q.one = field_sim(s);
     q.strips = (s->nx + FUSED_OUT - 1) / FUSED_OUT;
     q.rows = rows;
     q.nitems = q.strips * ((s->ny + rows - 1) / rows);
     q.blocks = (s->ns + 255) / 256;
+    q.single = single;
     return q;
 }
 
@@ -700,21 +702,22 @@ std::map<std::tuple<int, int, int, int>, Tuned> &tune_cache() {
 }
 
 // Rows per item of the field form whose rounds over the resident workgroups
-// cost least (a workgroup takes rows + 6 lead rows), with the items of each
+// cost least (a workgroup takes rows + 6 lead rows, a single wavefront
+// rows + 4), with the items of each
 // simulation counted as they are cut: 1024^2, N = 10 on 256 slots takes 74
 // rows (252 items in one round, us a step), where strip rows in total would
 // give 72 (270 items, two rounds).
-int field_model_rows(const std::vector<const fuglbm_sim *> &sims) {
+int field_model_rows(const std::vector<const fuglbm_sim *> &sims, bool single) {
     int ny = 1;
     for (auto *s : sims) ny = std::max(ny, s->ny);
-    const int64_t slots = (int64_t)compute_units() * field_blocks_per_cu2d(sims[0]->N);
+    const int64_t slots = (int64_t)compute_units() * field_blocks_per_cu2d(sims[0]->N, single);
     int best = 1;
     int64_t best_cost = INT64_MAX;
     for (int rows = 1; rows <= ny; ++rows) {
         int64_t items = 0;
         for (auto *s : sims)
             items += (int64_t)((s->nx + FUSED_OUT - 1) / FUSED_OUT) * ((s->ny + rows - 1) / rows);
-        const int64_t cost = (items + slots - 1) / slots * (rows + 6);
+        const int64_t cost = (items + slots - 1) / slots * (rows + (single ? 4 : 6));
         if (cost < best_cost) {
             best_cost = cost;
             best = rows;
@@ -723,13 +726,19 @@ int field_model_rows(const std::vector<const fuglbm_sim *> &sims) {
     return best;
 }
 
-// Times the field form over `set_rows(rows)` (which gives the run to
-// launch): its moments and EOS kernels once, its step kernel at each rows
+// Times the field form of simulations of up to ny rows over `set_rows(rows)`
+// (which gives the run to launch): its moments and EOS kernels once, its step
+// kernel and, for few components, the one by single wavefronts at each rows
 // candidate; two passes, ranked by the sum.  The trials read the current
 // populations and write the spare buffer and workspace only.
 template <class SetRows>
-fuglbm_status time_field(const std::vector<int> &cand, int ncomp, bool fp32, hipStream_t st,
+fuglbm_status time_field(const std::vector<const fuglbm_sim *> &sims, hipStream_t st,
                          SetRows set_rows, Tuned &t) {
+    const int ncomp = sims[0]->N;
+    const bool fp32 = sims[0]->fp32;
+    int ny = 1;
+    for (auto *s : sims) ny = std::max(ny, s->ny);
+    const std::vector<int> cand = tune_candidates(ny, field_model_rows(sims, false));
     FieldRun q;
     fuglbm_status rc = set_rows(cand[0], q);
     if (rc != FUGLBM_OK) return rc;
@@ -760,6 +769,25 @@ fuglbm_status time_field(const std::vector<int> &cand, int ncomp, bool fp32, hip
     if (rc != FUGLBM_OK) return rc;
     t.frows = best;
     t.field_ms = eos_ms + best_ms / (2 * TUNE_LAUNCHES);
+    if (ncomp <= field_single_comp()) {
+        rc = time_candidates(
+            tune_candidates(ny, field_model_rows(sims, true)), st,
+            [&](int r) {
+                fuglbm_status e = set_rows(r, q);
+                q.single = true;
+                return e;
+            },
+            [&] { return launch_field_step2d(q, ncomp, fp32, false, 0, st); }, best, &best_ms);
+        if (rc != FUGLBM_OK) return rc;
+        const float ms = eos_ms + best_ms / (2 * TUNE_LAUNCHES);
+        // clearly faster alone: at 512^2 x 3 the trials call the two equal and
+        // a run does not (22.9 / 23.5 us a step)
+        if (ms < 0.95f * t.field_ms) {
+            t.frows = best;
+            t.field_ms = ms;
+            t.single = true;
+        }
+    }
     return FUGLBM_OK;
 }
 
@@ -857,9 +885,9 @@ fuglbm_status autotune_rows(fuglbm_sim *s, hipStream_t st) {
         tn.fused_ms = best_ms / (2 * TUNE_LAUNCHES);
         if (field_usable(s)) {
             fuglbm_status rc = time_field(
-                tune_candidates(s->ny, field_model_rows({s})), s->N, s->fp32, st,
+                {s}, st,
                 [&](int r, FieldRun &q) {
-                    q = field_run(s, r);
+                    q = field_run(s, r, false);
                     return FUGLBM_OK;
                 },
                 tn);
@@ -1431,7 +1459,7 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *s, int64_t nsteps, void *hip_stream) {
         if (rc != FUGLBM_OK) return rc;
     }
     if (s->tuned && field_usable(s) && field_pays(s->tune, left)) {
-        fuglbm_status rc = run_field(field_run(s, s->tune.frows), s->N, s->fp32, left,
+        fuglbm_status rc = run_field(field_run(s, s->tune.frows, s->tune.single), s->N, s->fp32, left,
                                      s->fgraph[s->parity], st);
         if (rc != FUGLBM_OK) return rc;
         s->step += left;
@@ -1837,6 +1865,7 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
         fuglbm_status rc = build_batch(bt, group, st, hit->second.rows, hit->second.kernel);
         if (rc == FUGLBM_OK && hit->second.frows)
             rc = build_field_batch(bt, group, hit->second.frows, st);
+        bt.frun.single = hit->second.single;
         if (rc == FUGLBM_OK) bt.tune = hit->second;
         return rc;
     }
@@ -1862,7 +1891,7 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
     fuglbm_status rc = FUGLBM_OK;
     if (field) {
         rc = time_field(
-            tune_candidates(ny_max, field_model_rows({group.begin(), group.end()})), nc, f32, st,
+            {group.begin(), group.end()}, st,
             [&](int r, FieldRun &q) {
                 fuglbm_status e = build_field_batch(bt, group, r, st);
                 q = bt.frun;
@@ -1870,6 +1899,7 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
             },
             tn);
         if (rc == FUGLBM_OK) rc = build_field_batch(bt, group, tn.frows, st);
+        bt.frun.single = tn.single;
     }
     if (rc == FUGLBM_OK) rc = build_batch(bt, group, st, tn.rows, tn.kernel);
     if (rc != FUGLBM_OK) return rc;

@@ -131,9 +131,11 @@ struct FieldRun {
     int nitems, strips, rows;
     int64_t blocks;
     int flip;
+    bool single;          // steps (but the last) by single wavefronts
 };
 int field_max_comp();   // built for ncomp <= this
-int field_blocks_per_cu2d(int ncomp);
+int field_single_comp();  // `single` for ncomp <= this
+int field_blocks_per_cu2d(int ncomp, bool single);
 // populations -> set 0
 hipError_t launch_field_moments2d(const FieldRun &q, bool fp32, hipStream_t st);
 // psi and 1/rho of set `set`

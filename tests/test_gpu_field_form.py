@@ -47,7 +47,7 @@ def field(N, shape, seed):
 
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("N,shape,seed", [
-    (1, (1021, 1019), 9), (2, (541, 600), 11), (3, (479, 361), 31), (4, (659, 240), 11),
+    (1, (1021, 1019), 9), (1, (512, 511), 9), (2, (541, 600), 11), (3, (479, 361), 31), (4, (659, 240), 11),
     (6, (361, 181), 4), (9, (239, 211), 4), (10, (181, 300), 4), (10, (420, 97), 5)])
 def test_field_form_matches_fused_bitwise(N, shape, seed, precision):
     capi = _capi()
@@ -61,6 +61,24 @@ def test_field_form_matches_fused_bitwise(N, shape, seed, precision):
         assert b.diagnostics()["status"] == 0
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_field_form_large_batch_matches_alone_bitwise(precision):
+    """Enough rows for the step by single wavefronts to be the faster one."""
+    capi = _capi()
+    wls = [W.random_droplet(3, s, seed=31) for s in ((301, 240), (256, 256), (61, 400), (119, 121),
+                                                     (180, 7))] * 4
+    ref = [make(capi, wl, precision, 3, 5) for wl in wls[:5]]
+    got = [make(capi, wl, precision) for wl in wls]
+    for n in (12, 70):
+        for s in ref:
+            s.step_n(n)
+        capi.step_many(got, n)
+        for k, b in enumerate(got):
+            assert np.array_equal(ref[k % 5].read_populations(), b.read_populations()), (n, k)
+    for s in ref + got:
+        s.close()
 
 
 @pytest.mark.parametrize("precision", [0, 1])
