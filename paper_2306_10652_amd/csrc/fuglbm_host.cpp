@@ -953,6 +953,10 @@ struct Lanes {
 // another thread copies without it.
 constexpr size_t STAGE_SMALL = 4096, STAGE_SLOT = (size_t)4 << 20;
 constexpr int STAGE_SLOTS = 8, STAGE_THREADS = 6;
+// Parts up to this size are written to slot 0 by a kernel: rho of 256^2 x 3
+// (1.6 MB) takes 106 us so and 115 us through the ring, of 200^2 x 10 (3.2 MB)
+// the ring.
+constexpr size_t STAGE_SMALL_PART = STAGE_SLOT / 2;
 
 struct Stage {
     std::mutex use;             // held by the call that copies through it
@@ -1130,26 +1134,25 @@ fuglbm_status read_parts(fuglbm_sim *s, std::initializer_list<Part> parts) {
         s->sticky |= word;
         return FUGLBM_OK;
     }
-    HIP_TRY(hipMemcpyAsync(g.mem, s->status, sizeof(word), hipMemcpyDeviceToHost, st));
-    // small parts share slot 0 and the final wait; the others go through the
-    // ring first
-    size_t used = 0;
-    auto small = [&](const Part &p) { return p.bytes <= STAGE_SLOT / 4; };
+    // the large parts through the ring, the small ones (up to two, which then
+    // fit slot 0) and the status word by one kernel and one wait
+    // (callers pass at most two)
+    Part few[2] = {}, large[2] = {};
+    int n = 0, nl = 0;
     for (const Part &p : parts)
-        if (p.host && !small(p))
-            HIP_TRY(staged_copy(g, (char *)p.host, (char *)p.dev, p.bytes, true, st));
-    for (const Part &p : parts)
-        if (p.host && small(p)) {
-            HIP_TRY(hipMemcpyAsync(g.slot(0) + used, p.dev, p.bytes, hipMemcpyDeviceToHost, st));
-            used += p.bytes;
-        }
+        if (p.host) (p.bytes <= STAGE_SMALL_PART ? few[n++] : large[nl++]) = p;
+    if (n == 0 && nl > 0)
+        HIP_TRY(hipMemcpyAsync(g.mem, s->status, sizeof(word), hipMemcpyDeviceToHost, st));
+    for (int k = 0; k < nl; ++k)
+        HIP_TRY(staged_copy(g, (char *)large[k].host, (char *)large[k].dev, large[k].bytes, true,
+                            st));
+    if (n > 0 || nl == 0)
+        HIP_TRY(launch_to_host((const double *)few[0].dev, (int64_t)(few[0].bytes / 8),
+                               (const double *)few[1].dev, (int64_t)(few[1].bytes / 8), s->status,
+                               (double *)g.slot(0), (uint32_t *)g.mem, st));
     HIP_TRY(hipStreamSynchronize(st));
-    used = 0;
-    for (const Part &p : parts)
-        if (p.host && small(p)) {
-            std::memcpy(p.host, g.slot(0) + used, p.bytes);
-            used += p.bytes;
-        }
+    for (int k = 0; k < n; ++k)
+        std::memcpy(few[k].host, g.slot(0) + (k ? few[0].bytes : 0), few[k].bytes);
     std::memcpy(&word, g.mem, sizeof(word));
     s->sticky |= word;
     return FUGLBM_OK;

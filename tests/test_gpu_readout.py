@@ -44,6 +44,27 @@ def test_populations_round_trip(N, shape, lattice, precision):
     s.close()
 
 
+@pytest.mark.parametrize("N,shape", [(1, (7, 5)), (2, (301, 300)), (3, (400, 320)),
+                                     (3, (400, 340)), (4, (701, 640))])
+def test_moments_by_part_size(N, shape):
+    """rho and u that a kernel writes out (parts up to 2 MiB), that go through
+    the ring, and one of each: densities equal to the sums of the
+    populations, and the momentum of rho and u as the device sums it."""
+    capi = _capi()
+    s = sim_of(capi, N, shape, 0, 0)
+    s.step_n(2)
+    out = s.read_moments()
+    g = s.read_populations()
+    rho, u = out["rho"].reshape(N, -1), out["u"].reshape(2, -1)
+    assert np.max(np.abs(rho / g.sum(axis=1) - 1)) <= 1e-14
+    d = s.diagnostics()
+    p = (rho.sum(axis=0) * u).sum(axis=1)
+    scale = (rho.sum(axis=0) * np.abs(u)).sum()
+    assert np.max(np.abs(p - d["momentum"][:2])) <= 1e-12 * scale
+    assert out["status"] == 0
+    s.close()
+
+
 def test_reads_from_several_threads():
     capi = _capi()
     sims = [sim_of(capi, 3, (400, 300 + k), 0, 0) for k in range(4)]
