@@ -962,6 +962,7 @@ struct Stage {
     std::mutex use;             // held by the call that copies through it
     char *mem = nullptr;        // STAGE_SMALL + STAGE_SLOTS * STAGE_SLOT, pinned
     hipEvent_t ev[STAGE_SLOTS] = {};
+    bool asked = false;         // a small read-out has done without `mem`
     std::mutex life;
     int sims = 0;               // live simulations
     Lanes lanes;
@@ -995,6 +996,7 @@ struct Stage {
         std::lock_guard<std::mutex> u(use);
         if (mem) (void)hipHostFree(mem);
         mem = nullptr;
+        asked = false;
         for (hipEvent_t &e : ev) {
             if (e) (void)hipEventDestroy(e);
             e = nullptr;
@@ -1126,7 +1128,16 @@ fuglbm_status read_parts(fuglbm_sim *s, std::initializer_list<Part> parts) {
     Stage &g = *s->stage;
     std::unique_lock<std::mutex> lk(g.use, std::try_to_lock);
     uint32_t word = 0;
-    if (!lk.owns_lock() || !g.ready()) {
+    // (callers pass at most two parts)
+    Part few[2] = {}, large[2] = {};
+    int n = 0, nl = 0;
+    for (const Part &p : parts)
+        if (p.host) (p.bytes <= STAGE_SMALL_PART ? few[n++] : large[nl++]) = p;
+    // making and giving back the staging costs more (60 us) than it spares
+    // the only small read-out of a simulation on its own: plain copies first
+    bool plain = !lk.owns_lock();
+    if (!plain && !g.mem && nl == 0 && !g.asked) plain = g.asked = true;
+    if (plain || !g.ready()) {
         HIP_TRY(hipStreamSynchronize(st));
         for (const Part &p : parts)
             if (p.host) HIP_TRY(hipMemcpy(p.host, p.dev, p.bytes, hipMemcpyDeviceToHost));
@@ -1136,11 +1147,6 @@ fuglbm_status read_parts(fuglbm_sim *s, std::initializer_list<Part> parts) {
     }
     // the large parts through the ring, the small ones (up to two, which then
     // fit slot 0) and the status word by one kernel and one wait
-    // (callers pass at most two)
-    Part few[2] = {}, large[2] = {};
-    int n = 0, nl = 0;
-    for (const Part &p : parts)
-        if (p.host) (p.bytes <= STAGE_SMALL_PART ? few[n++] : large[nl++]) = p;
     if (n == 0 && nl > 0)
         HIP_TRY(hipMemcpyAsync(g.mem, s->status, sizeof(word), hipMemcpyDeviceToHost, st));
     for (int k = 0; k < nl; ++k)
