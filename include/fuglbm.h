@@ -240,10 +240,16 @@ fuglbm_status fuglbm_read_populations(fuglbm_sim *sim, double *g_out);
 fuglbm_status fuglbm_write_populations(fuglbm_sim *sim, const double *g_in, int64_t step);
 
 /* Launch tuning: kernel 0 = automatic, 1 = four-pass generic kernels,
- * 2 = fused one-pass D2Q9 kernel (register ring), 3 = fused one-pass D2Q9
- * kernel with store wavefronts (ncomp <= 10; bit-identical results).
+ * 2 = fused one-pass D2Q9 kernel (register ring; its form for work items of
+ * one or two rows where rows <= 2), 3 = fused one-pass D2Q9 kernel with store
+ * wavefronts (ncomp <= 10; bit-identical results).
  * Automatic: the fused kernels for D2Q9 (1 beyond 2^32 buffer elements),
- * 1 for D3Q19;
+ * 1 for D3Q19.  At tau = 1 a run of several steps (fuglbm_step_n,
+ * fuglbm_step_many) may carry densities and momentum instead of populations
+ * between its first and last step, in the population buffer that the run does
+ * not read: on D2Q9 with kernel 0 and rows 0, where the trials find it
+ * faster; on D3Q19 on grids that fill the GPU.  The state it ends in is
+ * bitwise the same;
  * rows = output rows per fused work item (>= 1, fixed), or 0 = autotuned:
  * the next fuglbm_step_n times a few trial launches per candidate (they
  * read the current state and write the spare buffer, so the state does

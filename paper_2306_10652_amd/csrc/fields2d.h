@@ -20,6 +20,10 @@
 // (FP32 storage: 100 in the same unit).  All terms come from the functions
 // the fused kernels use, and the populations enter the sums rounded to the
 // storage type and in direction order: the state is bitwise theirs.
+//
+// Measured, us a step (fused kernel before): 1024^2 x 10 332 -> 121 FP64,
+// 252 -> 123 FP32 storage; 512^2 x 10 103 -> 39; 200^2 x 10 26.9 -> 17.6;
+// 1024^2 x 3 116 -> 52.
 #pragma once
 
 #include "fused_common.h"
@@ -144,7 +148,13 @@ __global__ __launch_bounds__(TPB) void k_field_moments(const FieldSim *tab, int 
 // psi_i and 1/rho of set `set`.  One thread per site with every component in
 // registers: the N x N mixing sums, N + 2 logarithms and the reciprocals are
 // independent chains of one thread, there is no exchange between threads,
-// and s is read with its eight neighbours (cache hits).
+// and s is read with its eight neighbours (cache hits).  Bound by VALU work:
+// 1330 instructions a wavefront for ten components, 900 of them logarithms;
+// 48 us for 1024^2 x 10 (36 us of issue, 193 MB), 20.5 us x 3.  Slower: 64
+// registers for eight wavefronts a SIMD (60 us, spills), persistent
+// workgroups that load a site ahead (56 to 60 us), components split over
+// workgroups on small grids (200^2 x 10: 17.6 us a step -> 19.6 and more, as
+// every group repeats the N x N sums).
 template <int NC>
 __global__ __launch_bounds__(TPB) void k_field_eos(const FieldSim *tab, int nm, FieldSim one,
                                                    int flip, int set) {
@@ -238,7 +248,10 @@ struct StepLds<NC, true> {
 // so every exchange has a whole row's time to arrive.  The component
 // wavefronts only load and helper 1 only stores (loads and stores in flight
 // share one counter: a wavefront with both can only wait for all of them);
-// rows are requested three ahead.
+// rows are requested three ahead.  72 us for 1024^2 x 10 in 74-row items (252
+// workgroups, one per CU, 302 MB and halos at 4.6 TB/s).  Slower: F_i of the
+// next row after the barrier, beside the collision (85 -> 88 us in 96-row
+// items); rows requested six ahead (no change, three components 80 -> 96).
 template <int NC, typename ST, bool LAST>
 __global__ __launch_bounds__(64 * (NC + HELPERS)) void k_field_step(
     const FieldSim *tab, FieldSim one, const FusedItem *items, int nitems, int strips, int rows_,
