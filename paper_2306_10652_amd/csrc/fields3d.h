@@ -26,7 +26,8 @@
 // hand five populations into the chunk, once took all of that (75 64 50 FP32
 // storage 139 us, 50 120 24 FP64 129 -> 109).  Taken back: the plane loop
 // unrolled by three to spare the copies of the ring of planes (FP64 232
-// registers, FP32 55 spills).
+// registers, FP32 55 spills); three wavefronts a SIMD in FP64 (168 registers,
+// 15 spills: 128^3 956 -> 936, but 100^3 448 -> 522).
 #pragma once
 
 #include <type_traits>
@@ -116,14 +117,15 @@ __global__ __launch_bounds__(TPB) void k_eos3(GenMember g) {
     flag_status(g.status, bad);
 }
 
-// One plane of a field at a lane: own row with its west and east neighbours,
-// and the rows south and north of it.
+// One plane of a field at a lane: own row and the rows south and north of
+// it.  Its lane shifts are taken where they are used: kept, they cost 16
+// registers and 1 to 2 % of the step (128^3 x 10: 965 us FP64, 905 FP32
+// storage, against 956 and 889).
 struct Plane {
-    double s, c, n, w, e;
+    double s, c, n;
+    __device__ __forceinline__ double w() const { return from_left(c); }
+    __device__ __forceinline__ double e() const { return from_right(c); }
 };
-__device__ __forceinline__ Plane plane_of(double s, double c, double n) {
-    return {s, c, n, from_left(c), from_right(c)};
-}
 
 // Lattice gradient in pairwise-difference form, the operations of
 // lattice_grad: planes below (b), own (o), above (t).
@@ -131,9 +133,9 @@ __device__ __forceinline__ void grad19(const Plane &b, const Plane &o, const Pla
                                        double &gy, double &gz) {
 #pragma clang fp contract(off)
     constexpr double w1 = 1.0 / 18.0, w2 = 1.0 / 36.0;
-    const double d1 = o.e - o.w, d3 = o.n - o.s, d5 = t.c - b.c;
+    const double d1 = o.e() - o.w(), d3 = o.n - o.s, d5 = t.c - b.c;
     const double d7 = from_right(o.n) - from_left(o.s), d9 = from_right(o.s) - from_left(o.n);
-    const double d11 = t.e - b.w, d13 = b.e - t.w, d15 = t.n - b.s, d17 = b.n - t.s;
+    const double d11 = t.e() - b.w(), d13 = b.e() - t.w(), d15 = t.n - b.s, d17 = b.n - t.s;
     gx = fma(w2, d13, fma(w2, d11, fma(w2, d9, fma(w2, d7, w1 * d1))));
     gy = fma(w2, d17, fma(w2, d15, fma(-w2, d9, fma(w2, d7, w1 * d3))));
     gz = fma(-w2, d17, fma(w2, d15, fma(-w2, d13, fma(w2, d11, w1 * d5))));
@@ -216,9 +218,9 @@ __global__ __launch_bounds__(64 * WAVES, sizeof(ST) == 4 ? 3 : 2) void k_stream3
             return {at(r, os), at(r, oc), at(r, on), at(p, os), at(p, oc), at(p, on)};
         };
         Raw q = load(z0 - 2);
-        Plane hb = plane_of(q.hs, q.hc, q.hn), pb = plane_of(q.ps, q.pc, q.pn);
+        Plane hb{q.hs, q.hc, q.hn}, pb{q.ps, q.pc, q.pn};
         q = load(z0 - 1);
-        Plane ho = plane_of(q.hs, q.hc, q.hn), po = plane_of(q.ps, q.pc, q.pn);
+        Plane ho{q.hs, q.hc, q.hn}, po{q.ps, q.pc, q.pn};
         q = load(z0);
         // sums on their way to plane z - 1 (done but for what comes down
         // from plane z) and populations going up to plane z
@@ -229,7 +231,7 @@ __global__ __launch_bounds__(64 * WAVES, sizeof(ST) == 4 ? 3 : 2) void k_stream3
         // chunk the five populations that move into it and nothing else
         auto step = [&](int z, auto below, auto above) {
             constexpr bool BELOW = decltype(below)::value, ABOVE = decltype(above)::value;
-            const Plane ht = plane_of(q.hs, q.hc, q.hn), pt = plane_of(q.ps, q.pc, q.pn);
+            const Plane ht{q.hs, q.hc, q.hn}, pt{q.ps, q.pc, q.pn};
             const int64_t zo = plane * zwrap(z);
             const double ux = at(gc.u_f + zo, oc), uy = at(gc.u_f + ns + zo, oc),
                          uz = at(gc.u_f + 2 * ns + zo, oc);
