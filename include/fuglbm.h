@@ -248,8 +248,8 @@ fuglbm_status fuglbm_write_populations(fuglbm_sim *sim, const double *g_in, int6
  * fuglbm_step_many) may carry densities and momentum instead of populations
  * between its first and last step, in the population buffer that the run does
  * not read: on D2Q9 with kernel 0 and rows 0, where the trials find it
- * faster; on D3Q19 on grids that fill the GPU.  The state it ends in is
- * bitwise the same;
+ * faster; on D3Q19 on grids that fill the GPU and with one or two components.
+ * The state it ends in is bitwise the same;
  * rows = output rows per fused work item (>= 1, fixed), or 0 = autotuned:
  * the next fuglbm_step_n times a few trial launches per candidate (they
  * read the current state and write the spare buffer, so the state does

@@ -207,6 +207,11 @@ struct GraphCache {
 // What the autotuner chose for a shape: the fused variant and its rows per
 // item, the field-form rows (0: not built for it), and what a step of each
 // and the field form's read of the populations took (ms).
+// Tiles of the D3Q19 stream kernel (field3_shape); W 0: not chosen yet.
+struct Shape3 {
+    int W = 0, waves = 0, zc = 0;
+    double cost = 0.0;
+};
 struct Tuned {
     int kernel = 0, rows = 0, frows = 0;
     bool single = false;
@@ -251,6 +256,7 @@ struct fuglbm_sim {
     bool done_valid;
     GraphCache graph;
     Tuned tune;            // valid with `tuned`
+    Shape3 shape3;
     hipGraphExec_t fgraph[2];   // field form, by the parity it was captured at
     Stage *stage;          // pinned staging of its device
     uint64_t uid;          // never reused; batch tables key on it, not on the address
@@ -548,11 +554,8 @@ fuglbm_status run_field(const FieldRun &q, int ncomp, bool fp32, int64_t n, hipG
 // planes of one wavefront that a SIMD works through.  Measured steps take
 // 12 us + 1.35 ... 1.8 us x cost (N = 9 and 10, 36^3 ... 128^3, both
 // precisions).
-struct Shape3 {
-    int W, waves, zc;
-    double cost;
-};
-Shape3 field3_shape(const fuglbm_sim *s) {
+const Shape3 &field3_shape(fuglbm_sim *s) {
+    if (s->shape3.W) return s->shape3;
     const int most = s->fp32 ? 12 : 8, cus = compute_units();
     Shape3 best{32, most, 1, 1e300};
     for (int waves = 4; waves <= most; waves += 4)
@@ -568,7 +571,7 @@ Shape3 field3_shape(const fuglbm_sim *s) {
                 if (cost < best.cost) best = {W, waves, zc, cost};
             }
         }
-    return best;
+    return s->shape3 = best;
 }
 
 // The field form moves a third of the bytes but collides the rims of its
@@ -583,15 +586,22 @@ Shape3 field3_shape(const fuglbm_sim *s) {
 //   FP32          64^3 (26 700) 146 / 150     128^3 (41 400) 1211 / 914
 //     part lines  50 120 24 (24 800) 103.5 / 104.1   90 50 50 (25 900) 170 / 135
 // A run of three steps gains what its first and last cost (64^3 FP64: 206
-// multi-pass, 184).
-bool field3_pays(const fuglbm_sim *s, int64_t n) {
+// multi-pass, 184).  With one and two components a step is mostly launches,
+// three instead of four (9 8 7, N = 1: 18.4 / 12.3, N = 2: 21.8 / 16.9; 40^3
+// 22.7 / 16.2 and 28.7 / 22.9; 64 64 24 25.3 / 20.9 and 29.8 / 30.2), up to
+// twelve units of cost (64 64 40, N = 2, FP32: 33.5 / 35.6 at 16); with three
+// it depends on the shape (24^3 26.0 / 22.0, 64 64 24 38.3 / 39.7).
+// Members of a batch share the multi-pass launches: there the
+// small grids stay with them (alone false).
+bool field3_pays(fuglbm_sim *s, int64_t n, bool alone) {
     if (n < 3 || !field3_usable(s)) return false;
+    if (alone && s->N <= 2 && field3_shape(s).cost <= 12.0) return true;
     const bool lines = s->nx % (s->fp32 ? 16 : 8) == 0;
     const double from = s->fp32 ? (lines ? 28000.0 : 25000.0) : (lines ? 22000.0 : 15000.0);
     return (double)s->ns * s->N >= from * field3_shape(s).cost;
 }
 
-FieldRun3 field3_run(const fuglbm_sim *s) {
+FieldRun3 field3_run(fuglbm_sim *s) {
     FieldRun3 q{};
     const Shape3 h = field3_shape(s);
     const int R = 64 * h.waves / h.W;
@@ -1474,7 +1484,7 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *s, int64_t nsteps, void *hip_stream) {
         s->step += left;
         return mark_done(s, st);
     }
-    if (field3_pays(s, left)) {
+    if (field3_pays(s, left, true)) {
         fuglbm_status rc = run_field3(s, left, st);
         if (rc != FUGLBM_OK) return rc;
         return mark_done(s, st);
@@ -2248,7 +2258,7 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         auto &group = kv.second;
         // members that each pay in field form fill the chip one by one
         if (std::all_of(group.begin(), group.end(),
-                        [&](const fuglbm_sim *s) { return field3_pays(s, nsteps); })) {
+                        [&](fuglbm_sim *s) { return field3_pays(s, nsteps, group.size() == 1); })) {
             tasks.push_back({group_cost(group), [&group, nsteps](hipStream_t to) {
                                  for (auto *s : group) {
                                      fuglbm_status rc = run_field3(s, nsteps, to);

@@ -118,10 +118,12 @@ def make3(capi, wl, precision):
 
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("N,shape,seed", [
-    (1, (61, 99, 97), 5), (2, (140, 73, 60), 21), (10, (85, 85, 71), 24), (7, (125, 45, 120), 4)])
+    (2, (9, 8, 7), 21), (1, (70, 6, 5), 5), (2, (1, 5, 3), 21), (1, (5, 1, 1), 5),
+    (2, (48, 33, 17), 21), (1, (61, 99, 97), 5), (2, (140, 73, 60), 21), (10, (85, 85, 71), 24), (7, (125, 45, 120), 4)])
 def test_field_form_3d_matches_single_steps_bitwise(N, shape, seed, precision):
-    """Runs on D3Q19 grids large enough for the field form (widths, heights
-    and depths that leave ragged tiles) against the same steps taken one at
+    """Runs on D3Q19 grids that take the field form (one and two components,
+    and grids that fill the GPU; widths, heights and depths that leave ragged
+    tiles, grids smaller than a tile's rim) against the same steps taken one at
     a time, which the multi-pass kernels do.  (The one-component drop is not
     an equilibrium and leaves the EOS domain during the last run: the same
     sites do so, with the same status.)"""
