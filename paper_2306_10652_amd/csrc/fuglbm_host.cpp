@@ -956,44 +956,59 @@ struct Lanes {
 
 // ---- copies between device and caller memory ------------------------------
 // Pinned staging shared by the read-outs and checkpoints of the process: a
-// small block for totals and status words, and a ring of slots that bulk
+// block as large as the small read-outs asked for, and a ring of slots that bulk
 // copies go through while a few threads move finished slots to (from) the
 // caller's pages, whose first touch is what a plain copy spends most of its
 // time on.  Held while any simulation exists; a call that finds it in use by
 // another thread copies without it.
-constexpr size_t STAGE_SMALL = 4096, STAGE_SLOT = (size_t)4 << 20;
+constexpr size_t STAGE_SLOT = (size_t)4 << 20, STAGE_WORD = 256;
 constexpr int STAGE_SLOTS = 8, STAGE_THREADS = 6;
-// Parts up to this size are written to slot 0 by a kernel: rho of 256^2 x 3
+// Parts up to this size are written to the block by a kernel: rho of 256^2 x 3
 // (1.6 MB) takes 106 us so and 115 us through the ring, of 200^2 x 10 (3.2 MB)
 // the ring.
 constexpr size_t STAGE_SMALL_PART = STAGE_SLOT / 2;
 
 struct Stage {
     std::mutex use;             // held by the call that copies through it
-    char *mem = nullptr;        // STAGE_SMALL + STAGE_SLOTS * STAGE_SLOT, pinned
+    char *block = nullptr;      // STAGE_WORD bytes for a status word, then data; pinned
+    size_t block_bytes = 0;
+    bool asked = false;         // a small read-out has done without the block
+    char *ring = nullptr;       // STAGE_SLOTS * STAGE_SLOT, pinned
     hipEvent_t ev[STAGE_SLOTS] = {};
-    bool asked = false;         // a small read-out has done without `mem`
     std::mutex life;
     int sims = 0;               // live simulations
     Lanes lanes;
 
-    char *slot(int64_t k) const { return mem + STAGE_SMALL + (k % STAGE_SLOTS) * STAGE_SLOT; }
+    char *slot(int64_t k) const { return ring + (k % STAGE_SLOTS) * STAGE_SLOT; }
+    uint32_t *word() const { return (uint32_t *)block; }
+    char *data() const { return block + STAGE_WORD; }
+    static char *pinned(size_t bytes) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, bytes, 0) == hipSuccess) return (char *)p;
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    // with `use` held: room for `bytes` of data in the block
+    bool block_for(size_t bytes) {
+        size_t want = (size_t)64 << 10;
+        while (want < STAGE_WORD + bytes) want *= 2;
+        if (want <= block_bytes) return true;
+        if (block) (void)hipHostFree(block);
+        block = pinned(want);
+        block_bytes = block ? want : 0;
+        return block != nullptr;
+    }
     // with `use` held
     bool ready() {
-        if (mem) return true;
-        void *p = nullptr;
-        if (hipHostMalloc(&p, STAGE_SMALL + STAGE_SLOTS * STAGE_SLOT, 0) != hipSuccess) {
-            (void)hipGetLastError();
-            return false;
-        }
+        if (ring) return true;
         for (hipEvent_t &e : ev)
             if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
                 e = nullptr;
-                (void)hipHostFree(p);
+                (void)hipGetLastError();
                 return false;
             }
-        mem = (char *)p;
-        return true;
+        ring = pinned(STAGE_SLOTS * STAGE_SLOT);
+        return ring != nullptr;
     }
     void add_sim() {
         std::lock_guard<std::mutex> g(life);
@@ -1004,8 +1019,10 @@ struct Stage {
         if (--sims > 0) return;
         lanes.release();
         std::lock_guard<std::mutex> u(use);
-        if (mem) (void)hipHostFree(mem);
-        mem = nullptr;
+        if (block) (void)hipHostFree(block);
+        if (ring) (void)hipHostFree(ring);
+        block = ring = nullptr;
+        block_bytes = 0;
         asked = false;
         for (hipEvent_t &e : ev) {
             if (e) (void)hipEventDestroy(e);
@@ -1143,11 +1160,12 @@ fuglbm_status read_parts(fuglbm_sim *s, std::initializer_list<Part> parts) {
     int n = 0, nl = 0;
     for (const Part &p : parts)
         if (p.host) (p.bytes <= STAGE_SMALL_PART ? few[n++] : large[nl++]) = p;
-    // making and giving back the staging costs more (60 us) than it spares
-    // the only small read-out of a simulation on its own: plain copies first
+    // making the block and giving it back costs as much (40 to 60 us) as it
+    // spares the only small read-out of a simulation on its own: plain copies
+    // first
     bool plain = !lk.owns_lock();
-    if (!plain && !g.mem && nl == 0 && !g.asked) plain = g.asked = true;
-    if (plain || !g.ready()) {
+    if (!plain && !g.block && nl == 0 && !g.asked) plain = g.asked = true;
+    if (plain || !g.block_for(few[0].bytes + few[1].bytes) || (nl > 0 && !g.ready())) {
         HIP_TRY(hipStreamSynchronize(st));
         for (const Part &p : parts)
             if (p.host) HIP_TRY(hipMemcpy(p.host, p.dev, p.bytes, hipMemcpyDeviceToHost));
@@ -1155,21 +1173,21 @@ fuglbm_status read_parts(fuglbm_sim *s, std::initializer_list<Part> parts) {
         s->sticky |= word;
         return FUGLBM_OK;
     }
-    // the large parts through the ring, the small ones (up to two, which then
-    // fit slot 0) and the status word by one kernel and one wait
+    // the large parts through the ring, the small ones and the status word by
+    // one kernel and one wait
     if (n == 0 && nl > 0)
-        HIP_TRY(hipMemcpyAsync(g.mem, s->status, sizeof(word), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(g.word(), s->status, sizeof(word), hipMemcpyDeviceToHost, st));
     for (int k = 0; k < nl; ++k)
         HIP_TRY(staged_copy(g, (char *)large[k].host, (char *)large[k].dev, large[k].bytes, true,
                             st));
     if (n > 0 || nl == 0)
         HIP_TRY(launch_to_host((const double *)few[0].dev, (int64_t)(few[0].bytes / 8),
                                (const double *)few[1].dev, (int64_t)(few[1].bytes / 8), s->status,
-                               (double *)g.slot(0), (uint32_t *)g.mem, st));
+                               (double *)g.data(), g.word(), st));
     HIP_TRY(hipStreamSynchronize(st));
     for (int k = 0; k < n; ++k)
-        std::memcpy(few[k].host, g.slot(0) + (k ? few[0].bytes : 0), few[k].bytes);
-    std::memcpy(&word, g.mem, sizeof(word));
+        std::memcpy(few[k].host, g.data() + (k ? few[0].bytes : 0), few[k].bytes);
+    word = *g.word();
     s->sticky |= word;
     return FUGLBM_OK;
 }
