@@ -432,7 +432,8 @@ fuglbm_status build_items(fuglbm_sim *s) {
     return FUGLBM_OK;
 }
 
-void drop_graph(fuglbm_sim *s) {
+// Every graph of the simulation; its work must have ended.
+void drop_graphs(fuglbm_sim *s) {
     if (s->graph.exec) (void)hipGraphExecDestroy(s->graph.exec);
     s->graph = GraphCache{};
     for (auto &g : s->fgraph) {
@@ -480,7 +481,13 @@ fuglbm_status capture_steps(Launch launch, hipGraphExec_t &ex, const char *what)
 fuglbm_status ensure_graph(fuglbm_sim *s) {
     if (s->graph.exec && s->graph.kernel == s->kernel && s->graph.rows == s->rows)
         return FUGLBM_OK;
-    drop_graph(s);
+    // only this form's graph: one of the field form may be running, and stays
+    // valid
+    if (s->graph.exec) {
+        HIP_TRY(hipStreamSynchronize(s->last_stream));
+        (void)hipGraphExecDestroy(s->graph.exec);
+        s->graph = GraphCache{};
+    }
     fuglbm_status rc = capture_steps(
         [&](int k, hipStream_t cs) { return launch_one_step(s, k & 1, cs); }, s->graph.exec,
         "step graph");
@@ -1464,7 +1471,7 @@ fuglbm_status fuglbm_set_tuning(fuglbm_sim *s, int32_t kernel, int32_t rows) {
         fuglbm_status rc = build_items(s);
         if (rc != FUGLBM_OK) return rc;
     }
-    drop_graph(s);
+    drop_graphs(s);
     return FUGLBM_OK;
 }
 
@@ -1696,7 +1703,7 @@ void fuglbm_destroy_sim(fuglbm_sim *s) {
     if (!s) return;
     (void)hipStreamSynchronize(s->last_stream);
     forget_sim_in_batches(s);
-    drop_graph(s);
+    drop_graphs(s);
     if (s->done) (void)hipEventDestroy(s->done);
     if (s->owned) (void)hipFree(s->base);
     s->stage->drop_sim();
