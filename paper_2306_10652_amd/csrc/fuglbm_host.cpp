@@ -386,6 +386,9 @@ static GenMember field3_member(const fuglbm_sim *s, int parity, int set) {
     return g;
 }
 
+// The simulation left out of every cached batch table (its work has ended).
+static void forget_sim_in_batches(const fuglbm_sim *s);
+
 static uint64_t next_sim_uid() {
     static uint64_t n = 0;
     return ++n;
@@ -1465,6 +1468,7 @@ fuglbm_status fuglbm_set_tuning(fuglbm_sim *s, int32_t kernel, int32_t rows) {
         s->tuned = false;
     }
     HIP_TRY(hipStreamSynchronize(s->last_stream));
+    forget_sim_in_batches(s);   // their tables hold what was chosen before
     s->kernel = k;
     if (r != s->rows) {
         s->rows = r;
@@ -1697,8 +1701,6 @@ fuglbm_status fuglbm_poke_population(fuglbm_sim *s, int32_t comp, int32_t a, int
     return FUGLBM_OK;
 }
 
-void forget_sim_in_batches(const fuglbm_sim *s);
-
 void fuglbm_destroy_sim(fuglbm_sim *s) {
     if (!s) return;
     (void)hipStreamSynchronize(s->last_stream);
@@ -1716,7 +1718,7 @@ void fuglbm_destroy_sim(fuglbm_sim *s) {
 // Batched stepping: D2Q9 simulations on the fused kernel that share the
 // component count and precision run as ONE launch per step over a combined
 // work-item table; the table is rebuilt only when the set of simulations
-// (or their buffer parities) changes.
+// (or their buffer parities, or the tuning that a caller set) changes.
 // ---------------------------------------------------------------------------
 namespace {
 
@@ -2038,9 +2040,10 @@ fuglbm_status build_gen_batch(GenBatch &gb, const std::vector<fuglbm_sim *> &gro
     return FUGLBM_OK;
 }
 
-// A destroyed simulation's buffers may be handed to someone else: drop every
-// cached table (and its captured graph) that still refers to it.
-void forget_sim_in_batches(const fuglbm_sim *s) {
+// A destroyed simulation's buffers may be handed to someone else, and one whose
+// tuning is set anew takes other kernels: drop every cached table (and its
+// captured graph) that refers to it.
+static void forget_sim_in_batches(const fuglbm_sim *s) {
     for (auto &kv : gen_batches()) {
         GenBatch &gb = kv.second;
         for (size_t k = 0; k < gb.sims.size(); ++k) {

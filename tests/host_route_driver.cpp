@@ -387,9 +387,30 @@ static void graph_in_flight() {
     CHECK(captures == before + 1);
 }
 
+// A batch's plan follows set_tuning of its members.
+static void tuning_between_batches() {
+    times(1.0, 0.2, 0.1);
+    Sim a(3, 64, 64), b(3, 70, 40);
+    step_many({&a, &b}, 8);
+    CHECK(took("field last") == 1);
+    for (Sim *s : {&a, &b}) CHECK(fuglbm_set_tuning(s->s, 2, 2) == FUGLBM_OK);
+    launched.clear();
+    step_many({&a, &b}, 8);
+    CHECK(took("field last") == 0);
+    CHECK(took("fused block") == 8 && last_rows == 2);
+    for (Sim *s : {&a, &b}) CHECK(fuglbm_set_tuning(s->s, 0, 0) == FUGLBM_OK);
+    step_many({&a, &b}, 8);
+    CHECK(took("field last") == 1);
+    // one member fixed: neither is left to the trials
+    CHECK(fuglbm_set_tuning(b.s, 3, 5) == FUGLBM_OK);
+    step_many({&a, &b}, 8);
+    CHECK(took("field last") == 0);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, std::function<void()>> all = {
         {"graph_in_flight", graph_in_flight},
+        {"tuning_between_batches", tuning_between_batches},
     };
     if (argc < 2) {
         for (auto &k : all) std::printf("%s\n", k.first.c_str());
