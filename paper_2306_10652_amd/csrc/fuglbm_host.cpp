@@ -2248,6 +2248,10 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
     // what each group still needs of the host (tables, tuning) on st, and its
     // steps as a task
     std::vector<GroupTask> tasks;
+    if (nsteps == 0) {   // no table either: it would be one that is not tuned
+        groups.clear();
+        others.clear();
+    }
     for (auto &kv : groups) {
         auto &group = kv.second;
         BatchTable &bt = batch_tables()[kv.first];
@@ -2269,8 +2273,7 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         const bool f32 = kv.first.second != 0;
         if (!same) {
             bt.tune = Tuned{};
-            fuglbm_status rc = nsteps > 0 ? tune_batch(bt, group, nc, f32, st)
-                                          : build_batch(bt, group, st);
+            fuglbm_status rc = tune_batch(bt, group, nc, f32, st);
             if (rc != FUGLBM_OK) return rc;
             flip = 0;
         }

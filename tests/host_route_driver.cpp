@@ -407,10 +407,23 @@ static void tuning_between_batches() {
     CHECK(took("field last") == 0);
 }
 
+// A call of no steps launches nothing and leaves the next one as it would be
+// without it.
+static void no_steps_first() {
+    times(1.0, 0.2, 0.1);
+    Sim a(3, 64, 64), b(3, 70, 40), c(2, 9, 8, 7);
+    launched.clear();
+    step_many({&a, &b, &c}, 0);
+    CHECK(launched.empty());
+    step_many({&a, &b, &c}, 8);
+    CHECK(took("field last") == 1);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, std::function<void()>> all = {
         {"graph_in_flight", graph_in_flight},
         {"tuning_between_batches", tuning_between_batches},
+        {"no_steps_first", no_steps_first},
     };
     if (argc < 2) {
         for (auto &k : all) std::printf("%s\n", k.first.c_str());

@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 HIPCC = "/opt/rocm/bin/hipcc"
 
-SCENARIOS = ["graph_in_flight", "tuning_between_batches"]
+SCENARIOS = ["graph_in_flight", "tuning_between_batches", "no_steps_first"]
 
 
 @pytest.fixture(scope="module")
