@@ -39,11 +39,13 @@ def kernel_name(kernel, st):
     return KERNEL_NAMES[kernel] % st if kernel in KERNEL_NAMES else "multi-pass (generic)"
 
 
-def step_kernel(r, st):
-    """Kernels of a time_gpu result's steps."""
-    if "population_bytes" in r:
+def step_kernel(kernel, form, st):
+    """Kernels of the steps of a run in the form that the library reports
+    (capi.FORM_*; the ten-component field)."""
+    from paper_2306_10652_amd import capi
+    if form == capi.FORM_FIELDS:
         return "k_field_eos<10> + k_field_step<10,%s>" % st
-    return kernel_name(r["kernel"], st)
+    return kernel_name(kernel, st)
 
 
 def kernel_hash():
@@ -102,7 +104,7 @@ def time_gpu(precision, steps, warmup, n, diag_every=100, rows=0, kernel=0, stea
     alg = info["alg_bytes_per_step"]
     res = dict(csu=csu, csu_per_step=N * n * n, wall=wall, ms_per_step=wall * 1e3 / steps,
                launch_ms=launch_s * 1e3, alg_bytes=alg, achieved_gbs=alg / launch_s / 1e9, kernel=tuning["kernel"],
-               rows=tuning["rows"],
+               rows=tuning["rows"], form_code=sim.form(),
                status=d["status"], residual=d["residual"], mass=d["mass"].tolist(),
                mass_drift=float(np.max(np.abs(np.array(d["mass"], dtype=float) - mass0) / mass0)))
     if steady_steps:
@@ -130,13 +132,13 @@ def time_gpu(precision, steps, warmup, n, diag_every=100, rows=0, kernel=0, stea
     return res
 
 
-def field_form(r, steps, copy_gbs):
-    """Puts the bytes that a step moved into a time_gpu result.  Populations
-    cannot be moved faster than a device copy moves bytes: steps that would
-    need that ran in field form, which carries rho_i, j and s from step to
-    step (5 N + 9 FP64 values per site and step on D2Q9: fields2d.h) and moves
-    the populations once per run of steps."""
-    if r["achieved_gbs"] <= copy_gbs:
+def field_form(r, steps):
+    """Puts the bytes that a step moved into a time_gpu result whose runs the
+    library reports to have been in field form, which carries rho_i, j and s
+    from step to step (5 N + 9 FP64 values per site and step on D2Q9:
+    fields2d.h) and moves the populations once per run of steps."""
+    from paper_2306_10652_amd import capi
+    if r["form_code"] != capi.FORM_FIELDS:
         r["form"] = "populations every step"
         return
     sites = r["csu_per_step"] // 10
@@ -540,7 +542,7 @@ def cpu_baseline(n, budget_s=15.0, gpu_check=True):
         g = sim.read_moments(velocity=False)["rho"]
         ref = o.rho()
         parity = dict(steps=k, rho_max_rel=float(np.max(np.abs(g - ref) / ref)),
-                      kernel=kernel_name(sim.info()["kernel"], "double"))
+                      kernel=step_kernel(sim.info()["kernel"], sim.form(), "double"))
         sim.close()
         mix.close()
     set_threads(1)
@@ -773,14 +775,14 @@ def main():
                    steady_steps=args.steady_steps)
     copy_gbs = copy_rate()
     for r in (r64, r32):
-        field_form(r, args.steps, copy_gbs)
+        field_form(r, args.steps)
     # the counter summary is of the fused kernel
     traffic = None if "population_bytes" in r64 else pmc_traffic(r64["alg_bytes"])
     roof = dict(bound="hbm", achieved=round(r64["achieved_gbs"], 1), peak=HBM_PEAK_GBS,
                 unit="GB/s", frac=round(r64["achieved_gbs"] / HBM_PEAK_GBS, 4),
                 traffic=traffic, alg_bytes_per_launch=r64["alg_bytes"],
                 launch_ms=round(r64["launch_ms"], 5),
-                kernel=step_kernel(r64, "double"), form=r64["form"],
+                kernel=step_kernel(r64["kernel"], r64["form_code"], "double"), form=r64["form"],
                 rows_per_item=r64["rows"])
     if "population_bytes" in r64:
         roof["population_bytes_per_step"] = r64["population_bytes"]
@@ -805,7 +807,7 @@ def main():
                                  frac_72B=round(72 * r32["csu_per_step"] / (r32["launch_ms"] * 1e-3)
                                                 / 1e9 / HBM_PEAK_GBS, 4),
                                  frac_of_copy=round(r32["achieved_gbs"] / copy_gbs, 4),
-                                 kernel=step_kernel(r32, "float"), form=r32["form"],
+                                 kernel=step_kernel(r32["kernel"], r32["form_code"], "float"), form=r32["form"],
                                  rows_per_item=r32["rows"], steady_state=r32.get("steady")),
                status=[r64["status"], r32["status"]],
                mass_drift=[r64["mass_drift"], r32["mass_drift"]])

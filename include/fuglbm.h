@@ -264,8 +264,33 @@ fuglbm_status fuglbm_set_tuning(fuglbm_sim *sim, int32_t kernel, int32_t rows);
 
 /* Query the launch tuning in use: kernel (1 generic, 2 or 3 fused) and
  * fused rows per work item (0 for the generic kernels; with autotuning,
- * the values chosen once a step has run). */
+ * the values chosen once a step has run).  They are those of the steps that
+ * keep populations; fuglbm_get_form tells which form a run took. */
 fuglbm_status fuglbm_get_tuning(const fuglbm_sim *sim, int32_t *kernel, int32_t *rows);
+
+/* What a run of steps carries from one of its steps to the next.  The state it
+ * ends in is bitwise the same.
+ *   POPULATIONS    the populations, in memory at every step;
+ *   FIELDS         densities and momentum (tau = 1), see fuglbm_set_tuning;
+ *   FIELDS_SINGLE  the same with D2Q9 steps by single wavefronts (ncomp <= 3). */
+typedef enum {
+    FUGLBM_FORM_AUTO = 0,
+    FUGLBM_FORM_POPULATIONS = 1,
+    FUGLBM_FORM_FIELDS = 2,
+    FUGLBM_FORM_FIELDS_SINGLE = 3
+} fuglbm_form;
+
+/* Fix the form of the simulation's runs (fuglbm_step_n, fuglbm_step_many), or
+ * leave it to the library (AUTO, the default).  FIELDS and FIELDS_SINGLE take
+ * the rows per work item that fuglbm_set_tuning fixed, else those of a model
+ * (no trials).  fuglbm_set_tuning resets it: to POPULATIONS for kernel 1, 2
+ * or 3, else to AUTO.  EINVAL for a form the simulation cannot take (tau != 1,
+ * more than 10 components, D2Q9 on the generic kernels or beyond 2^32 buffer
+ * elements, D3Q19 beyond 2^29 sites in a plane). */
+fuglbm_status fuglbm_set_form(fuglbm_sim *sim, int32_t form);
+
+/* Query the form of the simulation's last run of steps (AUTO: none yet). */
+fuglbm_status fuglbm_get_form(const fuglbm_sim *sim, int32_t *form);
 
 /* Query: Q, spatial dimension, sites, bytes moved per step by the
  * algorithm (every population read and written once: 2 N (8 + (Q-1) s)

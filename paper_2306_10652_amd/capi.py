@@ -19,6 +19,7 @@ FUGLBM_MAX_COMP = 16
 D2Q9, D3Q19 = 0, 1
 FP64, FP32_STORAGE = 0, 1
 EOS_PR, EOS_SRK, EOS_VDW = 0, 1, 2
+FORM_AUTO, FORM_POPULATIONS, FORM_FIELDS, FORM_FIELDS_SINGLE = 0, 1, 2, 3
 EOS_CODES = {"PR": EOS_PR, "SRK": EOS_SRK, "vdW": EOS_VDW}
 STATUS_NAMES = {0: "OK", 1: "EINVAL", 2: "ENOMEM", 3: "EDEVICE", 4: "EUNPHYSICAL",
                 5: "ENONFINITE", 6: "ESTATE"}
@@ -29,7 +30,7 @@ EXPORTED = [
     "fuglbm_read_moments", "fuglbm_diagnostics", "fuglbm_read_populations",
     "fuglbm_write_populations", "fuglbm_set_tuning", "fuglbm_get_tuning", "fuglbm_sim_info",
     "fuglbm_poke_population", "fuglbm_destroy_sim", "fuglbm_last_error",
-    "fuglbm_step_many_noalloc",
+    "fuglbm_step_many_noalloc", "fuglbm_set_form", "fuglbm_get_form",
 ]
 
 
@@ -99,6 +100,8 @@ def lib():
         "fuglbm_write_populations": ([vp, dp, i64], i32),
         "fuglbm_set_tuning": ([vp, i32, i32], i32),
         "fuglbm_get_tuning": ([vp, ctypes.POINTER(i32), ctypes.POINTER(i32)], i32),
+        "fuglbm_set_form": ([vp, i32], i32),
+        "fuglbm_get_form": ([vp, ctypes.POINTER(i32)], i32),
         "fuglbm_sim_info": ([vp, ctypes.POINTER(i32), ctypes.POINTER(i32), ctypes.POINTER(i64),
                              ctypes.POINTER(i64), ctypes.POINTER(i32)], i32),
         "fuglbm_poke_population": ([vp, i32, i32, i64, ctypes.c_double], i32),
@@ -264,6 +267,15 @@ class Simulation:
         k, r = ctypes.c_int32(), ctypes.c_int32()
         check(lib().fuglbm_get_tuning(self.handle, ctypes.byref(k), ctypes.byref(r)))
         return dict(kernel=k.value, rows=r.value)
+
+    def set_form(self, form):
+        check(lib().fuglbm_set_form(self.handle, int(form)))
+
+    def form(self):
+        """FORM_* of the last run of steps (FORM_AUTO: none yet)."""
+        f = ctypes.c_int32()
+        check(lib().fuglbm_get_form(self.handle, ctypes.byref(f)))
+        return f.value
 
     def info(self):
         Q, D, k = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()

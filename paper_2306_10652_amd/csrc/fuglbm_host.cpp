@@ -204,17 +204,18 @@ struct GraphCache {
     int rows = 0;
 };
 
-// What the autotuner chose for a shape: the fused variant and its rows per
-// item, the field-form rows (0: not built for it), and what a step of each
-// and the field form's read of the populations took (ms).
 // Tiles of the D3Q19 stream kernel (field3_shape); W 0: not chosen yet.
 struct Shape3 {
     int W = 0, waves = 0, zc = 0;
     double cost = 0.0;
 };
+// What the autotuner chose for a shape: the fused variant and its rows per
+// item, the field-form rows (0: not built for it), and what a step of each
+// and the field form's read of the populations took (ms).  fixed: the form is
+// the caller's (fuglbm_set_form), nothing was timed.
 struct Tuned {
     int kernel = 0, rows = 0, frows = 0;
-    bool single = false;
+    bool single = false, fixed = false;
     float fused_ms = 0.f, field_ms = 0.f, moments_ms = 0.f;
 };
 
@@ -256,6 +257,9 @@ struct fuglbm_sim {
     bool done_valid;
     GraphCache graph;
     Tuned tune;            // valid with `tuned`
+    int form;              // fuglbm_form asked for
+    int form_rows;         // FIELDS, FIELDS_SINGLE on D2Q9: rows per item
+    int taken;             // fuglbm_form of the last run
     Shape3 shape3;
     hipGraphExec_t fgraph[2];   // field form, by the parity it was captured at
     Stage *stage;          // pinned staging of its device
@@ -303,18 +307,24 @@ static FusedSim fused_sim(const fuglbm_sim *s) {
     return {s->dc, {s->buf[0], s->buf[1]}, s->status, s->parity, s->nx, s->ny, 0};
 }
 
-// Steps in field form (fields2d.h): D2Q9 on the fused kernels, at
-// tau = 1, with variant and rows left to the library.
-static bool field_usable(const fuglbm_sim *s) {
-    return is_fused(s->kernel) && s->auto_kernel && s->autotune && s->hc.omega == 1.0 &&
-           s->N <= field_max_comp();
+// Steps in field form (fields2d.h): D2Q9 on the fused kernels, at tau = 1.
+static bool field_fits(const fuglbm_sim *s) {
+    return is_fused(s->kernel) && s->hc.omega == 1.0 && s->N <= field_max_comp();
 }
+
+// The same, with form, variant and rows left to the library.
+static bool field_usable(const fuglbm_sim *s) {
+    return field_fits(s) && s->form == FUGLBM_FORM_AUTO && s->auto_kernel && s->autotune;
+}
+
+// The caller asked for the field form.
+static bool form_fixed(const fuglbm_sim *s) { return s->form >= FUGLBM_FORM_FIELDS; }
 
 // Whether a run of n steps is taken in field form.  Beside its steps it
 // reads the populations at its start and writes them at its end (about as
 // long); both forms give bitwise the same state.
 static bool field_pays(const Tuned &t, int64_t n) {
-    return t.frows > 0 && (double)n * (t.fused_ms - t.field_ms) > 2.0 * t.moments_ms;
+    return t.fixed || t.frows > 0 && (double)n * (t.fused_ms - t.field_ms) > 2.0 * t.moments_ms;
 }
 
 // All fields lie in the spare population buffer where they fit, components
@@ -353,7 +363,7 @@ static FieldRun field_run(const fuglbm_sim *s, int rows, bool single) {
 
 // D3Q19 steps in field form (fields3d.h): tau = 1, planes within 32-bit byte
 // offsets.
-static bool field3_usable(const fuglbm_sim *s) {
+static bool field3_fits(const fuglbm_sim *s) {
     return s->lattice == FUGLBM_D3Q19 && s->kernel == 1 && s->hc.omega == 1.0 && s->N <= field_max_comp() &&
            (int64_t)s->nx * s->ny < ((int64_t)1 << 29) && s->ns < ((int64_t)1 << 31);
 }
@@ -604,7 +614,9 @@ const Shape3 &field3_shape(fuglbm_sim *s) {
 // Members of a batch share the multi-pass launches: there the
 // small grids stay with them (alone false).
 bool field3_pays(fuglbm_sim *s, int64_t n, bool alone) {
-    if (n < 3 || !field3_usable(s)) return false;
+    if (n < 1 || s->form == FUGLBM_FORM_POPULATIONS || !field3_fits(s)) return false;
+    if (form_fixed(s)) return true;
+    if (n < 3) return false;
     if (alone && s->N <= 2 && field3_shape(s).cost <= 12.0) return true;
     const bool lines = s->nx % (s->fp32 ? 16 : 8) == 0;
     const double from = s->fp32 ? (lines ? 28000.0 : 25000.0) : (lines ? 22000.0 : 15000.0);
@@ -633,7 +645,10 @@ fuglbm_status run_field3(fuglbm_sim *s, int64_t n, hipStream_t st) {
         [&](int set, hipStream_t to) { return launch_field_step3(q, s->N, s->fp32, set, to); },
         [&](int set) { return launch_field_last3(q, s->fp32, set, st); }, n,
         s->fgraph[s->parity], st);
-    if (rc == FUGLBM_OK) s->step += n;
+    if (rc == FUGLBM_OK) {
+        s->step += n;
+        s->taken = FUGLBM_FORM_FIELDS;
+    }
     return rc;
 }
 
@@ -1436,6 +1451,8 @@ fuglbm_status fuglbm_init_fields(const fuglbm_mixture *mix, fuglbm_lattice latti
     s->sticky = 0;
     s->autotune = fused;
     s->tuned = false;
+    s->form = s->taken = FUGLBM_FORM_AUTO;
+    s->form_rows = 0;
     s->fgraph[0] = s->fgraph[1] = nullptr;
     s->uid = next_sim_uid();
     s->stage = &device_stage();
@@ -1470,12 +1487,38 @@ fuglbm_status fuglbm_set_tuning(fuglbm_sim *s, int32_t kernel, int32_t rows) {
     HIP_TRY(hipStreamSynchronize(s->last_stream));
     forget_sim_in_batches(s);   // their tables hold what was chosen before
     s->kernel = k;
+    s->form = kernel ? FUGLBM_FORM_POPULATIONS : FUGLBM_FORM_AUTO;
     if (r != s->rows) {
         s->rows = r;
         fuglbm_status rc = build_items(s);
         if (rc != FUGLBM_OK) return rc;
     }
     drop_graphs(s);
+    return FUGLBM_OK;
+}
+
+fuglbm_status fuglbm_set_form(fuglbm_sim *s, int32_t form) {
+    if (!s) return fail(FUGLBM_EINVAL, "null sim");
+    const bool single = form == FUGLBM_FORM_FIELDS_SINGLE;
+    if (form < FUGLBM_FORM_AUTO || form > FUGLBM_FORM_FIELDS_SINGLE)
+        return fail(FUGLBM_EINVAL, "unknown form");
+    if (form >= FUGLBM_FORM_FIELDS && !field_fits(s) && (single || !field3_fits(s)))
+        return fail(FUGLBM_EINVAL, "the simulation's steps have no such form");
+    if (single && s->N > field_single_comp())
+        return fail(FUGLBM_EINVAL, "steps by single wavefronts are built for at most 3 components");
+    HIP_TRY(hipStreamSynchronize(s->last_stream));
+    forget_sim_in_batches(s);
+    drop_graphs(s);
+    s->form = form;
+    s->form_rows = form_fixed(s) && is_fused(s->kernel)
+                       ? (s->autotune ? field_model_rows({s}, single) : s->rows)
+                       : 0;
+    return FUGLBM_OK;
+}
+
+fuglbm_status fuglbm_get_form(const fuglbm_sim *s, int32_t *form) {
+    if (!s || !form) return fail(FUGLBM_EINVAL, "null argument");
+    *form = s->taken;
     return FUGLBM_OK;
 }
 
@@ -1502,15 +1545,20 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *s, int64_t nsteps, void *hip_stream) {
         if (rc != FUGLBM_OK) return rc;
     }
     int64_t left = nsteps;
-    if (left > 0 && is_fused(s->kernel) && s->autotune && !s->tuned) {
+    if (left == 0) return mark_done(s, st);
+    const bool fixed = form_fixed(s) && field_fits(s);
+    if (is_fused(s->kernel) && s->autotune && !s->tuned && !fixed) {
         fuglbm_status rc = autotune_rows(s, st);
         if (rc != FUGLBM_OK) return rc;
     }
-    if (s->tuned && field_usable(s) && field_pays(s->tune, left)) {
-        fuglbm_status rc = run_field(field_run(s, s->tune.frows, s->tune.single), s->N, s->fp32, left,
+    if (fixed || (s->tuned && field_usable(s) && field_pays(s->tune, left))) {
+        const int rows = fixed ? s->form_rows : s->tune.frows;
+        const bool single = fixed ? s->form == FUGLBM_FORM_FIELDS_SINGLE : s->tune.single;
+        fuglbm_status rc = run_field(field_run(s, rows, single), s->N, s->fp32, left,
                                      s->fgraph[s->parity], st);
         if (rc != FUGLBM_OK) return rc;
         s->step += left;
+        s->taken = single ? FUGLBM_FORM_FIELDS_SINGLE : FUGLBM_FORM_FIELDS;
         return mark_done(s, st);
     }
     if (field3_pays(s, left, true)) {
@@ -1518,6 +1566,7 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *s, int64_t nsteps, void *hip_stream) {
         if (rc != FUGLBM_OK) return rc;
         return mark_done(s, st);
     }
+    s->taken = FUGLBM_FORM_POPULATIONS;
     // odd parity first so that graph replays start from buffer 0
     if (left > 0 && s->parity == 1 && left >= 2 * GRAPH_STEPS) {
         hipError_t e = launch_one_step(s, s->parity, st);
@@ -1763,8 +1812,11 @@ void drop_batch_graphs(BatchTable &bt) {
     }
 }
 
-std::map<std::pair<int, int>, BatchTable> &batch_tables() {
-    static std::map<std::pair<int, int>, BatchTable> t;
+// By component count, precision and the form that the members' callers fixed
+// (AUTO where none did).
+using BatchKey = std::tuple<int, int, int>;
+std::map<BatchKey, BatchTable> &batch_tables() {
+    static std::map<BatchKey, BatchTable> t;
     return t;
 }
 
@@ -1889,6 +1941,19 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
                          hipStream_t st) {
     static std::map<std::tuple<int, int, int, int>, Tuned> cache;
     bt.tune = Tuned{};
+    if (form_fixed(group[0])) {   // and with it every member (BatchKey)
+        const bool single = group[0]->form == FUGLBM_FORM_FIELDS_SINGLE;
+        const int rows = group[0]->autotune
+                             ? field_model_rows({group.begin(), group.end()}, single)
+                             : group[0]->rows;
+        fuglbm_status rc = build_batch(bt, group, st);
+        if (rc == FUGLBM_OK) rc = build_field_batch(bt, group, rows, st);
+        if (rc != FUGLBM_OK) return rc;
+        bt.frun.single = bt.tune.single = single;
+        bt.tune.frows = rows;
+        bt.tune.fixed = true;
+        return FUGLBM_OK;
+    }
     for (auto *s : group)
         if (!s->autotune) return build_batch(bt, group, st);   // rows fixed by the caller
     bool auto_k = true, field = true;
@@ -2081,7 +2146,10 @@ fuglbm_status step_group(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
         bt.frun.flip = flip;
         fuglbm_status rc = run_field(bt.frun, nc, f32, left, bt.fgraph[flip], st);
         if (rc != FUGLBM_OK) return rc;
-        for (auto *s : group) s->step += nsteps;
+        for (auto *s : group) {
+            s->step += nsteps;
+            s->taken = bt.frun.single ? FUGLBM_FORM_FIELDS_SINGLE : FUGLBM_FORM_FIELDS;
+        }
         return FUGLBM_OK;
     }
     if (left >= 2 * GRAPH_STEPS && flip == 1) {
@@ -2107,6 +2175,7 @@ fuglbm_status step_group(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
     for (auto *s : group) {
         s->parity ^= (int)(nsteps & 1);
         s->step += nsteps;
+        s->taken = FUGLBM_FORM_POPULATIONS;
     }
     return FUGLBM_OK;
 }
@@ -2138,6 +2207,7 @@ fuglbm_status step_gen_group(GenBatch &gb, const std::vector<fuglbm_sim *> &grou
     for (auto *s : group) {
         s->parity ^= (int)(nsteps & 1);
         s->step += nsteps;
+        s->taken = FUGLBM_FORM_POPULATIONS;
     }
     return FUGLBM_OK;
 }
@@ -2223,7 +2293,7 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
     if (count < 0 || (count > 0 && !sims)) return fail(FUGLBM_EINVAL, "bad sims array");
     if (nsteps < 0) return fail(FUGLBM_EINVAL, "nsteps must be >= 0");
     hipStream_t st = (hipStream_t)hip_stream;
-    std::map<std::pair<int, int>, std::vector<fuglbm_sim *>> groups;
+    std::map<BatchKey, std::vector<fuglbm_sim *>> groups;
     std::vector<fuglbm_sim *> others;
     bool skipped = false;
     for (int k = 0; k < count; ++k) {
@@ -2236,7 +2306,7 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
             continue;
         }
         if (s->lattice == FUGLBM_D2Q9 && is_fused(s->kernel))
-            groups[{s->N, s->fp32 ? 1 : 0}].push_back(s);
+            groups[{s->N, s->fp32 ? 1 : 0, form_fixed(s) ? s->form : 0}].push_back(s);
         else
             others.push_back(s);
     }
@@ -2269,8 +2339,8 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
             for (size_t k = 0; k < group.size(); ++k)
                 if ((group[k]->parity ^ bt.parity0[k]) != flip) same = false;
         }
-        const int nc = kv.first.first;
-        const bool f32 = kv.first.second != 0;
+        const int nc = std::get<0>(kv.first);
+        const bool f32 = std::get<1>(kv.first) != 0;
         if (!same) {
             bt.tune = Tuned{};
             fuglbm_status rc = tune_batch(bt, group, nc, f32, st);
@@ -2544,6 +2614,7 @@ extern "C" fuglbm_status fuglbm_step_many_noalloc(fuglbm_sim *const *sims, int32
         fuglbm_sim *s = sims[k];
         s->parity ^= (int)(nsteps & 1);
         s->step += nsteps;
+        if (nsteps) s->taken = FUGLBM_FORM_POPULATIONS;
         s->last_stream = st;
         s->done_valid = false;   // not recorded here (the caller orders streams)
     }

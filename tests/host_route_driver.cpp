@@ -419,11 +419,76 @@ static void no_steps_first() {
     CHECK(took("field last") == 1);
 }
 
+static int form_of(const Sim &s) {
+    int32_t f = -1;
+    if (fuglbm_get_form(s.s, &f) != FUGLBM_OK) fault("get_form");
+    return f;
+}
+
+// The form a run took is reported, a fixed one is taken, and fixed kernels
+// keep populations.
+static void form_reported_and_fixed() {
+    times(1.0, 0.2, 0.1);
+    Sim a(3, 64, 64), b(3, 70, 40), c(2, 24, 24, 24), d(2, 64, 64, 0, 0.8), e(4, 64, 64);
+    CHECK(form_of(a) == FUGLBM_FORM_AUTO);
+    a.step(0);
+    CHECK(form_of(a) == FUGLBM_FORM_AUTO);
+    a.step(8);
+    CHECK(form_of(a) == FUGLBM_FORM_FIELDS);
+    a.step(1);
+    CHECK(form_of(a) == FUGLBM_FORM_FIELDS || form_of(a) == FUGLBM_FORM_POPULATIONS);
+    CHECK(fuglbm_set_tuning(a.s, 2, 4) == FUGLBM_OK);
+    a.step(8);
+    CHECK(form_of(a) == FUGLBM_FORM_POPULATIONS);
+    // fixed: rows of set_tuning, no trials
+    CHECK(fuglbm_set_tuning(a.s, 0, 7) == FUGLBM_OK);
+    for (int f : {FUGLBM_FORM_FIELDS, FUGLBM_FORM_FIELDS_SINGLE}) {
+        CHECK(fuglbm_set_form(a.s, f) == FUGLBM_OK);
+        CHECK(fuglbm_set_form(b.s, f) == FUGLBM_OK);
+        launched.clear();
+        a.step(1);
+        CHECK(form_of(a) == f && took("field last") == 1 && last_rows == 7);
+        CHECK(took("fused") + took("fused ws") + took("fused block") == 0);
+        a.step(5);
+        CHECK(took(f == FUGLBM_FORM_FIELDS ? "field step" : "field single") == 4);
+        step_many({&a, &b}, 3);
+        CHECK(form_of(a) == f && form_of(b) == f && took("field last") == 2);
+        CHECK(took(f == FUGLBM_FORM_FIELDS ? "field step" : "field single") == 2);
+        CHECK(took("fused") + took("fused ws") + took("fused block") == 0);
+    }
+    CHECK(fuglbm_set_form(a.s, FUGLBM_FORM_POPULATIONS) == FUGLBM_OK);
+    a.step(8);
+    step_many({&a, &b}, 3);
+    CHECK(form_of(a) == FUGLBM_FORM_POPULATIONS && form_of(b) == FUGLBM_FORM_FIELDS_SINGLE);
+    // D3Q19: the four passes where a caller asks for them
+    c.step(8);
+    CHECK(form_of(c) == FUGLBM_FORM_FIELDS && took("field3 last") == 1);
+    CHECK(fuglbm_set_tuning(c.s, 1, 0) == FUGLBM_OK);
+    c.step(8);
+    CHECK(form_of(c) == FUGLBM_FORM_POPULATIONS && took("passes") == 8);
+    step_many({&c}, 8);
+    CHECK(form_of(c) == FUGLBM_FORM_POPULATIONS && took("passes batch") == 8);
+    CHECK(fuglbm_set_tuning(c.s, 0, 0) == FUGLBM_OK);
+    c.step(8);
+    CHECK(form_of(c) == FUGLBM_FORM_FIELDS);
+    CHECK(fuglbm_set_form(c.s, FUGLBM_FORM_FIELDS) == FUGLBM_OK);
+    c.step(1);
+    CHECK(form_of(c) == FUGLBM_FORM_FIELDS);
+    // refused
+    CHECK(fuglbm_set_form(c.s, FUGLBM_FORM_FIELDS_SINGLE) == FUGLBM_EINVAL);
+    CHECK(fuglbm_set_form(d.s, FUGLBM_FORM_FIELDS) == FUGLBM_EINVAL);
+    CHECK(fuglbm_set_form(e.s, FUGLBM_FORM_FIELDS_SINGLE) == FUGLBM_EINVAL);
+    CHECK(fuglbm_set_form(e.s, 4) == FUGLBM_EINVAL && fuglbm_set_form(e.s, -1) == FUGLBM_EINVAL);
+    CHECK(fuglbm_set_form(nullptr, 0) == FUGLBM_EINVAL);
+    CHECK(fuglbm_get_form(e.s, nullptr) == FUGLBM_EINVAL);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, std::function<void()>> all = {
         {"graph_in_flight", graph_in_flight},
         {"tuning_between_batches", tuning_between_batches},
         {"no_steps_first", no_steps_first},
+        {"form_reported_and_fixed", form_reported_and_fixed},
     };
     if (argc < 2) {
         for (auto &k : all) std::printf("%s\n", k.first.c_str());

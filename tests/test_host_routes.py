@@ -11,7 +11,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 HIPCC = "/opt/rocm/bin/hipcc"
 
-SCENARIOS = ["graph_in_flight", "tuning_between_batches", "no_steps_first"]
+SCENARIOS = ["graph_in_flight", "tuning_between_batches", "no_steps_first",
+             "form_reported_and_fixed"]
 
 
 @pytest.fixture(scope="module")
