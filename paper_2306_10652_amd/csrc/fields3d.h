@@ -359,6 +359,14 @@ hipError_t stream(const FieldRun3 &q, int set, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
+template <typename ST, int WAVES>
+int stream_blocks() {
+    int nb = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &nb, (const void *)k_stream3<ST, WAVES>, 64 * WAVES, 0);
+    return e == hipSuccess && nb > 0 ? nb : 1;
+}
+
 template <int NC>
 hipError_t eos(const FieldRun3 &q, int set, hipStream_t st) {
     hipLaunchKernelGGL((k_eos3<NC>), dim3(nblocks(q.ns)), dim3(TPB), 0, st, q.f[set]);
@@ -372,6 +380,14 @@ void velocity(const FieldRun3 &q, int set, hipStream_t st) {
 }
 
 }  // namespace fields3
+
+int field3_blocks_per_cu(bool fp32, int waves) {
+    switch (waves) {
+        case 4: return fp32 ? fields3::stream_blocks<float, 4>() : fields3::stream_blocks<double, 4>();
+        case 8: return fp32 ? fields3::stream_blocks<float, 8>() : fields3::stream_blocks<double, 8>();
+        default: return fields3::stream_blocks<float, 12>();
+    }
+}
 
 hipError_t launch_field_moments3(const FieldRun3 &q, bool fp32, hipStream_t st) {
     const dim3 nb(nblocks(q.ns));

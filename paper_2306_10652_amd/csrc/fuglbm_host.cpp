@@ -567,8 +567,9 @@ fuglbm_status run_field(const FieldRun &q, int ncomp, bool fp32, int64_t n, hipG
 // Tiles of the stream kernel.  A workgroup collides W x R sites a plane for
 // (W - 4) x (R - 2) of output, and its two rim planes cost 0.9 of a plane,
 // so wide, tall and long tiles waste least; but all of them should be
-// resident at once, and a SIMD works through its wavefronts one after
-// another.  The cheapest of the widths, heights and chunk lengths by
+// resident at once (as many to a CU as the kernel's registers allow: 8
+// wavefronts in FP64, 12 in FP32 storage), and a SIMD works through its
+// wavefronts one after another.  The cheapest of the widths, heights and chunk lengths by
 //   cost = rounds x (zc + 0.9) x wavefronts per SIMD (at least 2: latency)
 //          x components,
 // planes of one wavefront that a SIMD works through.  Measured steps take
@@ -578,19 +579,23 @@ const Shape3 &field3_shape(fuglbm_sim *s) {
     if (s->shape3.W) return s->shape3;
     const int most = s->fp32 ? 12 : 8, cus = compute_units();
     Shape3 best{32, most, 1, 1e300};
-    for (int waves = 4; waves <= most; waves += 4)
+    for (int waves = 4; waves <= most; waves += 4) {
+        const int per_cu = field3_blocks_per_cu(s->fp32, waves), slots = cus * per_cu;
         for (int W = 16; W <= 64; W *= 2) {
-            const int R = 64 * waves / W, slots = cus * (12 / waves);
+            const int R = 64 * waves / W;
             const int64_t cols = (int64_t)((s->nx + W - 5) / (W - 4)) * ((s->ny + R - 3) / (R - 2));
-            for (int zc = 1; zc <= s->nz; ++zc) {
-                const int64_t items = cols * ((s->nz + zc - 1) / zc);
+            // chunk lengths: the shortest for each count of chunks
+            for (int zc = 1, tz = 0; tz != 1; zc = tz > 1 ? (s->nz + tz - 2) / (tz - 1) : zc) {
+                tz = (s->nz + zc - 1) / zc;
+                const int64_t items = cols * tz;
                 const double rounds = (double)((items + slots - 1) / slots);
-                const int resident = (int)std::min<int64_t>(12 / waves, (items + cus - 1) / cus);
+                const int resident = (int)std::min<int64_t>(per_cu, (items + cus - 1) / cus);
                 const double per_simd = std::max(2.0, waves * resident / 4.0);
                 const double cost = rounds * (zc + 0.9) * per_simd * s->N;
                 if (cost < best.cost) best = {W, waves, zc, cost};
             }
         }
+    }
     return s->shape3 = best;
 }
 
@@ -601,7 +606,7 @@ const Shape3 &field3_shape(fuglbm_sim *s) {
 // lines, so that it writes parts of them; the field step goes by its cost.
 // Measured either side of each line, ns N / cost and multi-pass / field us a
 // step, N = 10:
-//   FP64          48^3 (19 400) 102 / 108     64^3 (26 700) 198 / 160
+//   FP64          48^3 (19 100) 105 / 101     64^3 (26 700) 198 / 160
 //     part lines  36^3 (12 300) 71 / 73       90 50 50 (23 000) 252 / 160
 //   FP32          64^3 (26 700) 146 / 150     128^3 (41 400) 1211 / 914
 //     part lines  50 120 24 (24 800) 103.5 / 104.1   90 50 50 (25 900) 170 / 135

@@ -163,6 +163,8 @@ struct FieldRun3 {
     Tiles3 tiles;
     int64_t total[3];     // work units as of GenMember::end
 };
+// Resident workgroups of the stream kernel per CU (occupancy query).
+int field3_blocks_per_cu(bool fp32, int waves);
 // populations -> set 0 with its psi
 hipError_t launch_field_moments3(const FieldRun3 &q, bool fp32, hipStream_t st);
 // one step from set `set` to the other one with its psi

@@ -286,6 +286,8 @@ hipError_t launch_field_step2d(const FieldRun &q, int, bool, bool last, int, hip
     run(last ? "field last" : (q.single ? "field single" : "field step"), s);
     return hipSuccess;
 }
+// FP64 at two wavefronts a SIMD, FP32 storage at three
+int field3_blocks_per_cu(bool fp32, int waves) { return (fp32 ? 12 : 8) / waves; }
 hipError_t launch_field_moments3(const FieldRun3 &, bool, hipStream_t s) {
     run("field3 moments", s);
     return hipSuccess;
@@ -483,11 +485,27 @@ static void form_reported_and_fixed() {
     CHECK(fuglbm_get_form(e.s, nullptr) == FUGLBM_EINVAL);
 }
 
+// The tiles of the D3Q19 stream kernel count what is resident at a time: 48^3 x
+// 10 in FP64 takes one round of 512 workgroups of four wavefronts, in FP32
+// storage one of 768.
+static void tiles_that_are_resident() {
+    Sim a(10, 48, 48, 48), b(10, 48, 48, 48, 1.0, FUGLBM_FP32_STORAGE);
+    CHECK(fuglbm_set_form(a.s, FUGLBM_FORM_FIELDS) == FUGLBM_OK);
+    a.step(3);
+    CHECK(stream3_waves == 4 && stream3_tiles.W == 16 && stream3_tiles.zc == 2);
+    CHECK(stream3_items == 384);
+    CHECK(fuglbm_set_form(b.s, FUGLBM_FORM_FIELDS) == FUGLBM_OK);
+    b.step(3);
+    CHECK(stream3_waves == 4 && stream3_tiles.W == 16 && stream3_tiles.zc == 1);
+    CHECK(stream3_items == 768);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, std::function<void()>> all = {
         {"graph_in_flight", graph_in_flight},
         {"tuning_between_batches", tuning_between_batches},
         {"no_steps_first", no_steps_first},
+        {"tiles_that_are_resident", tiles_that_are_resident},
         {"form_reported_and_fixed", form_reported_and_fixed},
     };
     if (argc < 2) {

@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 HIPCC = "/opt/rocm/bin/hipcc"
 
 SCENARIOS = ["graph_in_flight", "tuning_between_batches", "no_steps_first",
-             "form_reported_and_fixed"]
+             "form_reported_and_fixed", "tiles_that_are_resident"]
 
 
 @pytest.fixture(scope="module")
