@@ -206,8 +206,14 @@ struct GraphCache {
 
 // Tiles of the D3Q19 stream kernel (field3_shape); W 0: not chosen yet.
 struct Shape3 {
+    static constexpr double NONE = 1e300;   // cost where no launch can hold the tiles
     int W = 0, waves = 0, zc = 0;
     double cost = 0.0;
+    double rounds = 0.0, simd = 0.0;        // wavefronts that share a SIMD
+};
+// What a step of a D3Q19 simulation takes in four passes and in field form (us).
+struct Step3 {
+    double passes = 0.0, fields = 0.0;
 };
 // What the autotuner chose for a shape: the fused variant and its rows per
 // item, the field-form rows (0: not built for it), and what a step of each
@@ -572,13 +578,11 @@ fuglbm_status run_field(const FieldRun &q, int ncomp, bool fp32, int64_t n, hipG
 // wavefronts one after another.  The cheapest of the widths, heights and chunk lengths by
 //   cost = rounds x (zc + 0.9) x wavefronts per SIMD (at least 2: latency)
 //          x components,
-// planes of one wavefront that a SIMD works through.  Measured steps take
-// 12 us + 1.35 ... 1.8 us x cost (N = 9 and 10, 36^3 ... 128^3, both
-// precisions).
+// planes of one wavefront that a SIMD works through.
 const Shape3 &field3_shape(fuglbm_sim *s) {
     if (s->shape3.W) return s->shape3;
     const int most = s->fp32 ? 12 : 8, cus = compute_units();
-    Shape3 best{32, most, 1, 1e300};
+    Shape3 best{32, most, 1, Shape3::NONE};
     for (int waves = 4; waves <= most; waves += 4) {
         const int per_cu = field3_blocks_per_cu(s->fp32, waves), slots = cus * per_cu;
         for (int W = 16; W <= 64; W *= 2) {
@@ -588,44 +592,88 @@ const Shape3 &field3_shape(fuglbm_sim *s) {
             for (int zc = 1, tz = 0; tz != 1; zc = tz > 1 ? (s->nz + tz - 2) / (tz - 1) : zc) {
                 tz = (s->nz + zc - 1) / zc;
                 const int64_t items = cols * tz;
+                if ((items + 7) * 64 * waves >= (int64_t)1 << 32) continue;   // threads of a launch
                 const double rounds = (double)((items + slots - 1) / slots);
                 const int resident = (int)std::min<int64_t>(per_cu, (items + cus - 1) / cus);
                 const double per_simd = std::max(2.0, waves * resident / 4.0);
                 const double cost = rounds * (zc + 0.9) * per_simd * s->N;
-                if (cost < best.cost) best = {W, waves, zc, cost};
+                if (cost < best.cost)
+                    best = {W, waves, zc, cost, rounds, waves * resident / 4.0};
             }
         }
     }
     return s->shape3 = best;
 }
 
-// The field form moves a third of the bytes but collides the rims of its
-// tiles twice, and a chip of one or two short tiles per CU does little else.
-// The multi-pass step takes about 75 ps per site and component in FP64 and
-// 57 ps in FP32 storage, 115 and 72 ps where rows are not whole 64-byte
-// lines, so that it writes parts of them; the field step goes by its cost.
-// Measured either side of each line, ns N / cost and multi-pass / field us a
-// step, N = 10:
-//   FP64          48^3 (19 100) 105 / 101     64^3 (26 700) 198 / 160
-//     part lines  36^3 (12 300) 71 / 73       90 50 50 (23 000) 252 / 160
-//   FP32          64^3 (26 700) 146 / 150     128^3 (41 400) 1211 / 914
-//     part lines  50 120 24 (24 800) 103.5 / 104.1   90 50 50 (25 900) 170 / 135
-// A run of three steps gains what its first and last cost (64^3 FP64: 206
-// multi-pass, 184).  With one and two components a step is mostly launches,
-// three instead of four (9 8 7, N = 1: 18.4 / 12.3, N = 2: 21.8 / 16.9; 40^3
-// 22.7 / 16.2 and 28.7 / 22.9; 64 64 24 25.3 / 20.9 and 29.8 / 30.2), up to
-// twelve units of cost (64 64 40, N = 2, FP32: 33.5 / 35.6 at 16); with three
-// it depends on the shape (24^3 26.0 / 22.0, 64 64 24 38.3 / 39.7).
-// Members of a batch share the multi-pass launches: there the
-// small grids stay with them (alone false).
-bool field3_pays(fuglbm_sim *s, int64_t n, bool alone) {
-    if (n < 1 || s->form == FUGLBM_FORM_POPULATIONS || !field3_fits(s)) return false;
-    if (form_fixed(s)) return true;
-    if (n < 3) return false;
-    if (alone && s->N <= 2 && field3_shape(s).cost <= 12.0) return true;
+// What the four passes take beside their volume (us): launches and latencies,
+// which the members of a batch share.
+double step3_latency(int ncomp) { return 14.0 + 3.2 * ncomp; }
+
+// What a step takes in either form (us).  The four passes: latencies
+// (components one after another); sites and components, more where rows are
+// not whole 64-byte lines, so that the collision writes parts of them, and
+// more again for those past what the last-level cache holds; and the sites
+// that the 64 x 2 x 2 tiles of the collision cover.  The field form: latencies,
+// the planes that a SIMD works through (the more wavefronts share it the longer
+// each takes), the EOS by sites and components, and the velocity pass by the
+// sites that its 16 x 4 x 4 tiles cover.
+//
+// Fitted to 616 pairs of steps measured in runs of 65 (N = 1 ... 10, 9 7 8 ...
+// 128^3, widths from 8, both precisions): 4.8 and 3.6 % off (rms).  The form
+// they pick is the slower one by more than 5 % for eleven of the pairs, 8.5 %
+// at worst (33 33 120, N = 10, FP32 storage: passes 111, fields 121 us), 0.3 %
+// in the mean; thresholds on sites per cost, which these replace, lost up to
+// 83 % (8 96 96, N = 3: 65.7 and 36.0 us) and 5.4 % in the mean.  Far from a
+// tie: 128^3 x 10 FP64 1868 / 973, FP32 storage 1210 / 892; 32 17 96, N = 10,
+// FP32 storage 69 / 84.  Trials at the first run of a shape were no better:
+// short ones find the clocks low, which the field form's VALU work feels more
+// (64^3 x 10 FP64: 203 / 199 in trials of four steps, 199 / 157 in a run).
+Step3 step3_estimate(fuglbm_sim *s) {
+    const double n = s->N, sites = 1e-6 * (double)s->ns, work = sites * n;
     const bool lines = s->nx % (s->fp32 ? 16 : 8) == 0;
-    const double from = s->fp32 ? (lines ? 28000.0 : 25000.0) : (lines ? 22000.0 : 15000.0);
-    return (double)s->ns * s->N >= from * field3_shape(s).cost;
+    int64_t units[3];
+    generic_units(1, s->N, s->nx, s->ny, s->nz, units);
+    const double velocity = 256e-6 * (double)units[1] * n, collision = 256e-6 * (double)units[2];
+    const double far = std::max(0.0, work - (s->fp32 ? 0.9 : 0.6));
+    const Shape3 &h = field3_shape(s);
+    Step3 e;
+    e.passes = step3_latency(s->N) + 39.0 * sites + 20.5 * collision +
+               (s->fp32 ? (lines ? 3.0 * work + 23.0 * far : 4.0 * work + 29.0 * far)
+                        : (lines ? 15.0 * work + 26.0 * far : 21.0 * work + 53.0 * far));
+    e.fields = 7.9 + (s->fp32 ? 3.6 : 3.9) * n + 22.0 * sites + (s->fp32 ? 7.0 : 8.0) * work +
+               4.0 * velocity +
+               (s->fp32 ? 1.17 * h.simd - 0.43 : 1.36 * h.simd - 0.58) * h.rounds * h.zc * n;
+    return e;
+}
+
+// Members of a D3Q19 group that take a run of n steps in field form, the
+// others in `rest`: those whose caller fixed it, and, from three steps on,
+// those whose step is faster so than what it adds to the passes that the group
+// shares; or all, where that is faster than shared passes for the few that are
+// left.
+void split_forms3(const std::vector<fuglbm_sim *> &group, int64_t n,
+                  std::vector<fuglbm_sim *> &fields, std::vector<fuglbm_sim *> &rest) {
+    double shared = 0.0, apart = 0.0, latency = 0.0;
+    bool all = true;   // every one in `rest` may take the field form
+    for (auto *s : group) {
+        const bool fits = field3_fits(s) && field3_shape(s).cost < Shape3::NONE;
+        const bool open = fits && n >= 3 && s->form == FUGLBM_FORM_AUTO;
+        const double lat = step3_latency(s->N);
+        const Step3 c = open ? step3_estimate(s) : Step3{};
+        if ((fits && form_fixed(s)) || (open && c.fields < c.passes - lat)) {
+            fields.push_back(s);
+            continue;
+        }
+        rest.push_back(s);
+        all = all && open;
+        shared += c.passes - lat;
+        apart += c.fields;
+        latency = std::max(latency, lat);
+    }
+    if (all && apart < shared + latency) {
+        fields = group;
+        rest.clear();
+    }
 }
 
 FieldRun3 field3_run(fuglbm_sim *s) {
@@ -1507,7 +1555,8 @@ fuglbm_status fuglbm_set_form(fuglbm_sim *s, int32_t form) {
     const bool single = form == FUGLBM_FORM_FIELDS_SINGLE;
     if (form < FUGLBM_FORM_AUTO || form > FUGLBM_FORM_FIELDS_SINGLE)
         return fail(FUGLBM_EINVAL, "unknown form");
-    if (form >= FUGLBM_FORM_FIELDS && !field_fits(s) && (single || !field3_fits(s)))
+    if (form >= FUGLBM_FORM_FIELDS && !field_fits(s) &&
+        (single || !field3_fits(s) || field3_shape(s).cost == Shape3::NONE))
         return fail(FUGLBM_EINVAL, "the simulation's steps have no such form");
     if (single && s->N > field_single_comp())
         return fail(FUGLBM_EINVAL, "steps by single wavefronts are built for at most 3 components");
@@ -1566,10 +1615,14 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *s, int64_t nsteps, void *hip_stream) {
         s->taken = single ? FUGLBM_FORM_FIELDS_SINGLE : FUGLBM_FORM_FIELDS;
         return mark_done(s, st);
     }
-    if (field3_pays(s, left, true)) {
-        fuglbm_status rc = run_field3(s, left, st);
-        if (rc != FUGLBM_OK) return rc;
-        return mark_done(s, st);
+    if (s->lattice == FUGLBM_D3Q19) {
+        std::vector<fuglbm_sim *> fields, rest;
+        split_forms3({s}, left, fields, rest);
+        if (!fields.empty()) {
+            fuglbm_status rc = run_field3(s, left, st);
+            if (rc != FUGLBM_OK) return rc;
+            return mark_done(s, st);
+        }
     }
     s->taken = FUGLBM_FORM_POPULATIONS;
     // odd parity first so that graph replays start from buffer 0
@@ -2362,9 +2415,10 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         ggroups[{s->lattice, s->fp32 ? 1 : 0, s->hc.omega != 1.0 ? 1 : 0}].push_back(s);
     for (auto &kv : ggroups) {
         auto &group = kv.second;
-        // members that each pay in field form fill the chip one by one
-        if (std::all_of(group.begin(), group.end(),
-                        [&](fuglbm_sim *s) { return field3_pays(s, nsteps, group.size() == 1); })) {
+        // members that all take the field form do so one by one
+        std::vector<fuglbm_sim *> fields, rest;
+        if (group[0]->lattice == FUGLBM_D3Q19) split_forms3(group, nsteps, fields, rest);
+        if (fields.size() == group.size()) {
             tasks.push_back({group_cost(group), [&group, nsteps](hipStream_t to) {
                                  for (auto *s : group) {
                                      fuglbm_status rc = run_field3(s, nsteps, to);

@@ -229,9 +229,12 @@ hipError_t launch_to_host(const double *a, int64_t na, const double *b, int64_t 
     *word = *status;
     return hipSuccess;
 }
+// tiles of 16 x 4 x 4 and 64 x 2 x 2 sites
 void generic_units(int, int ncomp, int nx, int ny, int nz, int64_t units[3]) {
-    units[0] = units[1] = ((int64_t)nx * ny * nz + 255) / 256;
-    units[2] = units[0] * ncomp;
+    auto up = [](int a, int b) { return (int64_t)((a + b - 1) / b); };
+    units[0] = ((int64_t)nx * ny * nz + 255) / 256;
+    units[1] = up(nx, 16) * up(ny, 4) * up(nz, 4);
+    units[2] = up(nx, 64) * up(ny, 2) * up(nz, 2) * ncomp;
 }
 hipError_t launch_step_generic_batch(int, bool, bool, const GenMember *, int n, const int64_t[3], int,
                                      hipStream_t s) {
@@ -500,12 +503,42 @@ static void tiles_that_are_resident() {
     CHECK(stream3_items == 768);
 }
 
+// The form of a D3Q19 run follows what either is estimated to take, for small
+// grids of several components and narrow ones too.
+static void cube_forms_by_estimate() {
+    struct {
+        int n, nx, ny, nz;
+        fuglbm_precision prec;
+        bool fields;
+    } cases[] = {
+        // N, shape, storage: measured passes / fields, us
+        {3, 24, 24, 24, FUGLBM_FP64, true},              // 26 / 22
+        {3, 8, 96, 96, FUGLBM_FP64, true},               // 70 / 39
+        {8, 12, 132, 50, FUGLBM_FP32_STORAGE, true},     // 112 / 64
+        {10, 64, 64, 64, FUGLBM_FP64, true},             // 199 / 157
+        {2, 9, 8, 7, FUGLBM_FP64, true},                 // 21 / 17
+        {10, 32, 17, 96, FUGLBM_FP32_STORAGE, false},    // 69 / 84
+        {10, 48, 48, 48, FUGLBM_FP32_STORAGE, false},    // 85 / 93
+        {10, 27, 10, 9, FUGLBM_FP64, false},             // 48 / 55
+    };
+    for (auto &k : cases) {
+        Sim s(k.n, k.nx, k.ny, k.nz, 1.0, k.prec);
+        s.step(2);
+        CHECK(form_of(s) == FUGLBM_FORM_POPULATIONS);
+        s.step(3);
+        if ((form_of(s) == FUGLBM_FORM_FIELDS) != k.fields)
+            fault("form of " + std::to_string(k.n) + " x " + std::to_string(k.nx) + " " +
+                  std::to_string(k.ny) + " " + std::to_string(k.nz));
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, std::function<void()>> all = {
         {"graph_in_flight", graph_in_flight},
         {"tuning_between_batches", tuning_between_batches},
         {"no_steps_first", no_steps_first},
         {"tiles_that_are_resident", tiles_that_are_resident},
+        {"cube_forms_by_estimate", cube_forms_by_estimate},
         {"form_reported_and_fixed", form_reported_and_fixed},
     };
     if (argc < 2) {

@@ -12,7 +12,8 @@ ROOT = os.path.dirname(HERE)
 HIPCC = "/opt/rocm/bin/hipcc"
 
 SCENARIOS = ["graph_in_flight", "tuning_between_batches", "no_steps_first",
-             "form_reported_and_fixed", "tiles_that_are_resident"]
+             "form_reported_and_fixed", "tiles_that_are_resident",
+             "cube_forms_by_estimate"]
 
 
 @pytest.fixture(scope="module")
