@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstring>
 #include <functional>
+#include <list>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -650,8 +651,11 @@ Step3 step3_estimate(fuglbm_sim *s) {
 // others in `rest`: those whose caller fixed it, and, from three steps on,
 // those whose step is faster so than what it adds to the passes that the group
 // shares; or all, where that is faster than shared passes for the few that are
-// left.
-void split_forms3(const std::vector<fuglbm_sim *> &group, int64_t n,
+// left.  What a member adds is its volume, in the passes of a batch
+// (`batched`), where every block looks its member up, 1.3 times of it: three
+// 64^3 x 4 take 267 us a step so (FP64; 273 by this) and 212 in field form,
+// four 40^3 x 3 90 us (88) and 153, 128^3 x 10 with 20 11 9 x 10 2090 and 975.
+void split_forms3(const std::vector<fuglbm_sim *> &group, int64_t n, bool batched,
                   std::vector<fuglbm_sim *> &fields, std::vector<fuglbm_sim *> &rest) {
     double shared = 0.0, apart = 0.0, latency = 0.0;
     bool all = true;   // every one in `rest` may take the field form
@@ -660,13 +664,14 @@ void split_forms3(const std::vector<fuglbm_sim *> &group, int64_t n,
         const bool open = fits && n >= 3 && s->form == FUGLBM_FORM_AUTO;
         const double lat = step3_latency(s->N);
         const Step3 c = open ? step3_estimate(s) : Step3{};
-        if ((fits && form_fixed(s)) || (open && c.fields < c.passes - lat)) {
+        const double adds = (batched ? 1.3 : 1.0) * (c.passes - lat);
+        if ((fits && form_fixed(s)) || (open && c.fields < adds)) {
             fields.push_back(s);
             continue;
         }
         rest.push_back(s);
         all = all && open;
-        shared += c.passes - lat;
+        shared += adds;
         apart += c.fields;
         latency = std::max(latency, lat);
     }
@@ -1617,7 +1622,7 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *s, int64_t nsteps, void *hip_stream) {
     }
     if (s->lattice == FUGLBM_D3Q19) {
         std::vector<fuglbm_sim *> fields, rest;
-        split_forms3({s}, left, fields, rest);
+        split_forms3({s}, left, false, fields, rest);
         if (!fields.empty()) {
             fuglbm_status rc = run_field3(s, left, st);
             if (rc != FUGLBM_OK) return rc;
@@ -2079,8 +2084,8 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
 }  // namespace
 
 // Batched multi-pass step (D3Q19, and D2Q9 simulations on the multi-pass
-// kernels): one member table per (lattice, storage precision, tau != 1),
-// cached while the member set is the same; four launches per step over all
+// kernels): one member table per (lattice, storage precision, tau != 1, and
+// whether other members of the group take the field form), cached while the member set is the same; four launches per step over all
 // members (no tuning: the multi-pass kernels have no variants), runs of
 // GRAPH_STEPS steps replayed from a captured graph as for the fused tables.
 struct GenBatch {
@@ -2112,8 +2117,8 @@ fuglbm_status gen_batch_graph(GenBatch &gb) {
                          gb.graph, "multi-pass batch graph");
 }
 
-std::map<std::tuple<int, int, int>, GenBatch> &gen_batches() {
-    static std::map<std::tuple<int, int, int>, GenBatch> t;
+std::map<std::tuple<int, int, int, int>, GenBatch> &gen_batches() {
+    static std::map<std::tuple<int, int, int, int>, GenBatch> t;
     return t;
 }
 
@@ -2409,26 +2414,25 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
                              return step_group(bt, group, nc, f32, flip, nsteps, to);
                          }});
     }
-    // multi-pass members: one table per (lattice, precision, tau != 1)
+    // multi-pass members by (lattice, precision, tau != 1): those that take the
+    // field form do so one by one, the others share one table
     std::map<std::tuple<int, int, int>, std::vector<fuglbm_sim *>> ggroups;
+    std::list<std::vector<fuglbm_sim *>> parts;   // what the tasks refer to
     for (auto *s : others)
         ggroups[{s->lattice, s->fp32 ? 1 : 0, s->hc.omega != 1.0 ? 1 : 0}].push_back(s);
     for (auto &kv : ggroups) {
-        auto &group = kv.second;
-        // members that all take the field form do so one by one
-        std::vector<fuglbm_sim *> fields, rest;
-        if (group[0]->lattice == FUGLBM_D3Q19) split_forms3(group, nsteps, fields, rest);
-        if (fields.size() == group.size()) {
-            tasks.push_back({group_cost(group), [&group, nsteps](hipStream_t to) {
-                                 for (auto *s : group) {
+        std::vector<fuglbm_sim *> &fields = parts.emplace_back(), &group = parts.emplace_back();
+        split_forms3(kv.second, nsteps, true, fields, group);
+        if (!fields.empty())
+            tasks.push_back({group_cost(fields), [&fields, nsteps](hipStream_t to) {
+                                 for (auto *s : fields) {
                                      fuglbm_status rc = run_field3(s, nsteps, to);
                                      if (rc != FUGLBM_OK) return rc;
                                  }
                                  return FUGLBM_OK;
                              }});
-            continue;
-        }
-        GenBatch &gb = gen_batches()[kv.first];
+        if (group.empty()) continue;
+        GenBatch &gb = gen_batches()[std::tuple_cat(kv.first, std::make_tuple(fields.empty() ? 0 : 1))];
         // the table is shared state: launches queued on another stream must
         // finish before this call rebuilds or reuses it
         if (gb.used && gb.last_stream != st) HIP_TRY(hipStreamSynchronize(gb.last_stream));

@@ -532,6 +532,33 @@ static void cube_forms_by_estimate() {
     }
 }
 
+// A D3Q19 member takes the form it would take, whatever else is in the batch:
+// a small one does not send a large one back to the passes.
+static void cubes_routed_one_by_one() {
+    Sim big(10, 80, 80, 80), small(10, 24, 24, 24), tiny(10, 27, 10, 9), old(3, 20, 20, 20, 0.8),
+        fixed(10, 27, 10, 9);
+    CHECK(fuglbm_set_form(fixed.s, FUGLBM_FORM_FIELDS) == FUGLBM_OK);
+    launched.clear();
+    step_many({&small, &big, &tiny, &old}, 5);
+    CHECK(form_of(big) == FUGLBM_FORM_FIELDS && took("field3 last") == 1);
+    CHECK(form_of(small) == FUGLBM_FORM_POPULATIONS && form_of(tiny) == FUGLBM_FORM_POPULATIONS);
+    CHECK(form_of(old) == FUGLBM_FORM_POPULATIONS);
+    CHECK(took("passes batch") == 10);          // tau = 1 and tau = 0.8, five steps each
+    step_many({&small, &big, &tiny}, 1);        // all share the passes
+    CHECK(last_members == 3 && took("passes batch") == 1 && took("field3 last") == 0);
+    step_many({&small, &big, &tiny}, 5);
+    CHECK(last_members == 2 && took("passes batch") == 5 && took("field3 last") == 1);
+    step_many({&tiny, &fixed}, 2);
+    CHECK(form_of(fixed) == FUGLBM_FORM_FIELDS && form_of(tiny) == FUGLBM_FORM_POPULATIONS);
+    // two that would take it alone share the passes' launches instead, where
+    // those cost less than what each adds to them
+    Sim a(6, 24, 24, 24), b(6, 24, 24, 24), c(6, 24, 24, 24);
+    a.step(5);
+    CHECK(form_of(a) == FUGLBM_FORM_FIELDS);
+    step_many({&a, &b, &c}, 5);
+    CHECK(form_of(a) == FUGLBM_FORM_POPULATIONS && form_of(c) == FUGLBM_FORM_POPULATIONS);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, std::function<void()>> all = {
         {"graph_in_flight", graph_in_flight},
@@ -539,6 +566,7 @@ int main(int argc, char **argv) {
         {"no_steps_first", no_steps_first},
         {"tiles_that_are_resident", tiles_that_are_resident},
         {"cube_forms_by_estimate", cube_forms_by_estimate},
+        {"cubes_routed_one_by_one", cubes_routed_one_by_one},
         {"form_reported_and_fixed", form_reported_and_fixed},
     };
     if (argc < 2) {
