@@ -248,14 +248,15 @@ fuglbm_status fuglbm_write_populations(fuglbm_sim *sim, const double *g_in, int6
  * fuglbm_step_many) may carry densities and momentum instead of populations
  * between its first and last step, in the population buffer that the run does
  * not read: on D2Q9 with kernel 0 and rows 0, where the trials find it
- * faster; on D3Q19 on grids that fill the GPU and with one or two components.
+ * faster; on D3Q19 with kernel 0 where it is estimated to be faster.
  * The state it ends in is bitwise the same;
  * rows = output rows per fused work item (>= 1, fixed), or 0 = autotuned:
  * the next fuglbm_step_n times a few trial launches per candidate (they
  * read the current state and write the spare buffer, so the state does
  * not move) and keeps the fastest; with kernel 0 both fused variants are
- * timed and the faster (variant, rows) is kept.  The choice is cached per
- * (nx, ny, ncomp, precision) for the process.  The state does not depend
+ * timed and the faster (variant, rows) is kept.  The form that carries
+ * densities and momentum is timed by the first call of two steps or more.
+ * The choice is cached per (nx, ny, ncomp, precision) for the process.  The state does not depend
  * on the variant or on rows.  fuglbm_step_many tunes one (variant, rows)
  * per batch shape the same way unless a member has fixed rows.
  * Autotuning is the default.  EINVAL for a kernel the simulation cannot

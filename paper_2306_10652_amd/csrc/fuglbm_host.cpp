@@ -217,7 +217,7 @@ struct Step3 {
     double passes = 0.0, fields = 0.0;
 };
 // What the autotuner chose for a shape: the fused variant and its rows per
-// item, the field-form rows (0: not built for it), and what a step of each
+// item, the field-form rows (0: not timed), and what a step of each
 // and the field form's read of the populations took (ms).  fixed: the form is
 // the caller's (fuglbm_set_form), nothing was timed.
 struct Tuned {
@@ -329,9 +329,10 @@ static bool form_fixed(const fuglbm_sim *s) { return s->form >= FUGLBM_FORM_FIEL
 
 // Whether a run of n steps is taken in field form.  Beside its steps it
 // reads the populations at its start and writes them at its end (about as
-// long); both forms give bitwise the same state.
+// long); both forms give bitwise the same state.  One step never gains.
 static bool field_pays(const Tuned &t, int64_t n) {
-    return t.fixed || t.frows > 0 && (double)n * (t.fused_ms - t.field_ms) > 2.0 * t.moments_ms;
+    if (t.fixed) return true;
+    return t.frows > 0 && n >= 2 && (double)n * (t.fused_ms - t.field_ms) > 2.0 * t.moments_ms;
 }
 
 // All fields lie in the spare population buffer where they fit, components
@@ -892,19 +893,23 @@ fuglbm_status set_rows(fuglbm_sim *s, int rows, hipStream_t st) {
 }
 
 // With the variant left to the tuner, both fused variants are timed (each
-// at its own rows candidates) and the faster (variant, rows) is kept; where
-// the steps can be taken in field form, that is timed too (time_field).
+// at its own rows candidates) and the faster (variant, rows) is kept.
 // The choice is cached.  Every candidate's work table
 // is uploaded once, before any timing, and the candidates run back to back
 // with an event pair each and one synchronisation at the end: the GPU
 // stays busy through the whole trial, so the candidates are timed under
 // the same sustained load (with a host wait between candidates the clocks
 // fall back and the early candidates run slower).
+std::tuple<int, int, int, int> tune_key(const fuglbm_sim *s) {
+    const bool both = s->auto_kernel && ws_usable(s->N, s->fp32);
+    const int tag = (both ? 0 : s->kernel) + (field_usable(s) ? 4 : 0);
+    return {s->nx, s->ny, s->N, (s->fp32 ? 1 : 0) + 2 * tag};
+}
+
 fuglbm_status autotune_rows(fuglbm_sim *s, hipStream_t st) {
     const TraceRange trace_range("fuglbm autotune rows");
     const bool both = s->auto_kernel && ws_usable(s->N, s->fp32);
-    const int tag = (both ? 0 : s->kernel) + (field_usable(s) ? 4 : 0);
-    const auto key = std::make_tuple(s->nx, s->ny, s->N, (s->fp32 ? 1 : 0) + 2 * tag);
+    const auto key = tune_key(s);
     auto hit = tune_cache().find(key);
     Tuned &tn = s->tune;
     if (hit != tune_cache().end()) {
@@ -976,22 +981,36 @@ fuglbm_status autotune_rows(fuglbm_sim *s, hipStream_t st) {
             }
         }
         tn.fused_ms = best_ms / (2 * TUNE_LAUNCHES);
-        if (field_usable(s)) {
-            fuglbm_status rc = time_field(
-                {s}, st,
-                [&](int r, FieldRun &q) {
-                    q = field_run(s, r, false);
-                    return FUGLBM_OK;
-                },
-                tn);
-            if (rc != FUGLBM_OK) return rc;
-        }
         tune_cache()[key] = tn;
     }
     HIP_TRY(hipStreamSynchronize(st));
     s->kernel = tn.kernel;
     s->tuned = true;
     return set_rows(s, tn.rows, st);
+}
+
+// The field form beside it, timed at the first run of several steps: programs
+// that take single steps do not pay for it.  Once per shape it costs (fused
+// variants / field form, ms): 64^2 x 3 9 / 4, 256^2 x 3 26 / 12, 200^2 x 10
+// 50 / 7, 1024^2 x 3 83 / 31, 1024^2 x 10 211 / 27; a batch of 12 grids of
+// 64^2 ... 152^2 x 3 23 / 14.
+fuglbm_status autotune_field(fuglbm_sim *s, hipStream_t st) {
+    const TraceRange trace_range("fuglbm autotune field form");
+    Tuned &c = tune_cache()[tune_key(s)];
+    if (!c.frows) {
+        Tuned tn = s->tune;
+        fuglbm_status rc = time_field(
+            {s}, st,
+            [&](int r, FieldRun &q) {
+                q = field_run(s, r, false);
+                return FUGLBM_OK;
+            },
+            tn);
+        if (rc != FUGLBM_OK) return rc;
+        c = tn;
+    }
+    s->tune = c;
+    return FUGLBM_OK;
 }
 
 // ---- side streams of a batch ----------------------------------------------
@@ -1610,6 +1629,11 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *s, int64_t nsteps, void *hip_stream) {
         fuglbm_status rc = autotune_rows(s, st);
         if (rc != FUGLBM_OK) return rc;
     }
+    // (a stream that the caller captures cannot be timed)
+    if (left >= 2 && s->tuned && field_usable(s) && !s->tune.frows && !capturing(st)) {
+        fuglbm_status rc = autotune_field(s, st);
+        if (rc != FUGLBM_OK) return rc;
+    }
     if (fixed || (s->tuned && field_usable(s) && field_pays(s->tune, left))) {
         const int rows = fixed ? s->form_rows : s->tune.frows;
         const bool single = fixed ? s->form == FUGLBM_FORM_FIELDS_SINGLE : s->tune.single;
@@ -2000,9 +2024,37 @@ static int log2_class(int64_t v) {
     return k;
 }
 
+using BatchClass = std::tuple<int, int, int, int>;
+std::map<BatchClass, Tuned> &batch_tune_cache() {
+    static std::map<BatchClass, Tuned> m;
+    return m;
+}
+
+// Every member leaves the form to the library and has one.
+bool field_usable(const std::vector<fuglbm_sim *> &group) {
+    return std::all_of(group.begin(), group.end(), [](fuglbm_sim *s) { return field_usable(s); });
+}
+
+// Both fused variants are the tuner's to choose from.
+bool both_variants(const std::vector<fuglbm_sim *> &group, int nc, bool f32) {
+    return ws_usable(nc, f32) &&
+           std::all_of(group.begin(), group.end(), [](fuglbm_sim *s) { return s->auto_kernel; });
+}
+
+BatchClass batch_class(const std::vector<fuglbm_sim *> &group, int nc, bool f32) {
+    int64_t strip_rows = 0;
+    int ny_max = 1;
+    for (auto *s : group) {
+        strip_rows += (int64_t)((s->nx + FUSED_OUT - 1) / FUSED_OUT) * s->ny;
+        ny_max = std::max(ny_max, s->ny);
+    }
+    const int tag = (both_variants(group, nc, f32) ? 0 : group[0]->kernel) +
+                    (field_usable(group) ? 4 : 0);
+    return {nc, (f32 ? 1 : 0) + 2 * tag, log2_class(strip_rows), log2_class(ny_max)};
+}
+
 fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group, int nc, bool f32,
                          hipStream_t st) {
-    static std::map<std::tuple<int, int, int, int>, Tuned> cache;
     bt.tune = Tuned{};
     if (form_fixed(group[0])) {   // and with it every member (BatchKey)
         const bool single = group[0]->form == FUGLBM_FORM_FIELDS_SINGLE;
@@ -2019,29 +2071,17 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
     }
     for (auto *s : group)
         if (!s->autotune) return build_batch(bt, group, st);   // rows fixed by the caller
-    bool auto_k = true, field = true;
-    for (auto *s : group) {
-        auto_k = auto_k && s->auto_kernel;
-        field = field && field_usable(s);
-    }
-    const bool both = auto_k && ws_usable(nc, f32);
-    int64_t strip_rows = 0;
+    const bool both = both_variants(group, nc, f32);
     int ny_max = 1;
-    for (auto *s : group) {
-        strip_rows += (int64_t)((s->nx + FUSED_OUT - 1) / FUSED_OUT) * s->ny;
-        ny_max = std::max(ny_max, s->ny);
-    }
-    const int tag = (both ? 0 : group[0]->kernel) + (field ? 4 : 0);
-    const auto key = std::make_tuple(nc, (f32 ? 1 : 0) + 2 * tag, log2_class(strip_rows),
-                                     log2_class(ny_max));
-    auto hit = cache.find(key);
-    if (hit != cache.end()) {
+    for (auto *s : group) ny_max = std::max(ny_max, s->ny);
+    const auto key = batch_class(group, nc, f32);
+    auto hit = batch_tune_cache().find(key);
+    if (hit != batch_tune_cache().end()) {
         fuglbm_status rc = build_batch(bt, group, st, hit->second.rows, hit->second.kernel);
-        if (rc == FUGLBM_OK && hit->second.frows)
-            rc = build_field_batch(bt, group, hit->second.frows, st);
-        bt.frun.single = hit->second.single;
-        if (rc == FUGLBM_OK) bt.tune = hit->second;
-        return rc;
+        if (rc != FUGLBM_OK) return rc;
+        bt.tune = hit->second;
+        bt.tune.frows = 0;   // its tables are not built (tune_batch_field)
+        return FUGLBM_OK;
     }
     Tuned tn;
     float best_ms = 1e30f;
@@ -2062,9 +2102,20 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
         }
     }
     tn.fused_ms = best_ms / (2 * TUNE_LAUNCHES);
-    fuglbm_status rc = FUGLBM_OK;
-    if (field) {
-        rc = time_field(
+    fuglbm_status rc = build_batch(bt, group, st, tn.rows, tn.kernel);
+    if (rc != FUGLBM_OK) return rc;
+    batch_tune_cache()[key] = bt.tune = tn;
+    return FUGLBM_OK;
+}
+
+// The field form of a tuned group, timed (or answered from the cache) at its
+// first run of several steps; builds its tables.
+fuglbm_status tune_batch_field(BatchTable &bt, const std::vector<fuglbm_sim *> &group, int nc,
+                               bool f32, hipStream_t st) {
+    Tuned &c = batch_tune_cache()[batch_class(group, nc, f32)];
+    if (!c.frows) {
+        Tuned tn = bt.tune;
+        fuglbm_status rc = time_field(
             {group.begin(), group.end()}, st,
             [&](int r, FieldRun &q) {
                 fuglbm_status e = build_field_batch(bt, group, r, st);
@@ -2072,12 +2123,13 @@ fuglbm_status tune_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group,
                 return e;
             },
             tn);
-        if (rc == FUGLBM_OK) rc = build_field_batch(bt, group, tn.frows, st);
-        bt.frun.single = tn.single;
+        if (rc != FUGLBM_OK) return rc;
+        c = tn;
     }
-    if (rc == FUGLBM_OK) rc = build_batch(bt, group, st, tn.rows, tn.kernel);
+    fuglbm_status rc = build_field_batch(bt, group, c.frows, st);
     if (rc != FUGLBM_OK) return rc;
-    cache[key] = bt.tune = tn;
+    bt.frun.single = c.single;
+    bt.tune = c;
     return FUGLBM_OK;
 }
 
@@ -2407,6 +2459,15 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         if (!same) {
             bt.tune = Tuned{};
             fuglbm_status rc = tune_batch(bt, group, nc, f32, st);
+            if (rc != FUGLBM_OK) return rc;
+            flip = 0;
+        }
+        // at the parities that the table was built for: the trials read the
+        // current populations
+        if (nsteps >= 2 && !bt.tune.fixed && !bt.tune.frows && field_usable(group) &&
+            !capturing(st)) {
+            fuglbm_status rc = flip ? tune_batch(bt, group, nc, f32, st) : FUGLBM_OK;
+            if (rc == FUGLBM_OK) rc = tune_batch_field(bt, group, nc, f32, st);
             if (rc != FUGLBM_OK) return rc;
             flip = 0;
         }

@@ -559,6 +559,37 @@ static void cubes_routed_one_by_one() {
     CHECK(form_of(a) == FUGLBM_FORM_POPULATIONS && form_of(c) == FUGLBM_FORM_POPULATIONS);
 }
 
+static int field_launches() {
+    return took("field moments") + took("field eos") + took("field step") + took("field single") +
+           took("field last");
+}
+
+// Calls of single steps do not time a form that they cannot take; the first
+// longer run does, once per shape.
+static void single_steps_time_no_field_form() {
+    times(1.0, 0.2, 0.1);
+    Sim a(3, 64, 64), b(3, 64, 64), c(4, 70, 40), d(4, 50, 30);
+    for (int k = 0; k < 3; ++k) {
+        a.step(1);
+        step_many({&c, &d}, 1);
+    }
+    CHECK(field_launches() == 0);
+    a.step(8);
+    CHECK(form_of(a) >= FUGLBM_FORM_FIELDS);
+    const int first = field_launches();
+    b.step(1);
+    b.step(8);
+    CHECK(form_of(b) == form_of(a));
+    CHECK(field_launches() == 1 + 8 + 8 && first > 17);
+    step_many({&c, &d}, 8);
+    CHECK(form_of(c) == FUGLBM_FORM_FIELDS);
+    CHECK(field_launches() > 17);
+    step_many({&c, &d}, 8);
+    CHECK(field_launches() == 17);
+    step_many({&c, &d}, 1);
+    CHECK(form_of(c) == FUGLBM_FORM_POPULATIONS && field_launches() == 0);
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, std::function<void()>> all = {
         {"graph_in_flight", graph_in_flight},
@@ -567,6 +598,7 @@ int main(int argc, char **argv) {
         {"tiles_that_are_resident", tiles_that_are_resident},
         {"cube_forms_by_estimate", cube_forms_by_estimate},
         {"cubes_routed_one_by_one", cubes_routed_one_by_one},
+        {"single_steps_time_no_field_form", single_steps_time_no_field_form},
         {"form_reported_and_fixed", form_reported_and_fixed},
     };
     if (argc < 2) {
