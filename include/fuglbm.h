@@ -188,8 +188,9 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *sim, int64_t nsteps, void *hip_stream);
  * table (one launch per step); the others (D3Q19, and D2Q9 on the
  * multi-pass kernels) that share lattice, precision and tau == 1 or not
  * into one member table per group (each of the four multi-pass kernels
- * launched once per step for the whole group).  Results are bitwise those
- * of stepping each simulation alone.  Handles must be distinct.
+ * launched once per step for the whole group).  Members for which another
+ * form is faster (fuglbm_set_tuning) are taken out of their group where that
+ * pays.  Results are bitwise those of stepping each simulation alone.  Handles must be distinct.
  * Asynchronous on hip_stream.  Several groups may run beside each other on
  * streams of the library, which wait for hip_stream's earlier work and which
  * its later work waits for. */

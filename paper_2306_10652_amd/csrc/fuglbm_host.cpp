@@ -330,9 +330,11 @@ static bool form_fixed(const fuglbm_sim *s) { return s->form >= FUGLBM_FORM_FIEL
 // Whether a run of n steps is taken in field form.  Beside its steps it
 // reads the populations at its start and writes them at its end (about as
 // long); both forms give bitwise the same state.  One step never gains.
-static bool field_pays(const Tuned &t, int64_t n) {
+// step_ms: what every step costs beside it.
+static bool field_pays(const Tuned &t, int64_t n, double step_ms = 0.0) {
     if (t.fixed) return true;
-    return t.frows > 0 && n >= 2 && (double)n * (t.fused_ms - t.field_ms) > 2.0 * t.moments_ms;
+    return t.frows > 0 && n >= 2 &&
+           (double)n * (t.fused_ms - t.field_ms - step_ms) > 2.0 * t.moments_ms;
 }
 
 // All fields lie in the spare population buffer where they fit, components
@@ -1899,9 +1901,9 @@ void drop_batch_graphs(BatchTable &bt) {
     }
 }
 
-// By component count, precision and the form that the members' callers fixed
-// (AUTO where none did).
-using BatchKey = std::tuple<int, int, int>;
+// By component count, precision, the form that the members' callers fixed
+// (AUTO where none did), and 1 or 2 for the halves of a group that is split.
+using BatchKey = std::tuple<int, int, int, int>;
 std::map<BatchKey, BatchTable> &batch_tables() {
     static std::map<BatchKey, BatchTable> t;
     return t;
@@ -2253,6 +2255,51 @@ static void forget_sim_in_batches(const fuglbm_sim *s) {
 // ---- the groups of a batch ------------------------------------------------
 namespace {
 
+// A group of which some members have a field form and others do not (tau != 1,
+// fixed kernel or rows) is split where the field form saves its members this
+// much a step beside what it costs: the others then take a launch of their
+// own, which on a small grid is all latency (64^2 x 3 5.6 us, 400 2 x 6 7.4 us
+// a step).  In one table / split (us a step, one member at tau = 0.8): 512^2 x
+// 10 and 64^2 x 10 115 / 48, two 512^2 x 10 202 / 137, 128^2 ... 240^2 x 3 and
+// 160^2 37.8 / 29.2; left in one: two 200^2 x 5 27.2 (13.2 + 17.1), 64^2 x 3 as
+// 8 + 1 14.4 (10.3 + 5.8).
+constexpr double SPLIT_MS = 8e-3;
+
+// The group's table brought up to date, on st, for a run of nsteps (tables and
+// tuning); flip: the parity to step it at.
+fuglbm_status prepare_batch(BatchTable &bt, const std::vector<fuglbm_sim *> &group, int nc,
+                            bool f32, int64_t nsteps, hipStream_t st, int &flip) {
+    // the table (and its graph) is shared state: launches queued on
+    // another stream must finish before this call rebuilds or reuses it
+    if (bt.used && bt.last_stream != st) HIP_TRY(hipStreamSynchronize(bt.last_stream));
+    bt.last_stream = st;
+    bt.used = true;
+    bool same = bt.sims.size() == group.size();
+    for (size_t k = 0; same && k < group.size(); ++k)
+        same = bt.sims[k] == group[k] && bt.uids[k] == group[k]->uid;
+    flip = 0;
+    if (same) {
+        flip = group[0]->parity ^ bt.parity0[0];
+        for (size_t k = 0; k < group.size(); ++k)
+            if ((group[k]->parity ^ bt.parity0[k]) != flip) same = false;
+    }
+    if (!same) {
+        bt.tune = Tuned{};
+        fuglbm_status rc = tune_batch(bt, group, nc, f32, st);
+        if (rc != FUGLBM_OK) return rc;
+        flip = 0;
+    }
+    // at the parities that the table was built for: the trials read the
+    // current populations
+    if (nsteps >= 2 && !bt.tune.fixed && !bt.tune.frows && field_usable(group) && !capturing(st)) {
+        fuglbm_status rc = flip ? tune_batch(bt, group, nc, f32, st) : FUGLBM_OK;
+        if (rc == FUGLBM_OK) rc = tune_batch_field(bt, group, nc, f32, st);
+        if (rc != FUGLBM_OK) return rc;
+        flip = 0;
+    }
+    return FUGLBM_OK;
+}
+
 // nsteps steps of a group on the fused kernels (its table, at parity flip).
 fuglbm_status step_group(BatchTable &bt, const std::vector<fuglbm_sim *> &group, int nc, bool f32,
                          int flip, int64_t nsteps, hipStream_t st) {
@@ -2421,7 +2468,7 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
             continue;
         }
         if (s->lattice == FUGLBM_D2Q9 && is_fused(s->kernel))
-            groups[{s->N, s->fp32 ? 1 : 0, form_fixed(s) ? s->form : 0}].push_back(s);
+            groups[{s->N, s->fp32 ? 1 : 0, form_fixed(s) ? s->form : 0, 0}].push_back(s);
         else
             others.push_back(s);
     }
@@ -2437,48 +2484,47 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         groups.clear();
         others.clear();
     }
+    std::list<std::vector<fuglbm_sim *>> parts;   // what the tasks refer to
     for (auto &kv : groups) {
-        auto &group = kv.second;
-        BatchTable &bt = batch_tables()[kv.first];
-        // the table (and its graph) is shared state: launches queued on
-        // another stream must finish before this call rebuilds or reuses it
-        if (bt.used && bt.last_stream != st) HIP_TRY(hipStreamSynchronize(bt.last_stream));
-        bt.last_stream = st;
-        bt.used = true;
-        bool same = bt.sims.size() == group.size();
-        for (size_t k = 0; same && k < group.size(); ++k)
-            same = bt.sims[k] == group[k] && bt.uids[k] == group[k]->uid;
-        int flip = 0;
-        if (same) {
-            flip = group[0]->parity ^ bt.parity0[0];
-            for (size_t k = 0; k < group.size(); ++k)
-                if ((group[k]->parity ^ bt.parity0[k]) != flip) same = false;
-        }
-        const int nc = std::get<0>(kv.first);
+        const int nc = std::get<0>(kv.first), form = std::get<2>(kv.first);
         const bool f32 = std::get<1>(kv.first) != 0;
-        if (!same) {
-            bt.tune = Tuned{};
-            fuglbm_status rc = tune_batch(bt, group, nc, f32, st);
+        // a group stepped by one table; which: a split group has two more
+        struct Table {
+            BatchTable *bt;
+            int flip;
+        };
+        auto prepare = [&](std::vector<fuglbm_sim *> &group, int which, Table &q) {
+            q.bt = &batch_tables()[{nc, f32 ? 1 : 0, form, which}];
+            return prepare_batch(*q.bt, group, nc, f32, nsteps, st, q.flip);
+        };
+        auto task = [&](std::vector<fuglbm_sim *> &group, Table q) {
+            tasks.push_back({group_cost(group), [q, &group, nc, f32, nsteps](hipStream_t to) {
+                                 return step_group(*q.bt, group, nc, f32, q.flip, nsteps, to);
+                             }});
+        };
+        // members with a field form beside others without (tau != 1, fixed
+        // kernel or rows)
+        std::vector<fuglbm_sim *> &fields = parts.emplace_back(), &rest = parts.emplace_back();
+        for (auto *s : kv.second) (field_usable(s) ? fields : rest).push_back(s);
+        Table q{}, p{};
+        if (nsteps >= 2 && !fields.empty() && !rest.empty() && !capturing(st)) {
+            fuglbm_status rc = prepare(fields, 1, q);
             if (rc != FUGLBM_OK) return rc;
-            flip = 0;
+            if (field_pays(q.bt->tune, nsteps, SPLIT_MS)) {
+                rc = prepare(rest, 2, p);
+                if (rc != FUGLBM_OK) return rc;
+                task(fields, q);
+                task(rest, p);
+                continue;
+            }
         }
-        // at the parities that the table was built for: the trials read the
-        // current populations
-        if (nsteps >= 2 && !bt.tune.fixed && !bt.tune.frows && field_usable(group) &&
-            !capturing(st)) {
-            fuglbm_status rc = flip ? tune_batch(bt, group, nc, f32, st) : FUGLBM_OK;
-            if (rc == FUGLBM_OK) rc = tune_batch_field(bt, group, nc, f32, st);
-            if (rc != FUGLBM_OK) return rc;
-            flip = 0;
-        }
-        tasks.push_back({group_cost(group), [&bt, &group, nc, f32, flip, nsteps](hipStream_t to) {
-                             return step_group(bt, group, nc, f32, flip, nsteps, to);
-                         }});
+        fuglbm_status rc = prepare(kv.second, 0, q);
+        if (rc != FUGLBM_OK) return rc;
+        task(kv.second, q);
     }
     // multi-pass members by (lattice, precision, tau != 1): those that take the
     // field form do so one by one, the others share one table
     std::map<std::tuple<int, int, int>, std::vector<fuglbm_sim *>> ggroups;
-    std::list<std::vector<fuglbm_sim *>> parts;   // what the tasks refer to
     for (auto *s : others)
         ggroups[{s->lattice, s->fp32 ? 1 : 0, s->hc.omega != 1.0 ? 1 : 0}].push_back(s);
     for (auto &kv : ggroups) {

@@ -111,6 +111,39 @@ def test_batches_bitwise(form, precision):
         s.close()
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+def test_members_of_other_forms_in_a_batch_bitwise(precision):
+    """Groups that are split: planes at tau = 1 beside one at tau = 0.8 and one
+    with fixed rows, and a large cube beside a small one and one whose form is
+    fixed; every member ends where it ends alone."""
+    capi = _capi()
+
+    def sims():
+        out = [make(capi, plane(3, s, 31, "PR"), precision) for s in ((301, 240), (256, 256), (61, 400))]
+        wl = plane(3, (61, 23), 31, "PR")
+        wl.tau = 0.8
+        out.append(make(capi, wl, precision))
+        out.append(make(capi, plane(3, (67, 45), 31, "PR"), precision, 2, 2))
+        out += [make3(capi, cube(2, s, 21, "PR"), precision) for s in ((96, 96, 96), (8, 7, 9), (20, 11, 9))]
+        out[-2].set_tuning(1)
+        out[-1].set_form(FIELDS)
+        return out
+
+    ref, got = sims(), sims()
+    for n in (12, 1, 70):
+        for s in ref:
+            s.step_n(n)
+        capi.step_many(got, n)
+        for k, (a, b) in enumerate(zip(ref, got)):
+            assert np.array_equal(a.read_populations(), b.read_populations()), (n, k)
+        forms = [s.form() for s in got]
+        assert forms[3:5] == [POPULATIONS] * 2
+        assert forms[5:] == [FIELDS if n > 1 else POPULATIONS, POPULATIONS, FIELDS]
+    for s in ref + got:
+        assert s.diagnostics()["status"] == 0
+        s.close()
+
+
 @pytest.mark.parametrize("N,shape,lattice", [(3, (67, 45), 0), (6, (59, 24), 0), (2, (30, 17, 15), 1)])
 def test_captured_run_replayed(N, shape, lattice):
     """A run in field form on a stream that the caller captures: each replay,
