@@ -1059,24 +1059,31 @@ struct Lanes {
 };
 
 // ---- copies between device and caller memory ------------------------------
-// Pinned staging shared by the read-outs and checkpoints of the process: a
-// block as large as the small read-outs asked for, and a ring of slots that bulk
-// copies go through while a few threads move finished slots to (from) the
-// caller's pages, whose first touch is what a plain copy spends most of its
-// time on.  Held while any simulation exists; a call that finds it in use by
-// another thread copies without it.
+// Pinned staging shared by the read-outs of the process: a block as large as
+// the small read-outs asked for, and a ring of slots that bulk copies go through
+// while a few threads move finished slots to the caller's pages, whose first
+// touch is what a plain copy spends most of its time on.  (Copies to the device
+// take the plain way: 8.6 MB of populations 280 us, through the ring 322.)
+// Held while any simulation exists; a call that finds it in use by another
+// thread copies without it.
 constexpr size_t STAGE_SLOT = (size_t)4 << 20, STAGE_WORD = 256;
 constexpr int STAGE_SLOTS = 8, STAGE_THREADS = 6;
 // Parts up to this size are written to the block by a kernel: rho of 256^2 x 3
 // (1.6 MB) takes 106 us so and 115 us through the ring, of 200^2 x 10 (3.2 MB)
 // the ring.
 constexpr size_t STAGE_SMALL_PART = STAGE_SLOT / 2;
+// Bytes of bulk read-outs from which the ring is made.  Making it and giving it
+// back costs 45 us and more (0.9 MB of populations read once 61 us plain, 103
+// us with the ring; 2.6 MB 168 / 194; 4.9 MB 314 / 317; 14 MB 854 / 624), a
+// plain copy 27 us a MB more than one through a ring that is there.
+constexpr size_t STAGE_RING_FROM = STAGE_SLOT;
 
 struct Stage {
     std::mutex use;             // held by the call that copies through it
     char *block = nullptr;      // STAGE_WORD bytes for a status word, then data; pinned
     size_t block_bytes = 0;
     bool asked = false;         // a small read-out has done without the block
+    size_t plain = 0;           // bytes of bulk read-outs that did without the ring
     char *ring = nullptr;       // STAGE_SLOTS * STAGE_SLOT, pinned
     hipEvent_t ev[STAGE_SLOTS] = {};
     std::mutex life;
@@ -1102,9 +1109,11 @@ struct Stage {
         block_bytes = block ? want : 0;
         return block != nullptr;
     }
-    // with `use` held
-    bool ready() {
+    // with `use` held: the ring, where a read-out of `bytes` shall go through it
+    bool ring_for(size_t bytes) {
         if (ring) return true;
+        plain += bytes;
+        if (plain < STAGE_RING_FROM) return false;
         for (hipEvent_t &e : ev)
             if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
                 e = nullptr;
@@ -1126,7 +1135,7 @@ struct Stage {
         if (block) (void)hipHostFree(block);
         if (ring) (void)hipHostFree(ring);
         block = ring = nullptr;
-        block_bytes = 0;
+        block_bytes = plain = 0;
         asked = false;
         for (hipEvent_t &e : ev) {
             if (e) (void)hipEventDestroy(e);
@@ -1144,33 +1153,19 @@ Stage &device_stage() {
     return all[dev & 63];
 }
 
-// Moves `bytes` between the device (dev) and the caller (host) on st, to the
-// caller if `out`; done when it returns.  Slots are handed to the threads in
-// order; none waits for anything but its own slot's turn, and all leave when
-// the last slot is taken or a copy fails.
-hipError_t staged_copy(Stage &g, char *host, char *dev, size_t bytes, bool out, hipStream_t st) {
+// Copies `bytes` from the device (dev) to the caller (host) through the ring, on
+// st; done when it returns.  Slots are handed to the threads in order; none
+// waits for anything but its own slot's turn, and all leave when the last slot
+// is taken or a copy fails.
+hipError_t staged_copy(Stage &g, char *host, const char *dev, size_t bytes, hipStream_t st) {
     const int64_t n = (int64_t)((bytes + STAGE_SLOT - 1) / STAGE_SLOT);
     auto size = [&](int64_t k) { return std::min(STAGE_SLOT, bytes - (size_t)k * STAGE_SLOT); };
-    auto host_at = [&](int64_t k) { return host + (size_t)k * STAGE_SLOT; };
-    auto dev_at = [&](int64_t k) { return dev + (size_t)k * STAGE_SLOT; };
     auto dma = [&](int64_t k) {
-        return out ? hipMemcpyAsync(g.slot(k), dev_at(k), size(k), hipMemcpyDeviceToHost, st)
-                   : hipMemcpyAsync(dev_at(k), g.slot(k), size(k), hipMemcpyHostToDevice, st);
+        return hipMemcpyAsync(g.slot(k), dev + (size_t)k * STAGE_SLOT, size(k),
+                              hipMemcpyDeviceToHost, st);
     };
-    auto move = [&](int64_t k) {
-        if (out)
-            std::memcpy(host_at(k), g.slot(k), size(k));
-        else
-            std::memcpy(g.slot(k), host_at(k), size(k));
-    };
+    auto move = [&](int64_t k) { std::memcpy(host + (size_t)k * STAGE_SLOT, g.slot(k), size(k)); };
     hipError_t err = hipSuccess;
-    if (n <= 1) {
-        if (!out) move(0);
-        err = dma(0);
-        if (err == hipSuccess) err = hipStreamSynchronize(st);
-        if (out && err == hipSuccess) move(0);
-        return err;
-    }
     // a thread may take slot k once `open` > k; `moved` of the ring position
     // counts the slots that it has finished there
     std::atomic<int64_t> open{0}, next{0};
@@ -1191,53 +1186,38 @@ hipError_t staged_copy(Stage &g, char *host, char *dev, size_t bytes, bool out, 
     };
     std::thread th[STAGE_THREADS];
     int nth = 0;
-    try {
-        for (; nth < STAGE_THREADS && nth < n; ++nth) th[nth] = std::thread(work);
-    } catch (...) {
+    if (n > 1) {
+        try {
+            for (; nth < STAGE_THREADS && nth < n; ++nth) th[nth] = std::thread(work);
+        } catch (...) {
+        }
     }
-    if (nth == 0) {                        // no thread to be had
+    if (nth == 0) {                        // one slot, or no thread to be had
         for (int64_t k = 0; k < n && err == hipSuccess; ++k) {
-            if (!out) move(k);
             err = dma(k);
             if (err == hipSuccess) err = hipStreamSynchronize(st);
-            if (out && err == hipSuccess) move(k);
+            if (err == hipSuccess) move(k);
         }
         return err;
     }
     auto finished = [&](int64_t k) {       // slot k's move is done
         return moved[k % STAGE_SLOTS].load(std::memory_order_acquire) > k / STAGE_SLOTS;
     };
-    if (out) {
-        int64_t issued = 0, landed = 0;
-        while (landed < n && err == hipSuccess) {
-            while (issued < n && issued < landed + STAGE_SLOTS && err == hipSuccess &&
-                   (issued < STAGE_SLOTS || finished(issued - STAGE_SLOTS))) {
-                err = dma(issued);
-                if (err == hipSuccess) err = hipEventRecord(g.ev[issued % STAGE_SLOTS], st);
-                ++issued;
-            }
-            if (err == hipSuccess && landed < issued) {
-                err = hipEventSynchronize(g.ev[landed % STAGE_SLOTS]);
-                ++landed;
-                if (err == hipSuccess) open.store(landed, std::memory_order_release);
-            } else {
-                std::this_thread::yield();
-            }
+    int64_t issued = 0, landed = 0;
+    while (landed < n && err == hipSuccess) {
+        while (issued < n && issued < landed + STAGE_SLOTS && err == hipSuccess &&
+               (issued < STAGE_SLOTS || finished(issued - STAGE_SLOTS))) {
+            err = dma(issued);
+            if (err == hipSuccess) err = hipEventRecord(g.ev[issued % STAGE_SLOTS], st);
+            ++issued;
         }
-    } else {
-        open.store(std::min<int64_t>(n, STAGE_SLOTS));
-        for (int64_t k = 0; k < n && err == hipSuccess; ++k) {
-            while (!finished(k)) std::this_thread::yield();
-            err = dma(k);
-            if (err == hipSuccess) err = hipEventRecord(g.ev[k % STAGE_SLOTS], st);
-            // the slot of the copy issued half a ring ago may be filled again
-            const int64_t old = k - STAGE_SLOTS / 2;
-            if (old >= 0 && err == hipSuccess) {
-                err = hipEventSynchronize(g.ev[old % STAGE_SLOTS]);
-                open.store(std::min<int64_t>(n, old + 1 + STAGE_SLOTS), std::memory_order_release);
-            }
+        if (err == hipSuccess && landed < issued) {
+            err = hipEventSynchronize(g.ev[landed % STAGE_SLOTS]);
+            ++landed;
+            if (err == hipSuccess) open.store(landed, std::memory_order_release);
+        } else {
+            std::this_thread::yield();
         }
-        if (err == hipSuccess) err = hipStreamSynchronize(st);
     }
     if (err != hipSuccess) stop.store(true);
     for (int k = 0; k < nth; ++k) th[k].join();
@@ -1269,7 +1249,8 @@ fuglbm_status read_parts(fuglbm_sim *s, std::initializer_list<Part> parts) {
     // first
     bool plain = !lk.owns_lock();
     if (!plain && !g.block && nl == 0 && !g.asked) plain = g.asked = true;
-    if (plain || !g.block_for(few[0].bytes + few[1].bytes) || (nl > 0 && !g.ready())) {
+    if (plain || !g.block_for(few[0].bytes + few[1].bytes) ||
+        (nl > 0 && !g.ring_for(large[0].bytes + large[1].bytes))) {
         HIP_TRY(hipStreamSynchronize(st));
         for (const Part &p : parts)
             if (p.host) HIP_TRY(hipMemcpy(p.host, p.dev, p.bytes, hipMemcpyDeviceToHost));
@@ -1282,7 +1263,7 @@ fuglbm_status read_parts(fuglbm_sim *s, std::initializer_list<Part> parts) {
     if (n == 0 && nl > 0)
         HIP_TRY(hipMemcpyAsync(g.word(), s->status, sizeof(word), hipMemcpyDeviceToHost, st));
     for (int k = 0; k < nl; ++k)
-        HIP_TRY(staged_copy(g, (char *)large[k].host, (char *)large[k].dev, large[k].bytes, true,
+        HIP_TRY(staged_copy(g, (char *)large[k].host, (const char *)large[k].dev, large[k].bytes,
                             st));
     if (n > 0 || nl == 0)
         HIP_TRY(launch_to_host((const double *)few[0].dev, (int64_t)(few[0].bytes / 8),
@@ -1761,23 +1742,61 @@ static fuglbm_status for_planes(const fuglbm_sim *s, Fn fn) {
     }
     return FUGLBM_OK;
 }
+
+// Up to this many bytes of populations the host orders them: a launch and a
+// wait take as long (0.22 MB 22 us to read and 21 to write, ordered by the
+// device 31 and 31; 0.88 MB 66 and 57, 58 and 55).
+constexpr int64_t HOST_ORDER = 512 << 10;
+static bool host_orders(const fuglbm_sim *s) { return (int64_t)s->N * s->Q * s->ns * 8 <= HOST_ORDER; }
+
+// Host copy `buf` of a population buffer -> g (OUT) or back.
+template <typename ST, bool OUT, class G>
+static void order_pops(const fuglbm_sim *s, char *buf, G *g) {
+    const int64_t rows = (int64_t)s->ny * s->nz;
+    const PopLayout<ST> P(s->N, s->Q, s->nx, rows);
+    for (int i = 0; i < s->N; ++i)
+        for (int a = 0; a < s->Q; ++a)
+            for (int64_t r = 0; r < rows; ++r) {
+                G *o = g + ((size_t)i * s->Q + a) * s->ns + (size_t)r * s->nx;
+                double *rest = (double *)(buf + P.rest(r, i, 0));
+                ST *move = a ? (ST *)(buf + P.move(r, i, a, 0)) : nullptr;
+                for (int x = 0; x < s->nx; ++x) {
+                    if constexpr (OUT)
+                        o[x] = a ? (double)move[host_pop_col(s, a, x)] : rest[x];
+                    else if (a)
+                        move[host_pop_col(s, a, x)] = (ST)o[x];
+                    else
+                        rest[x] = o[x];
+                }
+            }
+}
 }  // extern "C++"
 
 fuglbm_status fuglbm_read_populations(fuglbm_sim *s, double *g_out) {
     if (!s || !g_out) return fail(FUGLBM_EINVAL, "null argument");
     hipStream_t st = s->last_stream;
+    if (host_orders(s)) {
+        std::unique_ptr<char[]> tmp(new (std::nothrow) char[(size_t)pop_bytes(s)]);
+        if (!tmp) return fail(FUGLBM_ENOMEM, "host allocation");
+        HIP_TRY(hipStreamSynchronize(st));
+        HIP_TRY(hipMemcpy(tmp.get(), s->buf[s->parity], (size_t)pop_bytes(s),
+                          hipMemcpyDeviceToHost));
+        s->fp32 ? order_pops<float, true>(s, tmp.get(), g_out)
+                : order_pops<double, true>(s, tmp.get(), g_out);
+        return FUGLBM_OK;
+    }
     // the spare buffer is what the next step overwrites
     char *scratch = (char *)s->buf[s->parity ^ 1];
     Stage &g = *s->stage;
     std::unique_lock<std::mutex> lk(g.use, std::try_to_lock);
-    const bool staged = lk.owns_lock() && g.ready();
+    const bool staged = lk.owns_lock() && g.ring_for((size_t)s->N * s->Q * s->ns * 8);
     return for_planes(s, [&](int p, int n) -> fuglbm_status {
         char *host = (char *)(g_out + (size_t)p * s->ns);
         const size_t bytes = (size_t)n * s->ns * 8;
         HIP_TRY(launch_planes(s->lattice, s->fp32, true, s->N, s->nx, s->ny, s->nz, p, n,
                               s->buf[s->parity], scratch, st));
         if (staged) {
-            HIP_TRY(staged_copy(g, host, scratch, bytes, true, st));
+            HIP_TRY(staged_copy(g, host, scratch, bytes, st));
         } else {
             HIP_TRY(hipStreamSynchronize(st));
             HIP_TRY(hipMemcpy(host, scratch, bytes, hipMemcpyDeviceToHost));
@@ -1790,25 +1809,26 @@ fuglbm_status fuglbm_write_populations(fuglbm_sim *s, const double *g_in, int64_
     if (!s || !g_in) return fail(FUGLBM_EINVAL, "null argument");
     if (step < 0) return fail(FUGLBM_EINVAL, "step must be >= 0");
     hipStream_t st = s->last_stream;
-    char *scratch = (char *)s->buf[1];
-    Stage &g = *s->stage;
-    std::unique_lock<std::mutex> lk(g.use, std::try_to_lock);
-    const bool staged = lk.owns_lock() && g.ready();
     HIP_TRY(hipStreamSynchronize(st));
-    fuglbm_status rc = for_planes(s, [&](int p, int n) -> fuglbm_status {
-        char *host = (char *)(g_in + (size_t)p * s->ns);
-        const size_t bytes = (size_t)n * s->ns * 8;
-        if (staged) {
-            HIP_TRY(staged_copy(g, host, scratch, bytes, false, st));
-        } else {
-            HIP_TRY(hipMemcpy(scratch, host, bytes, hipMemcpyHostToDevice));
-        }
-        HIP_TRY(launch_planes(s->lattice, s->fp32, false, s->N, s->nx, s->ny, s->nz, p, n,
-                              s->buf[0], scratch, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        return FUGLBM_OK;
-    });
-    if (rc != FUGLBM_OK) return rc;
+    if (host_orders(s)) {
+        // (zeros in what the layout pads)
+        std::unique_ptr<char[]> tmp(new (std::nothrow) char[(size_t)pop_bytes(s)]());
+        if (!tmp) return fail(FUGLBM_ENOMEM, "host allocation");
+        s->fp32 ? order_pops<float, false>(s, tmp.get(), g_in)
+                : order_pops<double, false>(s, tmp.get(), g_in);
+        HIP_TRY(hipMemcpy(s->buf[0], tmp.get(), (size_t)pop_bytes(s), hipMemcpyHostToDevice));
+    } else {
+        char *scratch = (char *)s->buf[1];
+        fuglbm_status rc = for_planes(s, [&](int p, int n) -> fuglbm_status {
+            HIP_TRY(hipMemcpy(scratch, g_in + (size_t)p * s->ns, (size_t)n * s->ns * 8,
+                              hipMemcpyHostToDevice));
+            HIP_TRY(launch_planes(s->lattice, s->fp32, false, s->N, s->nx, s->ny, s->nz, p, n,
+                                  s->buf[0], scratch, st));
+            HIP_TRY(hipStreamSynchronize(st));
+            return FUGLBM_OK;
+        });
+        if (rc != FUGLBM_OK) return rc;
+    }
     s->parity = 0;
     s->step = step;
     s->have_snap = false;

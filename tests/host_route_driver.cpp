@@ -34,7 +34,7 @@ static void fault(const std::string &what) {
 static double now_ms = 0.0;                  // the device's clock
 static std::map<std::string, int> launched;  // by kernel
 static std::map<std::string, double> cost;   // ms of a launch, by kernel
-static int captures = 0, pinned_bytes_most = 0, pinned_calls = 0;
+static int captures = 0, pinned_calls = 0;
 static size_t pinned_bytes = 0;
 static int lane_launches = 0;                // launches on streams of the library
 static hipStream_t user_stream = nullptr;
@@ -618,6 +618,54 @@ static void planes_routed_by_form() {
     CHECK(form_of(e) == FUGLBM_FORM_FIELDS);
 }
 
+// Read-outs and checkpoints of a simulation's whole life: what is small, or
+// read once, or written, makes no pinned ring; what is large or read again does.
+static void staging_made_where_it_pays() {
+    for (auto prec : {FUGLBM_FP64, FUGLBM_FP32_STORAGE})
+        for (int nz : {0, 5}) {      // the host orders these: there and back
+            Sim s(2, 13, 7, nz, 1.0, prec);
+            const int Q = nz ? 19 : 9;
+            std::vector<double> g((size_t)2 * Q * 13 * 7 * (nz ? nz : 1)), h(g.size());
+            for (size_t k = 0; k < g.size(); ++k) g[k] = 1.0 / (double)(k + 3);
+            launched.clear();
+            CHECK(fuglbm_write_populations(s.s, g.data(), 0) == FUGLBM_OK);
+            CHECK(fuglbm_read_populations(s.s, h.data()) == FUGLBM_OK);
+            CHECK(launched.empty());
+            const size_t plane = g.size() / (2 * Q);
+            bool equal = true;
+            for (size_t k = 0; k < g.size(); ++k)
+                equal = equal && h[k] == (prec == FUGLBM_FP64 || k / plane % Q == 0
+                                              ? g[k] : (double)(float)g[k]);
+            CHECK(equal);
+        }
+    CHECK(pinned_calls == 0);
+    for (int k = 0; k < 3; ++k) {    // 0.9 MB, once each in a life
+        Sim s(3, 64, 64);
+        std::vector<double> g((size_t)27 * 4096, 0.01);
+        CHECK(fuglbm_write_populations(s.s, g.data(), 0) == FUGLBM_OK);
+        CHECK(fuglbm_read_populations(s.s, g.data()) == FUGLBM_OK);
+    }
+    CHECK(pinned_calls == 0);
+    {
+        Sim s(3, 256, 256);          // 14 MB written, then read
+        std::vector<double> g((size_t)27 * 65536, 0.01);
+        CHECK(fuglbm_write_populations(s.s, g.data(), 0) == FUGLBM_OK);
+        CHECK(pinned_calls == 0);
+        CHECK(fuglbm_read_populations(s.s, g.data()) == FUGLBM_OK);
+        CHECK(pinned_calls == 1 && pinned_bytes == (size_t)32 << 20);
+        CHECK(fuglbm_read_populations(s.s, g.data()) == FUGLBM_OK);
+        CHECK(pinned_calls == 1);
+    }
+    {
+        Sim s(3, 90, 90);            // 1.7 MB: from the third time on
+        std::vector<double> g((size_t)27 * 8100);
+        for (int k = 0; k < 2; ++k) CHECK(fuglbm_read_populations(s.s, g.data()) == FUGLBM_OK);
+        CHECK(pinned_calls == 1);
+        for (int k = 0; k < 2; ++k) CHECK(fuglbm_read_populations(s.s, g.data()) == FUGLBM_OK);
+        CHECK(pinned_calls == 2);
+    }
+}
+
 int main(int argc, char **argv) {
     const std::map<std::string, std::function<void()>> all = {
         {"graph_in_flight", graph_in_flight},
@@ -628,6 +676,7 @@ int main(int argc, char **argv) {
         {"cubes_routed_one_by_one", cubes_routed_one_by_one},
         {"single_steps_time_no_field_form", single_steps_time_no_field_form},
         {"planes_routed_by_form", planes_routed_by_form},
+        {"staging_made_where_it_pays", staging_made_where_it_pays},
         {"form_reported_and_fixed", form_reported_and_fixed},
     };
     if (argc < 2) {

@@ -14,7 +14,8 @@ HIPCC = "/opt/rocm/bin/hipcc"
 SCENARIOS = ["graph_in_flight", "tuning_between_batches", "no_steps_first",
              "form_reported_and_fixed", "tiles_that_are_resident",
              "cube_forms_by_estimate", "cubes_routed_one_by_one",
-             "single_steps_time_no_field_form", "planes_routed_by_form"]
+             "single_steps_time_no_field_form", "planes_routed_by_form",
+             "staging_made_where_it_pays"]
 
 
 @pytest.fixture(scope="module")
