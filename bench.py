@@ -31,6 +31,13 @@ PMC_SUMMARY = os.path.join(ROOT, "profiles", "fused_d2q9_spinodal10_1024_pmc.jso
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2306_10652_amd", "csrc", f)
                for f in ("lbm_common.h", "fused_common.h", "kernels_fused2d.hip",
                          "kernels_fused2d_ws.hip")]
+FIELD_PMC = os.path.join(ROOT, "profiles", "field_d2q9_spinodal10_1024_pmc.json")
+FIELD_SRCS = [os.path.join(ROOT, "paper_2306_10652_amd", "csrc", f)
+              for f in ("lbm_common.h", "fused_common.h", "fields2d.h")]
+# kernels of a run in field form, ST the storage type: read of the populations,
+# EOS, step, and the step that writes the populations
+FIELD_KERNELS = dict(moments="k_field_moments<%s>", eos="k_field_eos<10>",
+                     step="k_field_step<10,%s,false>", last="k_field_step<10,%s,true>")
 KERNEL_NAMES = {2: "k_fused_d2q9<10,%s>", 3: "k_fused_d2q9_ws<10,%s>"}
 
 
@@ -48,11 +55,12 @@ def step_kernel(kernel, form, st):
     return kernel_name(kernel, st)
 
 
-def kernel_hash():
-    """Hash of the fused kernels' sources (the profile summary records the
-    hash it was measured with; a changed kernel voids its traffic figure)."""
+def kernel_hash(srcs=None):
+    """Hash of the kernels' sources, the fused kernels' by default (a profile
+    summary records the hash it was measured with; a changed kernel voids its
+    traffic figure)."""
     h = hashlib.sha256()
-    for p in KERNEL_SRCS:
+    for p in srcs or KERNEL_SRCS:
         with open(p, "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -570,6 +578,20 @@ def pmc_traffic(launch_alg_bytes):
     return pm.get("hbm_bytes_per_launch")
 
 
+def field_traffic(precision, run):
+    """HBM bytes a step of a run of `run` steps in field form, from the counter
+    summary of its kernels: every step has an EOS kernel, all but the last a step
+    kernel, and the run reads the populations once and writes them once."""
+    if not os.path.exists(FIELD_PMC):
+        return None
+    with open(FIELD_PMC) as f:
+        pm = json.load(f)
+    if pm.get("kernel_sha256_16") != kernel_hash(FIELD_SRCS):
+        return None
+    b = {k: v["hbm_bytes_per_launch"] for k, v in pm["per_precision"][precision].items()}
+    return b["eos"] + (b["step"] * (run - 1) + b["moments"] + b["last"]) / run
+
+
 def trace_summary(db_path, steps, steady=0):
     """Per-kernel durations from a rocprofv3 results database (kernel-trace
     run of this script): every dispatch, and the timed window of each
@@ -685,6 +707,38 @@ def pmc_summary(out_path, fetch64, write64, fetch32, write32, calib_fetch, calib
     print(json.dumps(out, indent=1))
 
 
+def pmc_field_summary(out_path, fetch64, write64, fetch32, write32, calib_fetch, calib_write,
+                      steps, copy_bytes=1 << 30):
+    """The same for the kernels of a run in field form (counter runs of
+    `--precision P --steps S`, S < 64: plain launches): means over the timed
+    run's dispatches, the last S of the EOS kernel, S - 1 of the step kernel and
+    one each of the kernels at its ends."""
+    def copy_kib(path, counter):
+        return max(v for n, v in _counter_values(path, counter) if "copyBuffer" in n)
+    f_fac = copy_bytes / (copy_kib(calib_fetch, "FETCH_SIZE") * 1024.0)
+    w_fac = copy_bytes / (copy_kib(calib_write, "WRITE_SIZE") * 1024.0)
+    many = dict(eos=steps, step=steps - 1, moments=1, last=1)
+    per = {}
+    for prec, fpath, wpath, st in (("fp64", fetch64, write64, "double"),
+                                   ("fp32", fetch32, write32, "float")):
+        per[prec] = {}
+        for k, name in FIELD_KERNELS.items():
+            name = name % st if "%" in name else name
+
+            def mean(path, counter):
+                v = [v for n, v in _counter_values(path, counter) if name in n.replace(" ", "")]
+                return float(np.mean(v[-many[k]:])) * 1024.0
+            rd, wr = mean(fpath, "FETCH_SIZE") * f_fac, mean(wpath, "WRITE_SIZE") * w_fac
+            per[prec][k] = dict(kernel=name, dispatches=many[k], hbm_read_bytes_per_launch=rd,
+                                hbm_write_bytes_per_launch=wr, hbm_bytes_per_launch=rd + wr)
+    out = dict(kernel_sha256_16=kernel_hash(FIELD_SRCS), workload=WORKLOAD,
+               calibration=dict(copy_bytes=copy_bytes, fetch_factor=f_fac, write_factor=w_fac),
+               per_precision=per)
+    with open(out_path, "w") as f:
+        json.dump(out, f, indent=1)
+    print(json.dumps(out, indent=1))
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -732,7 +786,15 @@ def main():
                     help="only write the HBM traffic summary OUT from rocprofv3 counter "
                          "databases (FETCH_SIZE / WRITE_SIZE runs of --precision fp64 and fp32, "
                          "and of --calib-copy-mib 1024); the last --steps dispatches are used")
+    ap.add_argument("--pmc-field-summary", nargs=7, default=None,
+                    metavar=("OUT", "FETCH64", "WRITE64", "FETCH32", "WRITE32", "CALIB_FETCH",
+                             "CALIB_WRITE"),
+                    help="the same of the kernels of a run in field form (runs without --rows, "
+                         "--steps below 64)")
     args = ap.parse_args()
+    if args.pmc_field_summary:
+        pmc_field_summary(*args.pmc_field_summary, steps=args.steps)
+        return
     if args.pmc_summary:
         pmc_summary(*args.pmc_summary, steps=args.steps)
         return
@@ -776,8 +838,9 @@ def main():
     copy_gbs = copy_rate()
     for r in (r64, r32):
         field_form(r, args.steps)
-    # the counter summary is of the fused kernel
-    traffic = None if "population_bytes" in r64 else pmc_traffic(r64["alg_bytes"])
+    # from the counter summary of the kernels that ran
+    traffic = (field_traffic("fp64", min(args.steps, 100)) if "population_bytes" in r64 else
+               pmc_traffic(r64["alg_bytes"]))
     roof = dict(bound="hbm", achieved=round(r64["achieved_gbs"], 1), peak=HBM_PEAK_GBS,
                 unit="GB/s", frac=round(r64["achieved_gbs"] / HBM_PEAK_GBS, 4),
                 traffic=traffic, alg_bytes_per_launch=r64["alg_bytes"],
