@@ -18,8 +18,8 @@
 // bitwise the same state.
 //
 // Measured on 128^3, N = 10 (us a step, multi-pass before): FP64 1875 ->
-// 956 (velocity 125, k_stream3 725, k_eos3 106), FP32 storage 1211 -> 889
-// (128, 655, 106); 75 64 50, N = 9: 256 -> 130 and 153 -> 122.  What bounds
+// 956 ... 983 (velocity 125, k_stream3 730, k_eos3 106), FP32 storage 1211 ->
+// 889 ... 906 (128, 654, 106); 75 64 50, N = 9: 256 -> 127 and 153 -> 122.  What bounds
 // k_stream3 is VALU work (64 % busy with 2 to 3 wavefronts a SIMD, 2.7 GB at
 // 3.6 TB/s): 430 to 490 instructions a plane of a wavefront, of which the
 // rims of its tiles waste a quarter to a third.  The rim planes, which only

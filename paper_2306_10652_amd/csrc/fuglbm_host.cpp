@@ -338,8 +338,10 @@ static bool field_pays(const Tuned &t, int64_t n, double step_ms = 0.0) {
 }
 
 // All fields lie in the spare population buffer where they fit, components
-// a padded stride apart (see PopLayout<float>::pad for the gap); else (one
-// component, tiny grids) set 0 and psi use the workspace.
+// a padded stride apart (see PopLayout<float>::pad for the gap): they take 3 N +
+// 7 values of a site, the buffer has room for 9 N in FP64 (from two components
+// on) and 5 N in FP32 storage (from four on), less the gaps on small grids.
+// Else set 0 and psi use the workspace.
 static FieldSim field_sim(const fuglbm_sim *s) {
     FieldSim f{};
     f.c = s->dc;
@@ -799,10 +801,9 @@ std::map<std::tuple<int, int, int, int>, Tuned> &tune_cache() {
 
 // Rows per item of the field form whose rounds over the resident workgroups
 // cost least (a workgroup takes rows + 6 lead rows, a single wavefront
-// rows + 4), with the items of each
-// simulation counted as they are cut: 1024^2, N = 10 on 256 slots takes 74
-// rows (252 items in one round, us a step), where strip rows in total would
-// give 72 (270 items, two rounds).
+// rows + 4), with the items of each simulation counted as they are cut:
+// 1024^2, N = 10 on 256 slots takes 74 rows (252 items, one round, 121 us a
+// step), where strip rows in total would give 72 (270 items, two rounds, 130).
 int field_model_rows(const std::vector<const fuglbm_sim *> &sims, bool single) {
     int ny = 1;
     for (auto *s : sims) ny = std::max(ny, s->ny);

@@ -19,6 +19,8 @@
 //   -- 4 --
 //      (components)  u, collision, push
 //
+// (Two rows of nine and ten components in FP64 spill 2 and 4 of 128 registers.)
+//
 // One wavefront per component, lane = column of a 60-column strip, and one
 // helper wavefront per row that needs the EOS.  Terms, orders of summation
 // and work-item tables are those of the marching kernels: bitwise the same
