@@ -270,7 +270,9 @@ struct fuglbm_sim {
     Shape3 shape3;
     hipGraphExec_t fgraph[2];   // field form, by the parity it was captured at
     Stage *stage;          // pinned staging of its device
-    uint64_t uid;          // never reused; batch tables key on it, not on the address
+    // never reused, and renewed when a caller sets the tuning or the form: batch
+    // tables key on it, not on the address
+    uint64_t uid;
 };
 
 // Work about to be enqueued on st waits (on the device) for the
@@ -408,11 +410,8 @@ static GenMember field3_member(const fuglbm_sim *s, int parity, int set) {
     return g;
 }
 
-// The simulation left out of every cached batch table (its work has ended).
-static void forget_sim_in_batches(const fuglbm_sim *s);
-
 static uint64_t next_sim_uid() {
-    static uint64_t n = 0;
+    static std::atomic<uint64_t> n{0};
     return ++n;
 }
 
@@ -652,25 +651,36 @@ Step3 step3_estimate(fuglbm_sim *s) {
     return e;
 }
 
+// A run of n steps whose form the library chooses (from three steps on).
+bool field3_open(fuglbm_sim *s, int64_t n) {
+    return n >= 3 && s->form == FUGLBM_FORM_AUTO && field3_fits(s) &&
+           field3_shape(s).cost < Shape3::NONE;
+}
+
+// A simulation on its own takes a run of n steps in field form.
+bool field3_alone(fuglbm_sim *s, int64_t n) {
+    if (!field3_open(s, n)) return form_fixed(s) && field3_fits(s);
+    const Step3 c = step3_estimate(s);
+    return c.fields < c.passes;
+}
+
 // Members of a D3Q19 group that take a run of n steps in field form, the
-// others in `rest`: those whose caller fixed it, and, from three steps on,
-// those whose step is faster so than what it adds to the passes that the group
-// shares; or all, where that is faster than shared passes for the few that are
-// left.  What a member adds is its volume, in the passes of a batch
-// (`batched`), where every block looks its member up, 1.3 times of it: three
+// others in `rest`: those whose caller fixed it, and those whose step is faster
+// so than what it adds to the passes that the group shares; or all, where that
+// is faster than shared passes for the few that are left.  What a member adds
+// is 1.3 times its volume, as every block of a batch looks its member up: three
 // 64^3 x 4 take 267 us a step so (FP64; 273 by this) and 212 in field form,
 // four 40^3 x 3 90 us (88) and 153, 128^3 x 10 with 20 11 9 x 10 2090 and 975.
-void split_forms3(const std::vector<fuglbm_sim *> &group, int64_t n, bool batched,
+void split_forms3(const std::vector<fuglbm_sim *> &group, int64_t n,
                   std::vector<fuglbm_sim *> &fields, std::vector<fuglbm_sim *> &rest) {
     double shared = 0.0, apart = 0.0, latency = 0.0;
     bool all = true;   // every one in `rest` may take the field form
     for (auto *s : group) {
-        const bool fits = field3_fits(s) && field3_shape(s).cost < Shape3::NONE;
-        const bool open = fits && n >= 3 && s->form == FUGLBM_FORM_AUTO;
+        const bool open = field3_open(s, n);
         const double lat = step3_latency(s->N);
         const Step3 c = open ? step3_estimate(s) : Step3{};
-        const double adds = (batched ? 1.3 : 1.0) * (c.passes - lat);
-        if ((fits && form_fixed(s)) || (open && c.fields < adds)) {
+        const double adds = 1.3 * (c.passes - lat);
+        if ((form_fixed(s) && field3_fits(s)) || (open && c.fields < adds)) {
             fields.push_back(s);
             continue;
         }
@@ -1546,7 +1556,7 @@ fuglbm_status fuglbm_set_tuning(fuglbm_sim *s, int32_t kernel, int32_t rows) {
         s->tuned = false;
     }
     HIP_TRY(hipStreamSynchronize(s->last_stream));
-    forget_sim_in_batches(s);   // their tables hold what was chosen before
+    s->uid = next_sim_uid();   // batch tables hold what was chosen before
     s->kernel = k;
     s->form = kernel ? FUGLBM_FORM_POPULATIONS : FUGLBM_FORM_AUTO;
     if (r != s->rows) {
@@ -1569,7 +1579,7 @@ fuglbm_status fuglbm_set_form(fuglbm_sim *s, int32_t form) {
     if (single && s->N > field_single_comp())
         return fail(FUGLBM_EINVAL, "steps by single wavefronts are built for at most 3 components");
     HIP_TRY(hipStreamSynchronize(s->last_stream));
-    forget_sim_in_batches(s);
+    s->uid = next_sim_uid();
     drop_graphs(s);
     s->form = form;
     s->form_rows = form_fixed(s) && is_fused(s->kernel)
@@ -1628,14 +1638,10 @@ fuglbm_status fuglbm_step_n(fuglbm_sim *s, int64_t nsteps, void *hip_stream) {
         s->taken = single ? FUGLBM_FORM_FIELDS_SINGLE : FUGLBM_FORM_FIELDS;
         return mark_done(s, st);
     }
-    if (s->lattice == FUGLBM_D3Q19) {
-        std::vector<fuglbm_sim *> fields, rest;
-        split_forms3({s}, left, false, fields, rest);
-        if (!fields.empty()) {
-            fuglbm_status rc = run_field3(s, left, st);
-            if (rc != FUGLBM_OK) return rc;
-            return mark_done(s, st);
-        }
+    if (field3_alone(s, left)) {
+        fuglbm_status rc = run_field3(s, left, st);
+        if (rc != FUGLBM_OK) return rc;
+        return mark_done(s, st);
     }
     s->taken = FUGLBM_FORM_POPULATIONS;
     // odd parity first so that graph replays start from buffer 0
@@ -1858,6 +1864,10 @@ fuglbm_status fuglbm_poke_population(fuglbm_sim *s, int32_t comp, int32_t a, int
         HIP_TRY(hipMemcpy(b + off, &value, 8, hipMemcpyHostToDevice));
     }
     return FUGLBM_OK;
+}
+
+extern "C++" {
+static void forget_sim_in_batches(const fuglbm_sim *s);
 }
 
 void fuglbm_destroy_sim(fuglbm_sim *s) {
@@ -2243,14 +2253,13 @@ fuglbm_status build_gen_batch(GenBatch &gb, const std::vector<fuglbm_sim *> &gro
     return FUGLBM_OK;
 }
 
-// A destroyed simulation's buffers may be handed to someone else, and one whose
-// tuning is set anew takes other kernels: drop every cached table (and its
-// captured graph) that refers to it.
+// A destroyed simulation's buffers may be handed to someone else: drop every
+// cached table (and its captured graph) that refers to it.
 static void forget_sim_in_batches(const fuglbm_sim *s) {
     for (auto &kv : gen_batches()) {
         GenBatch &gb = kv.second;
         for (size_t k = 0; k < gb.sims.size(); ++k) {
-            if (gb.sims[k] == s && gb.uids[k] == s->uid) {
+            if (gb.sims[k] == s) {
                 drop_gen_graph(gb);
                 gb.sims.clear();
                 gb.uids.clear();
@@ -2262,7 +2271,7 @@ static void forget_sim_in_batches(const fuglbm_sim *s) {
     for (auto &kv : batch_tables()) {
         BatchTable &bt = kv.second;
         for (size_t k = 0; k < bt.sims.size(); ++k) {
-            if (bt.sims[k] == s && bt.uids[k] == s->uid) {
+            if (bt.sims[k] == s) {
                 drop_batch_graphs(bt);
                 bt.sims.clear();
                 bt.uids.clear();
@@ -2550,7 +2559,7 @@ extern "C" fuglbm_status fuglbm_step_many(fuglbm_sim *const *sims, int32_t count
         ggroups[{s->lattice, s->fp32 ? 1 : 0, s->hc.omega != 1.0 ? 1 : 0}].push_back(s);
     for (auto &kv : ggroups) {
         std::vector<fuglbm_sim *> &fields = parts.emplace_back(), &group = parts.emplace_back();
-        split_forms3(kv.second, nsteps, true, fields, group);
+        split_forms3(kv.second, nsteps, fields, group);
         if (!fields.empty())
             tasks.push_back({group_cost(fields), [&fields, nsteps](hipStream_t to) {
                                  for (auto *s : fields) {
