@@ -1070,12 +1070,11 @@ struct Lanes {
 };
 
 // ---- copies between device and caller memory ------------------------------
-// Pinned staging shared by the read-outs of the process: a block as large as
-// the small read-outs asked for, and a ring of slots that bulk copies go through
-// while a few threads move finished slots to the caller's pages, whose first
-// touch is what a plain copy spends most of its time on.  (Copies to the device
-// take the plain way: 8.6 MB of populations 280 us, through the ring 322.)
-// Held while any simulation exists; a call that finds it in use by another
+// Pinned staging shared by the read-outs and checkpoints of the process: a
+// block as large as the small read-outs asked for, and a ring of slots that bulk
+// copies go through while a few threads move finished slots to (from) the
+// caller's pages, whose first touch is what a plain copy spends most of its
+// time on.  Held while any simulation exists; a call that finds it in use by another
 // thread copies without it.
 constexpr size_t STAGE_SLOT = (size_t)4 << 20, STAGE_WORD = 256;
 constexpr int STAGE_SLOTS = 8, STAGE_THREADS = 6;
@@ -1088,6 +1087,10 @@ constexpr size_t STAGE_SMALL_PART = STAGE_SLOT / 2;
 // us with the ring; 2.6 MB 168 / 194; 4.9 MB 314 / 317; 14 MB 854 / 624), a
 // plain copy 27 us a MB more than one through a ring that is there.
 constexpr size_t STAGE_RING_FROM = STAGE_SLOT;
+// Copies to the device go through it from this size: populations of 8.6 MB take
+// 322 us to write so and 280 plain, 35 MB 1084 and 1113, 49 MB 1431 and 1706, 189
+// MB 4554 and 6444.
+constexpr size_t STAGE_WRITE_FROM = 9 * STAGE_SLOT;
 
 struct Stage {
     std::mutex use;             // held by the call that copies through it
@@ -1164,18 +1167,25 @@ Stage &device_stage() {
     return all[dev & 63];
 }
 
-// Copies `bytes` from the device (dev) to the caller (host) through the ring, on
-// st; done when it returns.  Slots are handed to the threads in order; none
-// waits for anything but its own slot's turn, and all leave when the last slot
-// is taken or a copy fails.
-hipError_t staged_copy(Stage &g, char *host, const char *dev, size_t bytes, hipStream_t st) {
+// Copies `bytes` between the device (dev) and the caller (host) through the ring,
+// on st, to the caller if `out`; done when it returns.  Slots are handed to the
+// threads in order; none waits for anything but its own slot's turn, and all
+// leave when the last slot is taken or a copy fails.
+hipError_t staged_copy(Stage &g, char *host, char *dev, size_t bytes, bool out, hipStream_t st) {
     const int64_t n = (int64_t)((bytes + STAGE_SLOT - 1) / STAGE_SLOT);
     auto size = [&](int64_t k) { return std::min(STAGE_SLOT, bytes - (size_t)k * STAGE_SLOT); };
+    auto host_at = [&](int64_t k) { return host + (size_t)k * STAGE_SLOT; };
+    auto dev_at = [&](int64_t k) { return dev + (size_t)k * STAGE_SLOT; };
     auto dma = [&](int64_t k) {
-        return hipMemcpyAsync(g.slot(k), dev + (size_t)k * STAGE_SLOT, size(k),
-                              hipMemcpyDeviceToHost, st);
+        return out ? hipMemcpyAsync(g.slot(k), dev_at(k), size(k), hipMemcpyDeviceToHost, st)
+                   : hipMemcpyAsync(dev_at(k), g.slot(k), size(k), hipMemcpyHostToDevice, st);
     };
-    auto move = [&](int64_t k) { std::memcpy(host + (size_t)k * STAGE_SLOT, g.slot(k), size(k)); };
+    auto move = [&](int64_t k) {
+        if (out)
+            std::memcpy(host_at(k), g.slot(k), size(k));
+        else
+            std::memcpy(g.slot(k), host_at(k), size(k));
+    };
     hipError_t err = hipSuccess;
     // a thread may take slot k once `open` > k; `moved` of the ring position
     // counts the slots that it has finished there
@@ -1205,30 +1215,47 @@ hipError_t staged_copy(Stage &g, char *host, const char *dev, size_t bytes, hipS
     }
     if (nth == 0) {                        // one slot, or no thread to be had
         for (int64_t k = 0; k < n && err == hipSuccess; ++k) {
+            if (!out) move(k);
             err = dma(k);
             if (err == hipSuccess) err = hipStreamSynchronize(st);
-            if (err == hipSuccess) move(k);
+            if (out && err == hipSuccess) move(k);
         }
         return err;
     }
     auto finished = [&](int64_t k) {       // slot k's move is done
         return moved[k % STAGE_SLOTS].load(std::memory_order_acquire) > k / STAGE_SLOTS;
     };
-    int64_t issued = 0, landed = 0;
-    while (landed < n && err == hipSuccess) {
-        while (issued < n && issued < landed + STAGE_SLOTS && err == hipSuccess &&
-               (issued < STAGE_SLOTS || finished(issued - STAGE_SLOTS))) {
-            err = dma(issued);
-            if (err == hipSuccess) err = hipEventRecord(g.ev[issued % STAGE_SLOTS], st);
-            ++issued;
+    if (out) {
+        int64_t issued = 0, landed = 0;
+        while (landed < n && err == hipSuccess) {
+            while (issued < n && issued < landed + STAGE_SLOTS && err == hipSuccess &&
+                   (issued < STAGE_SLOTS || finished(issued - STAGE_SLOTS))) {
+                err = dma(issued);
+                if (err == hipSuccess) err = hipEventRecord(g.ev[issued % STAGE_SLOTS], st);
+                ++issued;
+            }
+            if (err == hipSuccess && landed < issued) {
+                err = hipEventSynchronize(g.ev[landed % STAGE_SLOTS]);
+                ++landed;
+                if (err == hipSuccess) open.store(landed, std::memory_order_release);
+            } else {
+                std::this_thread::yield();
+            }
         }
-        if (err == hipSuccess && landed < issued) {
-            err = hipEventSynchronize(g.ev[landed % STAGE_SLOTS]);
-            ++landed;
-            if (err == hipSuccess) open.store(landed, std::memory_order_release);
-        } else {
-            std::this_thread::yield();
+    } else {
+        open.store(std::min<int64_t>(n, STAGE_SLOTS));
+        for (int64_t k = 0; k < n && err == hipSuccess; ++k) {
+            while (!finished(k)) std::this_thread::yield();
+            err = dma(k);
+            if (err == hipSuccess) err = hipEventRecord(g.ev[k % STAGE_SLOTS], st);
+            // the slot of the copy issued half a ring ago may be filled again
+            const int64_t old = k - STAGE_SLOTS / 2;
+            if (old >= 0 && err == hipSuccess) {
+                err = hipEventSynchronize(g.ev[old % STAGE_SLOTS]);
+                open.store(std::min<int64_t>(n, old + 1 + STAGE_SLOTS), std::memory_order_release);
+            }
         }
+        if (err == hipSuccess) err = hipStreamSynchronize(st);
     }
     if (err != hipSuccess) stop.store(true);
     for (int k = 0; k < nth; ++k) th[k].join();
@@ -1274,7 +1301,7 @@ fuglbm_status read_parts(fuglbm_sim *s, std::initializer_list<Part> parts) {
     if (n == 0 && nl > 0)
         HIP_TRY(hipMemcpyAsync(g.word(), s->status, sizeof(word), hipMemcpyDeviceToHost, st));
     for (int k = 0; k < nl; ++k)
-        HIP_TRY(staged_copy(g, (char *)large[k].host, (const char *)large[k].dev, large[k].bytes,
+        HIP_TRY(staged_copy(g, (char *)large[k].host, (char *)large[k].dev, large[k].bytes, true,
                             st));
     if (n > 0 || nl == 0)
         HIP_TRY(launch_to_host((const double *)few[0].dev, (int64_t)(few[0].bytes / 8),
@@ -1803,7 +1830,7 @@ fuglbm_status fuglbm_read_populations(fuglbm_sim *s, double *g_out) {
         HIP_TRY(launch_planes(s->lattice, s->fp32, true, s->N, s->nx, s->ny, s->nz, p, n,
                               s->buf[s->parity], scratch, st));
         if (staged) {
-            HIP_TRY(staged_copy(g, host, scratch, bytes, st));
+            HIP_TRY(staged_copy(g, host, scratch, bytes, true, st));
         } else {
             HIP_TRY(hipStreamSynchronize(st));
             HIP_TRY(hipMemcpy(host, scratch, bytes, hipMemcpyDeviceToHost));
@@ -1826,9 +1853,17 @@ fuglbm_status fuglbm_write_populations(fuglbm_sim *s, const double *g_in, int64_
         HIP_TRY(hipMemcpy(s->buf[0], tmp.get(), (size_t)pop_bytes(s), hipMemcpyHostToDevice));
     } else {
         char *scratch = (char *)s->buf[1];
+        Stage &g = *s->stage;
+        const size_t all = (size_t)s->N * s->Q * s->ns * 8;
+        std::unique_lock<std::mutex> lk(g.use, std::defer_lock);
+        const bool staged = all >= STAGE_WRITE_FROM && lk.try_lock() && g.ring_for(all);
         fuglbm_status rc = for_planes(s, [&](int p, int n) -> fuglbm_status {
-            HIP_TRY(hipMemcpy(scratch, g_in + (size_t)p * s->ns, (size_t)n * s->ns * 8,
-                              hipMemcpyHostToDevice));
+            char *host = (char *)(g_in + (size_t)p * s->ns);
+            const size_t bytes = (size_t)n * s->ns * 8;
+            if (staged)
+                HIP_TRY(staged_copy(g, host, scratch, bytes, false, st));
+            else
+                HIP_TRY(hipMemcpy(scratch, host, bytes, hipMemcpyHostToDevice));
             HIP_TRY(launch_planes(s->lattice, s->fp32, false, s->N, s->nx, s->ny, s->nz, p, n,
                                   s->buf[0], scratch, st));
             HIP_TRY(hipStreamSynchronize(st));
