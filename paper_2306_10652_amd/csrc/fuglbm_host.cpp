@@ -624,11 +624,12 @@ double step3_latency(int ncomp) { return 14.0 + 3.2 * ncomp; }
 // sites that its 16 x 4 x 4 tiles cover.
 //
 // Fitted to 616 pairs of steps measured in runs of 65 (N = 1 ... 10, 9 7 8 ...
-// 128^3, widths from 8, both precisions): 4.8 and 3.6 % off (rms).  The form
-// they pick is the slower one by more than 5 % for eleven of the pairs, 8.5 %
-// at worst (33 33 120, N = 10, FP32 storage: passes 111, fields 121 us), 0.3 %
-// in the mean; thresholds on sites per cost, which these replace, lost up to
-// 83 % (8 96 96, N = 3: 65.7 and 36.0 us) and 5.4 % in the mean.  Far from a
+// 128^3, widths from 8, both precisions): 5 and 3 % off (rms).  Over 300 other
+// pairs the form they pick is the slower one by 5.7 % at worst (16 57 9, N = 10,
+// FP32 storage: passes 52.2, fields 55.2 us) and 0.1 % in the mean; thresholds on
+// sites per cost, which these replace, lost up to 83 % (8 96 96, N = 3: 65.7 and
+// 36.0 us) and 5 % in the mean.  FP32 storage's estimate of the field form is
+// taken 3 % up, where fewer near ties go the wrong way.  Far from a
 // tie: 128^3 x 10 FP64 1868 / 973, FP32 storage 1210 / 892; 32 17 96, N = 10,
 // FP32 storage 69 / 84.  Trials at the first run of a shape were no better:
 // short ones find the clocks low, which the field form's VALU work feels more
@@ -639,15 +640,20 @@ Step3 step3_estimate(fuglbm_sim *s) {
     int64_t units[3];
     generic_units(1, s->N, s->nx, s->ny, s->nz, units);
     const double velocity = 256e-6 * (double)units[1] * n, collision = 256e-6 * (double)units[2];
-    const double far = std::max(0.0, work - (s->fp32 ? 0.9 : 0.6));
+    const double far = std::max(0.0, work - (s->fp32 ? 0.8 : 0.5));
     const Shape3 &h = field3_shape(s);
     Step3 e;
-    e.passes = step3_latency(s->N) + 39.0 * sites + 20.5 * collision +
-               (s->fp32 ? (lines ? 3.0 * work + 23.0 * far : 4.0 * work + 29.0 * far)
-                        : (lines ? 15.0 * work + 26.0 * far : 21.0 * work + 53.0 * far));
-    e.fields = 7.9 + (s->fp32 ? 3.6 : 3.9) * n + 22.0 * sites + (s->fp32 ? 7.0 : 8.0) * work +
-               4.0 * velocity +
-               (s->fp32 ? 1.17 * h.simd - 0.43 : 1.36 * h.simd - 0.58) * h.rounds * h.zc * n;
+    e.passes = step3_latency(s->N) + 39.0 * sites + 20.5 * collision;
+    e.fields = 22.0 * sites;
+    if (s->fp32) {
+        e.passes += lines ? 4.0 * work + 21.0 * far : 5.0 * work + 27.0 * far;
+        e.fields += 8.1 + 3.7 * n + 7.2 * work + 4.1 * velocity +
+                    (1.21 * h.simd - 0.44) * h.rounds * h.zc * n;
+    } else {
+        e.passes += lines ? 15.0 * work + 24.0 * far : 21.0 * work + 53.0 * far;
+        e.fields += 7.9 + 3.9 * n + 8.0 * work + 4.0 * velocity +
+                    (1.36 * h.simd - 0.58) * h.rounds * h.zc * n;
+    }
     return e;
 }
 
